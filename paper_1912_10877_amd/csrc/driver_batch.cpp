@@ -390,7 +390,7 @@ bool z_capable(const Item& it)
     if (it.nslots)
         for (const HostPass& p : it.bwd->passes)
             if (p.standalone >= 0) return false;
-    return obs_passes_ok(it.h, it.s->n, 1, it.s->dtype);
+    return obs_passes_ok(it.h, it.s->n, 1, it.s->dtype, OBS_VECTOR);
 }
 
 // Scratch of one circuit of a z unit: psi in FP64, lambda, reverse and H psi partial sums.

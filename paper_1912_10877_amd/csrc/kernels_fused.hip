@@ -1327,31 +1327,117 @@ size_t small_circuit_lds_bytes(int n)
 }
 
 // ------------------------------------------------------------------------------ observables
-// H psi and <psi|H|psi> in tile passes: the X-mask groups of the Pauli sum are split into
-// passes whose masks lie inside one tile qubit set; a pass reads each tile of psi into LDS once
-// and adds, for every element j of the tile and group g, c_t i^{ny} (-1)^{|(j ^ x) & z|}
-// psi[j ^ x] over the group's terms (eq. expectation). Partners stay inside the tile, so the
-// state is read once per pass instead of once per group.
+// H psi and <psi|H|psi>: the terms of one X mask x add c_t i^{ny} (-1)^{|(j ^ x) & z|} psi[j ^ x]
+// to element j (eq. expectation). A thread holds 2^RB elements that differ in the top RB index
+// bits (of its tile, or of the register), so per term it takes one sign, the parity of its own
+// index bits, and the signs of its elements relative to each other are the term's class: z's top
+// bits. The host folds i^{ny}, |x & z| and the coefficient into one number, puts the terms of a
+// mask in order of class, and terms of one class are summed (one FP64 add each) before they meet
+// the amplitudes. What bounds it is the vector units: per X mask and amplitude one read of the
+// partner and two FMAs per class, per term about one instruction per amplitude (before, six, and
+// two FMAs for every term). The 25-qubit Heisenberg energy at complex64 (75 terms, 3 passes) went
+// from 295 to about 145 us a pass; reading the partners one mask ahead also in the tile passes took
+// 134 VGPRs at complex128 and was slower (24 qubits: 562 against 317 us).
 constexpr int kObsRegBits = 3;  // elements per thread: 8
 constexpr int kObsMaxTile = 12;
-struct ObsGroupT {
-    uint32_t x;  // X mask in tile-bit coordinates
-    int t0, t1;  // terms
-    int pad;
-};
-struct ObsTermT {
+// One term. flags: bits 0..2 class (z on the thread's register bits), bit 3 imaginary (odd ny),
+// bit 4 last term of its class within its X mask, bit 5 first term of its X mask.
+struct ObsRec {
     double c;
-    uint64_t zout;  // Z mask on qubits outside the tile (qubit coordinates)
-    uint32_t zin;   // Z mask on the tile (tile-bit coordinates)
-    int ny;         // number of Y factors
+    uint64_t zout;    // Z mask on qubits outside the tile (index coordinates)
+    uint32_t zin;     // Z mask on the thread's own bits (tile bits, or the register's low bits)
+    uint32_t x;       // X mask (tile bits, or index bits)
+    uint32_t xnext;   // X mask of the next one in the list (the last one: 0)
+    uint32_t flags;
 };
+static_assert(sizeof(ObsRec) == 32, "one scalar load");
+constexpr uint32_t kObsLast = 16, kObsFirst = 32;
 
-// One pass: groups[0 .. ng) over every tile. With OUT, (H psi) of these groups is written to
-// a.lam (accumulate: added to what earlier passes wrote there). The pass's part of
-// <psi|H|psi> per batch slot and tile goes to partial[b * W + pcol0 + tile].
+// orr + i oi += f p with f = s (real) or i s (imaginary), for the elements of class CLS: the
+// elements whose register bits have odd overlap with CLS take -s.
+template <int RB, int CLS, bool IMAG>
+__device__ __forceinline__ void obs_add(double s, const double2 (&p)[1 << RB], double (&orr)[1 << RB],
+                                        double (&oi)[1 << RB])
+{
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) {
+        const double f = (__builtin_popcount(r & CLS) & 1) ? -s : s;
+        if constexpr (IMAG) {
+            orr[r] = fma(-f, p[r].y, orr[r]);
+            oi[r] = fma(f, p[r].x, oi[r]);
+        } else {
+            orr[r] = fma(f, p[r].x, orr[r]);
+            oi[r] = fma(f, p[r].y, oi[r]);
+        }
+    }
+}
+
+// The records rq[0 .. nrec) (one more is readable) over a thread's elements: ethr holds the
+// thread's own index bits, base the index bits outside the tile, and fetch(x, q) reads the
+// partners of the 2^RB elements under mask x. Records come a step ahead through the scalar cache
+// and the partners of the next X mask are read while the current one is worked on.
+template <int RB, bool AHEAD, typename V, typename F>
+__device__ __forceinline__ void obs_terms(const YAO_CONST ObsRec* rq, int nrec, uint32_t ethr, uint64_t base, F fetch,
+                                          double (&orr)[1 << RB], double (&oi)[1 << RB])
+{
+    constexpr int N = 1 << RB;
+#pragma unroll
+    for (int r = 0; r < N; ++r) orr[r] = oi[r] = 0;
+    V q[N];
+    double2 p[N];
+    auto load = [&](int k) __attribute__((always_inline)) {
+        ObsRec o;
+        o.c = rq[k].c;
+        o.zout = rq[k].zout;
+        o.zin = rq[k].zin;
+        o.x = rq[k].x;
+        o.xnext = rq[k].xnext;
+        o.flags = rq[k].flags;
+        return o;
+    };
+    ObsRec cur = load(0);
+    if constexpr (AHEAD) fetch(cur.x, q);
+    double s = 0;
+    for (int k = 0; k < nrec; ++k) {
+        const ObsRec next = load(k + 1);
+        if (cur.flags & kObsFirst) {
+            if constexpr (!AHEAD) fetch(cur.x, q);
+#pragma unroll
+            for (int r = 0; r < N; ++r) p[r] = make_double2((double)q[r].x, (double)q[r].y);
+            if constexpr (AHEAD) fetch(cur.xnext, q);
+        }
+        const double cb = (__popcll(base & cur.zout) & 1) ? -cur.c : cur.c;
+        const uint64_t sign = (uint64_t)((uint32_t)__popc(ethr & cur.zin) << 31) << 32;
+        s += __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, cb) ^ sign);
+        if (cur.flags & kObsLast) {
+#define YAO_OBS_CASE(C)                                        \
+    case C: obs_add<RB, C, false>(s, p, orr, oi); break;       \
+    case 8 + C: obs_add<RB, C, true>(s, p, orr, oi); break;
+            if constexpr (RB == 3) {
+                switch (cur.flags & 15) {
+                    YAO_OBS_CASE(0) YAO_OBS_CASE(1) YAO_OBS_CASE(2) YAO_OBS_CASE(3)
+                    YAO_OBS_CASE(4) YAO_OBS_CASE(5) YAO_OBS_CASE(6) YAO_OBS_CASE(7)
+                }
+            } else if constexpr (RB == 1) {
+                switch (cur.flags & 15) { YAO_OBS_CASE(0) YAO_OBS_CASE(1) }
+            } else {
+                static_assert(RB == 2, "1 to 3 register bits");
+                switch (cur.flags & 15) { YAO_OBS_CASE(0) YAO_OBS_CASE(1) YAO_OBS_CASE(2) YAO_OBS_CASE(3) }
+            }
+#undef YAO_OBS_CASE
+            s = 0;
+        }
+        cur = next;
+    }
+}
+
+// One pass over tiles: a pass reads each tile of psi into LDS once and adds the X masks that lie
+// inside the tile's qubits, so the state is read once per pass instead of once per mask. With
+// OUT, (H psi) of these masks is written to a.lam (accumulate: added to what earlier passes wrote
+// there). The pass's part of <psi|H|psi> per batch slot and tile goes to
+// partial[b * W + pcol0 + tile].
 template <typename RP, typename RO, bool OUT>
-__global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsGroupT* __restrict__ groups, int ng,
-                                                  const ObsTermT* __restrict__ terms, int accumulate,
+__global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsRec* __restrict__ recs, int nrec, int accumulate,
                                                   double* __restrict__ partial, int pcol0, int W)
 {
     constexpr int RB = kObsRegBits, N = 1 << RB;
@@ -1369,50 +1455,24 @@ __global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsGroupT* _
 #pragma unroll
     for (int r = 0; r < N; ++r) lp[swz((uint32_t)th + (uint32_t)r * nthr)] = gp[tile_off<RB>(a, tc, r)];
     __syncthreads();
-    const YAO_CONST ObsGroupT* gq = cptr(groups);
-    const YAO_CONST ObsTermT* tq = cptr(terms);
     VO* go = (VO*)z_lam(a);
     partial = z_partial(a, partial);
-    // Table entries are read once per thread (scalar loads) and applied to the thread's 16
-    // elements: group by group, term by term.
+    const uint32_t sw = swz((uint32_t)th);
+    uint32_t sr[N];  // the swizzle is linear over XOR
+#pragma unroll
+    for (int r = 0; r < N; ++r) sr[r] = swz((uint32_t)r * nthr);
     double orr[N], oi[N];
+    obs_terms<RB, false, VP>(cptr(recs), nrec, (uint32_t)th, tc.base,
+                      [&](uint32_t x, VP (&q)[N]) __attribute__((always_inline)) {
+                          const uint32_t sx = sw ^ swz(x);
 #pragma unroll
-    for (int r = 0; r < N; ++r) orr[r] = oi[r] = 0;
-    for (int g = 0; g < ng; ++g) {
-        const uint32_t x = gq[g].x;
-        const int t0 = gq[g].t0, t1 = gq[g].t1;
-        VP p[N];
-#pragma unroll
-        for (int r = 0; r < N; ++r) p[r] = lp[swz(((uint32_t)th + (uint32_t)r * nthr) ^ x)];
-        for (int k = t0; k < t1; ++k) {
-            const uint32_t zin = tq[k].zin;
-            const int ny = tq[k].ny;
-            // i^ny and the sign of the Z bits outside the tile, folded into the coefficient.
-            double cb = (__popcll(tc.base & tq[k].zout) & 1) ? -tq[k].c : tq[k].c;
-            if (ny & 2) cb = -cb;
-            if (ny & 1) {
-#pragma unroll
-                for (int r = 0; r < N; ++r) {
-                    const uint32_t src = ((uint32_t)th + (uint32_t)r * nthr) ^ x;
-                    const double cc = (__popc(src & zin) & 1) ? -cb : cb;
-                    orr[r] = fma(-cc, (double)p[r].y, orr[r]);
-                    oi[r] = fma(cc, (double)p[r].x, oi[r]);
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < N; ++r) {
-                    const uint32_t src = ((uint32_t)th + (uint32_t)r * nthr) ^ x;
-                    const double cc = (__popc(src & zin) & 1) ? -cb : cb;
-                    orr[r] = fma(cc, (double)p[r].x, orr[r]);
-                    oi[r] = fma(cc, (double)p[r].y, oi[r]);
-                }
-            }
-        }
-    }
+                          for (int r = 0; r < N; ++r) q[r] = lp[sx ^ sr[r]];
+                      },
+                      orr, oi);
     double acc = 0;
 #pragma unroll
     for (int r = 0; r < N; ++r) {
-        const VP ae = lp[swz((uint32_t)th + (uint32_t)r * nthr)];
+        const VP ae = lp[sw ^ sr[r]];
         acc += (double)ae.x * orr[r] + (double)ae.y * oi[r];
         if constexpr (OUT) {
             if (tc.bvalid) {
@@ -1442,6 +1502,51 @@ __global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsGroupT* _
         for (int k = th; k < E; k += Bc) sum += red[k];
         const int b = (int)(blockIdx.y << c) + th;
         if (b < a.B) partial[(uint64_t)b * W + pcol0 + blockIdx.x] = sum;
+    }
+}
+
+// The whole observable in one launch for single-slot states that the L2 caches hold: a thread's
+// partners are read from global memory (a wave's partners are one or a few contiguous runs for
+// any mask). Tiles of 2^12 leave most CUs idle on such states (16 tiles at 16 qubits). The launch
+// is bound by the latency of a handful of dependent steps.
+constexpr int kObsGatherThreads = 256;
+template <typename RP, typename RO, bool OUT, int RB>
+__global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather(PassArgs a, const ObsRec* __restrict__ recs, int nrec,
+                                                                  double* __restrict__ partial)
+{
+    constexpr int N = 1 << RB;
+    using VP = vec2_t<RP>;
+    using VO = vec2_t<RO>;
+    __shared__ double red[kObsGatherThreads];
+    const int th = threadIdx.x;
+    const uint32_t gid = blockIdx.x * blockDim.x + (uint32_t)th;
+    const int top = a.n - RB;
+    const VP* gp = (const VP*)z_psi(a);
+    VO* go = (VO*)z_lam(a);
+    partial = z_partial(a, partial);
+    VP own[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) own[r] = gp[gid | ((uint32_t)r << top)];
+    double orr[N], oi[N];
+    obs_terms<RB, true, VP>(cptr(recs), nrec, gid, 0,
+                      [&](uint32_t x, VP (&q)[N]) __attribute__((always_inline)) {
+#pragma unroll
+                          for (int r = 0; r < N; ++r) q[r] = gp[(gid ^ x) ^ ((uint32_t)r << top)];
+                      },
+                      orr, oi);
+    double acc = 0;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        acc += (double)own[r].x * orr[r] + (double)own[r].y * oi[r];
+        if constexpr (OUT) go[gid | ((uint32_t)r << top)] = mkv<VO, RO>((RO)orr[r], (RO)oi[r]);
+    }
+    red[th] = acc;
+    __syncthreads();
+    if (th < 64) {  // every thread of the first wave, in a fixed order
+        double v = 0;
+        for (int i = th; i < (int)blockDim.x; i += 64) v += red[i];
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (th == 0) partial[blockIdx.x] = v;
     }
 }
 
@@ -1731,27 +1836,93 @@ namespace {
 
 struct ObsPass {
     std::vector<int> tile_qubits;
-    int g0 = 0, g1 = 0;  // groups of the pass in the device table
+    int r0 = 0, r1 = 0;  // records of the pass in the device table
 };
 struct ObsPlan {
     bool ok = false;  // false: an X mask is wider than a tile (the observable takes the
                       // per-group kernels)
+    bool gather = false;  // one launch of k_obs_gather instead of tile passes
     int c = 0, t = 0;
     std::vector<ObsPass> passes;
-    ObsGroupT* dgroups = nullptr;
-    ObsTermT* dterms = nullptr;
+    ObsRec* drecs = nullptr;
 };
-using ObsKey = std::tuple<const yao_pauli_sum*, int, int, int>;  // h, n, B, dtype
+using ObsKey = std::tuple<const yao_pauli_sum*, int, int, int, int>;  // h, n, B, dtype, use
 std::map<ObsKey, ObsPlan*> g_obs;
 std::mutex g_obs_mu;
 
-// Group the terms by X mask, then put each group in the first pass whose tile qubits can take
-// its mask (first fit, over tiles of t - c qubits that keep the lowest qubits for contiguous
+// Elements per thread of k_obs_gather: two keep every CU busy up to 17 qubits (16 qubits,
+// complex128: 9.3 us; tiles 33.6 us), above that four share the terms' signs.
+int obs_gather_reg_bits(int n)
+{
+    return n <= 17 ? 1 : 2;
+}
+
+// Whether a single-slot state takes k_obs_gather rather than npasses tile passes over nmasks X
+// masks. Up to 20 qubits it always does (20-qubit Heisenberg H psi 20 against 47 us at complex64, 31
+// against 41 us at complex128; with 30 masks in one pass both 20 and 25 us). Above, a mask costs a
+// read of the state from the caches, and a pass its own read, with an output a read and a write of
+// that too: the Heisenberg chain's H psi (9 to 11 masks a pass) takes 540 against 955 us at 25
+// qubits complex64 and 493 against 561 us at 24 qubits complex128 (22 qubits: 121 against 111 us),
+// its energy 513 against 463 us at 25 qubits complex64. States beyond the 256 MiB Infinity Cache
+// take tiles. A mask wider than a tile has no tile pass at all.
+bool obs_gathers(int n, int B, int dtype, int use, int nmasks, int npasses, bool wide)
+{
+    if (use == OBS_TILES || B != 1 || n > 31) return false;
+    if (wide || n <= 20) return true;
+    if (n > (dtype == YAO_C64 ? 25 : 24)) return false;
+    const int per_pass = use == OBS_ENERGY ? 6 : (dtype == YAO_C64 ? 14 : 10);
+    return nmasks <= per_pass * npasses;
+}
+
+// The records of the terms of the X masks xs, in order: bit q of an index is bit pos[q] of the
+// thread's coordinates (-1: outside the tile), of which the top rb of nb bits are register bits.
+void obs_records(const yao_pauli_sum* h, const std::vector<uint64_t>& xs, const std::vector<int>& pos, int nb, int rb,
+                 std::vector<ObsRec>& out)
+{
+    auto inside = [&](uint64_t m) {
+        uint32_t r = 0;
+        for (size_t q = 0; q < pos.size(); ++q)
+            if (((m >> q) & 1) && pos[q] >= 0) r |= 1u << pos[q];
+        return r;
+    };
+    uint64_t outer = 0;
+    for (size_t q = 0; q < pos.size(); ++q)
+        if (pos[q] < 0) outer |= uint64_t(1) << q;
+    const uint32_t own = (1u << (nb - rb)) - 1;
+    const size_t first = out.size();
+    for (uint64_t x : xs) {
+        const size_t at = out.size();
+        for (size_t k = 0; k < h->coef.size(); ++k) {
+            if (h->x[k] != x) continue;
+            const uint32_t z = inside(h->z[k]), xi = inside(x);
+            const int ny = __builtin_popcountll(h->x[k] & h->z[k]);
+            // Every element's source is its own index ^ x: the sign of |x & z| belongs to the term.
+            const bool neg = (((ny >> 1) ^ __builtin_popcount(xi & z)) & 1) != 0;
+            ObsRec r;
+            r.c = neg ? -h->coef[k] : h->coef[k];
+            r.zout = h->z[k] & outer;
+            r.zin = z & own;
+            r.x = xi;
+            r.xnext = 0;
+            r.flags = (z >> (nb - rb)) | ((ny & 1) ? 8u : 0u);
+            out.push_back(r);
+        }
+        std::stable_sort(out.begin() + at, out.end(), [](const ObsRec& p, const ObsRec& q) { return p.flags < q.flags; });
+        for (size_t k = at; k < out.size(); ++k)
+            if (k + 1 == out.size() || (out[k + 1].flags & 15) != (out[k].flags & 15)) out[k].flags |= kObsLast;
+        out[at].flags |= kObsFirst;
+        for (size_t k = first; k < at; ++k)
+            if (out[k].x == out[at - 1].x) out[k].xnext = out[at].x;
+    }
+}
+
+// Group the terms by X mask, then put each mask in the first pass whose tile qubits can take
+// it (first fit, over tiles of t - c qubits that keep the lowest qubits for contiguous
 // rows), and fill every pass's tile with the lowest unused qubits.
-ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype)
+ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype, int use)
 {
     std::lock_guard<std::mutex> lk(g_obs_mu);
-    const ObsKey key{h, n, B, dtype};
+    const ObsKey key{h, n, B, dtype, use};
     auto it = g_obs.find(key);
     if (it != g_obs.end()) return it->second;
     const int lb = ilog2_ceil((uint64_t)B);
@@ -1759,23 +1930,21 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype)
     const int tq = std::min(n, kObsMaxTile - c);
     const int L = std::max(0, std::min((dtype == YAO_C64 ? 4 : 3) - c, tq));
     std::vector<uint64_t> xs;
+    bool wide = false;
     for (size_t k = 0; k < h->coef.size(); ++k) {
         bool seen = false;
         for (uint64_t x : xs) seen |= x == h->x[k];
         if (!seen) xs.push_back(h->x[k]);
+        wide |= __builtin_popcountll(h->x[k]) > tq;
     }
     const uint64_t low = L > 0 ? ((uint64_t(1) << L) - 1) : 0;
     ObsPlan* P = new ObsPlan;
     P->c = c;
     P->t = c + tq;
-    for (uint64_t x : xs)
-        if (__builtin_popcountll(x) > tq) {
-            g_obs[key] = P;
-            return P;
-        }
     std::vector<uint64_t> T;                // qubits of each pass
     std::vector<std::vector<uint64_t>> gx;  // X masks of each pass
     for (uint64_t x : xs) {
+        if (wide) break;
         size_t p = 0;
         while (p < T.size() && __builtin_popcountll(T[p] | x) > tq) ++p;
         if (p == T.size()) {
@@ -1786,47 +1955,39 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype)
         T[p] |= x;
         gx[p].push_back(x);
     }
-    std::vector<ObsGroupT> hg;
-    std::vector<ObsTermT> ht;
-    for (size_t p = 0; p < T.size(); ++p) {
+    P->gather = obs_gathers(n, B, dtype, use, (int)xs.size(), (int)T.size(), wide);
+    if (wide && !P->gather) {
+        g_obs[key] = P;
+        return P;
+    }
+    std::vector<ObsRec> hr;
+    if (P->gather) {
+        std::vector<int> pos(n);
+        for (int q = 0; q < n; ++q) pos[q] = q;
+        ObsPass ps;
+        obs_records(h, xs, pos, n, obs_gather_reg_bits(n), hr);
+        ps.r1 = (int)hr.size();
+        P->passes.push_back(ps);
+    }
+    for (size_t p = 0; p < T.size() && !P->gather; ++p) {
         uint64_t Tp = T[p];
         for (int q = 0; q < n && __builtin_popcountll(Tp) < tq; ++q) Tp |= uint64_t(1) << q;
         ObsPass ps;
+        std::vector<int> pos(n, -1);
         for (int q = 0; q < n; ++q)
-            if ((Tp >> q) & 1) ps.tile_qubits.push_back(q);
-        auto to_tile = [&](uint64_t m) {
-            uint32_t r = 0;
-            for (size_t j = 0; j < ps.tile_qubits.size(); ++j)
-                if ((m >> ps.tile_qubits[j]) & 1) r |= 1u << (c + (int)j);
-            return r;
-        };
-        ps.g0 = (int)hg.size();
-        for (uint64_t x : gx[p]) {
-            ObsGroupT g;
-            g.x = to_tile(x);
-            g.t0 = (int)ht.size();
-            for (size_t k = 0; k < h->coef.size(); ++k) {
-                if (h->x[k] != x) continue;
-                ObsTermT tt;
-                tt.c = h->coef[k];
-                tt.zin = to_tile(h->z[k]);
-                tt.zout = h->z[k] & ~Tp;
-                tt.ny = __builtin_popcountll(h->x[k] & h->z[k]);
-                ht.push_back(tt);
+            if ((Tp >> q) & 1) {
+                pos[q] = c + (int)ps.tile_qubits.size();
+                ps.tile_qubits.push_back(q);
             }
-            g.t1 = (int)ht.size();
-            g.pad = 0;
-            hg.push_back(g);
-        }
-        ps.g1 = (int)hg.size();
+        ps.r0 = (int)hr.size();
+        obs_records(h, gx[p], pos, P->t, kObsRegBits, hr);
+        ps.r1 = (int)hr.size();
         P->passes.push_back(ps);
     }
-    if (hipMalloc((void**)&P->dgroups, sizeof(ObsGroupT) * (hg.size() + 1)) != hipSuccess ||
-        hipMalloc((void**)&P->dterms, sizeof(ObsTermT) * (ht.size() + 1)) != hipSuccess ||
-        hipMemcpy(P->dgroups, hg.data(), sizeof(ObsGroupT) * hg.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(P->dterms, ht.data(), sizeof(ObsTermT) * ht.size(), hipMemcpyHostToDevice) != hipSuccess) {
-        if (P->dgroups) (void)hipFree(P->dgroups);
-        if (P->dterms) (void)hipFree(P->dterms);
+    hr.push_back(ObsRec{});  // read one past the last, never used
+    if (hipMalloc((void**)&P->drecs, sizeof(ObsRec) * hr.size()) != hipSuccess ||
+        hipMemcpy(P->drecs, hr.data(), sizeof(ObsRec) * hr.size(), hipMemcpyHostToDevice) != hipSuccess) {
+        if (P->drecs) (void)hipFree(P->drecs);
         delete P;
         set_error(YAO_ENOMEM, "observable pass tables");
         return nullptr;
@@ -1836,75 +1997,98 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype)
     return P;
 }
 
-template <typename RP, typename RO, bool OUT> int obs_launch_one(const PassArgs& a, dim3 grid, int nthr, size_t lds,
-                                                                 const ObsPlan* P, const ObsPass& ps, int accumulate,
-                                                                 double* partial, int pcol0, int W)
+// The launch arguments of one pass; run(<state real>, <output real>, <with output>) per type.
+template <typename F> int obs_by_type(int dtype, int out_dtype, bool out, F run)
 {
-    YAO_TRY(set_lds_limit(k_obs_pass<RP, RO, OUT>));
-    k_obs_pass<RP, RO, OUT><<<grid, nthr, lds, stream()>>>(a, P->dgroups + ps.g0, ps.g1 - ps.g0, P->dterms, accumulate,
-                                                           partial, pcol0, W);
-    YAO_HIP(hipGetLastError());
-    return 0;
+    if (!out) return dtype == YAO_C64 ? run(float(), float(), std::false_type()) : run(double(), double(), std::false_type());
+    if (dtype == YAO_C64)
+        return out_dtype == YAO_C64 ? run(float(), float(), std::true_type()) : run(float(), double(), std::true_type());
+    return out_dtype == YAO_C64 ? run(double(), float(), std::true_type()) : run(double(), double(), std::true_type());
+}
+
+int obs_gather_threads(int n)
+{
+    return (int)std::min<uint64_t>(kObsGatherThreads, uint64_t(1) << (n - obs_gather_reg_bits(n)));
+}
+
+// Columns of energy partials per batch slot.
+int obs_columns(const ObsPlan* P, int n)
+{
+    if (P->gather) return (int)((uint64_t(1) << (n - obs_gather_reg_bits(n))) / obs_gather_threads(n));
+    return (int)P->passes.size() * (1 << (n - (P->t - P->c)));
 }
 
 }  // namespace
 
-bool obs_passes_ok(const yao_pauli_sum* h, int n, int B, int dtype)
+bool obs_passes_ok(const yao_pauli_sum* h, int n, int B, int dtype, int use)
 {
     if (n < kObsRegBits + 1) return false;
-    const ObsPlan* P = obs_plan(h, n, B, dtype);
+    const ObsPlan* P = obs_plan(h, n, B, dtype, use);
     return P && P->ok;
 }
 
 int obs_tile_qubits(const yao_pauli_sum* h, int n, int B, int dtype)
 {
-    const ObsPlan* P = obs_plan(h, n, B, dtype);
+    const ObsPlan* P = obs_plan(h, n, B, dtype, OBS_TILES);
     return P && P->ok ? P->t - P->c : 0;
 }
 
-size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype)
+size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype, int use)
 {
-    const ObsPlan* P = obs_plan(h, n, B, dtype);
+    const ObsPlan* P = obs_plan(h, n, B, dtype, use);
     if (!P || !P->ok) return 0;
-    return (size_t)B * P->passes.size() * (size_t(1) << (n - (P->t - P->c)));
+    return (size_t)B * obs_columns(P, n);
 }
 
-// H psi into out (out == nullptr: the energy only) and the pass/tile partials of the energy
-// in partial[b * W + column]; *W receives the row length.
+// H psi into out (out == nullptr: the energy only) and the partials of the energy in
+// partial[b * W + column]; *W receives the row length (OBS_TILES: per pass and tile, in tile order).
 int launch_obs_passes(const void* psi, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
-                      double* partial, int* W)
+                      double* partial, int* W, int use)
 {
-    const ObsPlan* P = obs_plan(h, n, B, dtype);
+    const ObsPlan* P = obs_plan(h, n, B, dtype, use);
     if (!P) return YAO_ENOMEM;
     if (!P->ok) return set_error(YAO_EINVAL, "observable has an X mask wider than a tile");
+    *W = obs_columns(P, n);
+    const int nz = g_zbatch.zs ? g_zbatch.nz : 1;
+    PassArgs a;
+    memset(&a, 0, sizeof(a));
+    a.psi = const_cast<void*>(psi);
+    a.lam = out;
+    a.zs = g_zbatch.zs;
+    if (P->gather) {
+        a.n = n;
+        const dim3 grid(*W, 1, nz);
+        return obs_by_type(dtype, out_dtype, out != nullptr, [&](auto rp, auto ro, auto with) {
+            using RP = decltype(rp);
+            using RO = decltype(ro);
+            constexpr bool OUT = decltype(with)::value;
+            if (obs_gather_reg_bits(n) == 1)
+                k_obs_gather<RP, RO, OUT, 1><<<grid, obs_gather_threads(n), 0, stream()>>>(a, P->drecs, P->passes[0].r1, partial);
+            else
+                k_obs_gather<RP, RO, OUT, 2><<<grid, obs_gather_threads(n), 0, stream()>>>(a, P->drecs, P->passes[0].r1, partial);
+            YAO_HIP(hipGetLastError());
+            return 0;
+        });
+    }
     const int t = P->t, c = P->c;
     const int nthr = 1 << (t - kObsRegBits);
     const int ntiles = 1 << (n - (t - c));
-    *W = (int)P->passes.size() * ntiles;
     const int Bc = 1 << c;
-    const dim3 grid(ntiles, (B + Bc - 1) / Bc, g_zbatch.zs ? g_zbatch.nz : 1);
+    const dim3 grid(ntiles, (B + Bc - 1) / Bc, nz);
     const size_t lds = ((size_t)(dtype == YAO_C64 ? 8 : 16) << t) + sizeof(double) * (size_t)grad_entries(nthr, c);
     for (size_t p = 0; p < P->passes.size(); ++p) {
         const ObsPass& ps = P->passes[p];
-        PassArgs a;
-        memset(&a, 0, sizeof(a));
-        a.psi = const_cast<void*>(psi);
-        a.lam = out;
-        a.zs = g_zbatch.zs;
         tile_args(a, n, B, c, t, ps.tile_qubits, kObsRegBits);
         const int acc = p > 0 ? 1 : 0, col = (int)p * ntiles;
-        if (!out) {
-            if (dtype == YAO_C64) YAO_TRY((obs_launch_one<float, float, false>(a, grid, nthr, lds, P, ps, 0, partial, col, *W)));
-            else YAO_TRY((obs_launch_one<double, double, false>(a, grid, nthr, lds, P, ps, 0, partial, col, *W)));
-        } else if (dtype == YAO_C64 && out_dtype == YAO_C64) {
-            YAO_TRY((obs_launch_one<float, float, true>(a, grid, nthr, lds, P, ps, acc, partial, col, *W)));
-        } else if (dtype == YAO_C64) {
-            YAO_TRY((obs_launch_one<float, double, true>(a, grid, nthr, lds, P, ps, acc, partial, col, *W)));
-        } else if (out_dtype == YAO_C64) {
-            YAO_TRY((obs_launch_one<double, float, true>(a, grid, nthr, lds, P, ps, acc, partial, col, *W)));
-        } else {
-            YAO_TRY((obs_launch_one<double, double, true>(a, grid, nthr, lds, P, ps, acc, partial, col, *W)));
-        }
+        YAO_TRY(obs_by_type(dtype, out_dtype, out != nullptr, [&](auto rp, auto ro, auto with) {
+            using RP = decltype(rp);
+            using RO = decltype(ro);
+            constexpr bool OUT = decltype(with)::value;
+            YAO_TRY(set_lds_limit(k_obs_pass<RP, RO, OUT>));
+            k_obs_pass<RP, RO, OUT><<<grid, nthr, lds, stream()>>>(a, P->drecs + ps.r0, ps.r1 - ps.r0, acc, partial, col, *W);
+            YAO_HIP(hipGetLastError());
+            return 0;
+        }));
     }
     return 0;
 }
@@ -1915,8 +2099,7 @@ void drop_obs_plans(const yao_pauli_sum* h)
     for (auto it = g_obs.begin(); it != g_obs.end();) {
         if (std::get<0>(it->first) == h) {
             (void)hipDeviceSynchronize();
-            if (it->second->dgroups) (void)hipFree(it->second->dgroups);
-            if (it->second->dterms) (void)hipFree(it->second->dterms);
+            if (it->second->drecs) (void)hipFree(it->second->drecs);
             delete it->second;
             it = g_obs.erase(it);
         } else {

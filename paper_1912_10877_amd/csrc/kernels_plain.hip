@@ -262,6 +262,27 @@ __global__ __launch_bounds__(256) void k_row_sums(const double* __restrict__ par
     if (lane == 0) sums[r] = s;
 }
 
+// The same for rows too long for one wave (a 25-qubit energy has 24576 partials: 128 us with a
+// wave, bound by the latency of its 384 dependent loads): a workgroup per row, each thread a
+// strided sum, then a fixed tree.
+constexpr int kLongRow = 1024;
+__global__ __launch_bounds__(1024) void k_long_row_sums(const double* __restrict__ partial, int nblk,
+                                                        double* __restrict__ sums)
+{
+    __shared__ double red[16];
+    const double* row = partial + (uint64_t)blockIdx.x * nblk;
+    double s = 0;
+    for (int j = threadIdx.x; j < nblk; j += 1024) s += row[j];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x < 16) {
+        s = red[threadIdx.x];
+        for (int off = 8; off > 0; off >>= 1) s += __shfl_xor(s, off, 16);
+        if (threadIdx.x == 0) sums[blockIdx.x] = s;
+    }
+}
+
 template <typename RA, typename RB>
 __global__ __launch_bounds__(kThreads) void k_convert(const vec2_t<RA>* __restrict__ a, vec2_t<RB>* __restrict__ b,
                                                       uint64_t elems)
@@ -562,7 +583,8 @@ int launch_gate(void* data, int dtype, int n, int B, const HostMat& U, const int
 
 int launch_row_sums(const double* partial, int rows, int nblk, double* sums)
 {
-    k_row_sums<<<(rows + 3) / 4, 256, 0, stream()>>>(partial, rows, nblk, sums);
+    if (nblk > kLongRow) k_long_row_sums<<<rows, 1024, 0, stream()>>>(partial, nblk, sums);
+    else k_row_sums<<<(rows + 3) / 4, 256, 0, stream()>>>(partial, rows, nblk, sums);
     YAO_HIP(hipGetLastError());
     return 0;
 }
@@ -658,14 +680,14 @@ static int finish_slot_sums(double* partial, int B, int nblk, double* energy_hos
 
 int launch_expect(const void* data, int dtype, int n, int B, yao_pauli_sum* h, double* energy_host)
 {
-    if (obs_passes_ok(h, n, B, dtype)) {
-        const size_t np = obs_partial_doubles(h, n, B, dtype);
+    if (obs_passes_ok(h, n, B, dtype, OBS_ENERGY)) {
+        const size_t np = obs_partial_doubles(h, n, B, dtype, OBS_ENERGY);
         if (!np) return YAO_ENOMEM;
         double* partial = (double*)workspace(WS_PARTIAL, sizeof(double) * np);
         if (!partial) return YAO_ENOMEM;
         int W = 0;
         const int pi = prof_begin(YAO_KF_EXPECT);
-        YAO_TRY(launch_obs_passes(data, dtype, nullptr, dtype, n, B, h, partial, &W));
+        YAO_TRY(launch_obs_passes(data, dtype, nullptr, dtype, n, B, h, partial, &W, OBS_ENERGY));
         prof_end(pi, (double)(uint64_t(1) << n) * B * (dtype == YAO_C64 ? 8 : 16),
                  (double)(uint64_t(1) << n) * B * 4.0 * (double)h->coef.size());
         return finish_slot_sums(partial, B, W, energy_host);
@@ -692,13 +714,13 @@ int launch_expect(const void* data, int dtype, int n, int B, yao_pauli_sum* h, d
 int launch_hpsi(const void* data, int dtype, void* out, int out_dtype, int n, int B, yao_pauli_sum* h,
                 double* energy_host)
 {
-    if (obs_passes_ok(h, n, B, dtype)) {
-        const size_t np = obs_partial_doubles(h, n, B, dtype);
+    if (obs_passes_ok(h, n, B, dtype, OBS_VECTOR)) {
+        const size_t np = obs_partial_doubles(h, n, B, dtype, OBS_VECTOR);
         if (!np) return YAO_ENOMEM;
         double* partial = (double*)workspace(WS_PARTIAL, sizeof(double) * np);
         if (!partial) return YAO_ENOMEM;
         int W = 0;
-        YAO_TRY(launch_obs_passes(data, dtype, out, out_dtype, n, B, h, partial, &W));
+        YAO_TRY(launch_obs_passes(data, dtype, out, out_dtype, n, B, h, partial, &W, OBS_VECTOR));
         if (!energy_host) return 0;
         return finish_slot_sums(partial, B, W, energy_host);
     }
@@ -729,7 +751,7 @@ int launch_hpsi(const void* data, int dtype, void* out, int out_dtype, int n, in
 
 size_t hpsi_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype)
 {
-    if (obs_passes_ok(h, n, B, dtype)) return std::max<size_t>(1, obs_partial_doubles(h, n, B, dtype));
+    if (obs_passes_ok(h, n, B, dtype, OBS_VECTOR)) return std::max<size_t>(1, obs_partial_doubles(h, n, B, dtype, OBS_VECTOR));
     BatchGeom bg = make_batch_geom(B);
     return (size_t)B * reduce_grid_x(uint64_t(1) << n, bg.logBc);
 }
@@ -739,9 +761,9 @@ size_t hpsi_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype)
 int launch_hpsi_dev(const void* data, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
                     double* partial, double* energy_dev)
 {
-    if (obs_passes_ok(h, n, B, dtype)) {
+    if (obs_passes_ok(h, n, B, dtype, OBS_VECTOR)) {
         int W = 0;
-        YAO_TRY(launch_obs_passes(data, dtype, out, out_dtype, n, B, h, partial, &W));
+        YAO_TRY(launch_obs_passes(data, dtype, out, out_dtype, n, B, h, partial, &W, OBS_VECTOR));
         // Over several circuits at once, their partial rows follow each other.
         return launch_row_sums(partial, B * zbatch_count(), W, energy_dev);
     }

@@ -121,14 +121,17 @@ int launch_hpsi(const void* data, int dtype, void* out, int out_dtype, int n, in
 // Doubles of partials that launch_hpsi_dev needs for this observable and state shape (builds
 // the observable's pass tables on first use; call it outside graph capture).
 size_t hpsi_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype);
-// Observables in tile passes (states of >= 5 qubits): H psi into out (nullptr: energy only),
+// Observables in tile passes or one gathering launch (states of >= 4 qubits): H psi into out (nullptr: energy only),
 // energy partials partial[b * W + column].
-bool obs_passes_ok(const yao_pauli_sum* h, int n, int B, int dtype);
-size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype);
+// What an observable's launches are for: the energy alone, H psi as well, or energies per tile (tile
+// passes even where a state takes the one-launch form, whose sums cross the top qubits).
+enum ObsUse { OBS_ENERGY = 0, OBS_VECTOR = 1, OBS_TILES = 2 };
+bool obs_passes_ok(const yao_pauli_sum* h, int n, int B, int dtype, int use);
+size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype, int use);
 // Qubits of each observable pass's tile (the non-tile qubits index the tiles, ascending).
 int obs_tile_qubits(const yao_pauli_sum* h, int n, int B, int dtype);
 int launch_obs_passes(const void* psi, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
-                      double* partial, int* W);
+                      double* partial, int* W, int use);
 void drop_obs_plans(const yao_pauli_sum* h);
 int launch_hpsi_dev(const void* data, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
                     double* partial, double* energy_dev);

@@ -227,11 +227,11 @@ int shift_grad(const yao_state* st, const yao_circuit* c, const double* params, 
             hx.coef = h->coef;
             hx.x = h->x;
             hx.z = h->z;
-            const size_t np = obs_partial_doubles(&hx, nx, 1, dtype);
+            const size_t np = obs_partial_doubles(&hx, nx, 1, dtype, OBS_TILES);
             double* part = np ? (double*)workspace(WS_PARTIAL, sizeof(double) * np) : nullptr;
             int W = 0;
             if (!part) rc = YAO_ENOMEM;
-            else rc = launch_obs_passes(reg, dtype, nullptr, dtype, nx, 1, &hx, part, &W);
+            else rc = launch_obs_passes(reg, dtype, nullptr, dtype, nx, 1, &hx, part, &W, OBS_TILES);
             if (rc == 0) {
                 const uint64_t ntiles = uint64_t(1) << (nx - obs_tile_qubits(&hx, nx, 1, dtype));
                 const int npass = (int)(W / ntiles);
