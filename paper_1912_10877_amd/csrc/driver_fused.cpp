@@ -306,7 +306,7 @@ int build_program(const Plan& P, const yao_circuit* c, const double* params, boo
                     BindRec br;
                     br.op = (int)prog.ops.size();
                     br.f0 = (int)prog.facs.size();
-                    br.mode = bwd ? 2 : (dtype == YAO_C64 ? 0 : 1);
+                    br.mode = bwd ? 2 : (dtype == YAO_C64 ? 0 : 1);  // 3 for a split diagonal, below
                     if (placeholder(hop.gate)) {
                         for (int og : (*parts)[hop.gate].gates) {
                             const GateRec& h = orig->gates[og];
@@ -372,6 +372,8 @@ int build_program(const Plan& P, const yao_circuit* c, const double* params, boo
                     // The reverse Z-generator diagonal class leaves d0 to a phase of the tile.
                     diag_high = bwd && g.k == 1 && cls == 1;
                     if (diag_high && !pdep) split_diag_phase(op.u);
+                    if (diag_high && pdep) prog.binds.back().mode = 3;
+                    if (bwd && cls == 0 && pdep) prog.binds.back().mode = 4;
                 }
                 prog.ops.push_back(op);
                 prog.pass_flops.back() += op_flops(op, bwd, diag_high) / double(uint64_t(1) << g.nctrl);

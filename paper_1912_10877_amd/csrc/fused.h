@@ -85,6 +85,17 @@ __host__ __device__ inline void split_diag_phase(double* u)
     u[7] = ri;
 }
 
+// The unit form of a rotation: [[c, i s], [i s, c]] = f [[1, i k], [i k, 1]] and diag(c + i s, c - i s) =
+// f diag(1 + i k, 1 - i k) with f = c and k = s / c, as u[1] = k, u[2] = f. A rotation by pi has
+// c = 6e-17 in FP64 and keeps its precision: each entry of the product is one rounding of a + k b,
+// whatever k is. c = 0 takes 2^-60, below the rounding of s.
+__host__ __device__ inline void split_rotation(double* u, double s)
+{
+    const double c = u[0] == 0.0 ? 0x1p-60 : u[0];
+    u[1] = s / c;
+    u[2] = c;
+}
+
 struct PGroupDesc {
     int rpos[kMaxRegBits];  // tile-bit positions of the register bits, ascending
     int lds;             // 1: a single OT_LDSK op applied in LDS; 2: a single dense block, a
@@ -150,7 +161,9 @@ void tile_geometry_tq(int n, int B, int dtype, bool backward, int tq, int* t, in
 // Parameter binding on the device: op record `op` (index in the program's records) takes the
 // one-qubit matrix U = U_{nf-1} ... U_0 of factors f0 .. f0 + nf - 1, each a gate kind with
 // its angle from params[param] (param >= 0) or theta. mode 0: U as float[8] (forward,
-// complex64), 1: U as double[8] (forward, complex128), 2: U^dagger as double[8] (reverse).
+// complex64), 1: U as double[8] (forward, complex128), 2: U^dagger as double[8] (reverse), 3: the
+// same for the Z-generator diagonal class (entry 3 as d1 / d0, entries 1 and 2 the unit form), 4:
+// the same for the X-generator Rx-like class (entries 1 and 2 the unit form; split_rotation).
 struct BindRec {
     int op, f0, nf, mode;
 };

@@ -53,6 +53,7 @@ const char* kPrelude = R"YAO(
 typedef unsigned long long u64;
 #define GLB __attribute__((address_space(1)))
 #define CST __attribute__((address_space(4)))
+#define LDS __attribute__((address_space(3)))
 __device__ __forceinline__ unsigned swz(unsigned e) { return e ^ (((e >> 4) ^ (e >> 8)) & 15u); }
 )YAO";
 
@@ -250,6 +251,25 @@ __device__ __forceinline__ double row_sum16(double v)
     v += dpp_f64<0x128>(v);
     return v;
 }
+// The unit forms of rotations about X and Z on a pair.
+__device__ __forceinline__ void rx_unit(double2& a, double2& b, double k)
+{
+    const double2 p = a, q = b;
+    a = make_double2(fma(-k, q.y, p.x), fma(k, q.x, p.y));
+    b = make_double2(fma(-k, p.y, q.x), fma(k, p.x, q.y));
+}
+__device__ __forceinline__ void rz_unit(double2& a, double2& b, double k)
+{
+    const double2 p = a, q = b;
+    a = make_double2(fma(-k, p.y, p.x), fma(k, p.x, p.y));
+    b = make_double2(fma(k, q.y, q.x), fma(-k, q.x, q.y));
+}
+// |F| < 2^-40, wave-uniform.
+__device__ __forceinline__ bool scale_low(double F)
+{
+    const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(__builtin_bit_cast(u64, F) >> 32));
+    return (hi & 0x7fffffffu) < ((1023u - 40u) << 20);
+}
 // Exchanges two double2 registers in place (v_swap_b32 on each 32-bit half), so that a swap
 // under a lane mask needs neither selects nor copies where the lanes rejoin.
 __device__ __forceinline__ void swap_d2(double2& a, double2& b)
@@ -344,8 +364,11 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     for (int r = 0; r < N; ++r)
         o << "    lp[swz(th + " << r * nthr << "u)] = v" << r << "; ll[swz(th + " << r * nthr << "u)] = w" << r << ";\n";
     o << "  }\n  __syncthreads();\n";
-    o << "  double phr = 1.0, phi = 0.0;\n";
-    // Matrix entries each op reads (cls 0: u0, u5; cls 1: u3, u7 and the phase's u0, u4;
+    o << "  double F = 1.0;\n";
+    // LDS address of a lane pair's first partial, kept in a register: the partials' own offsets are immediates.
+    if (red_lanes == 2)
+        o << "  unsigned rad = (unsigned)(u64)(LDS double*)red0 + (th >> 1) * 8u;\n  asm volatile(\"\" : \"+v\"(rad));\n";
+    // Matrix entries each op reads (cls 0 and 1: k and f as u1, u2;
     // swaps none; generic: all eight). They come through the scalar cache a batch ahead:
     // batches of up to 8 consecutive ops (at most 16 entries); at the first op of batch b the
     // kernel waits for batch b's loads and issues batch b + 1's, so records that miss the
@@ -356,8 +379,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
         for (int i = 0; i < prog.groups[g0 + g].nops; ++i) seq.push_back({g, i});
     auto coeffs = [&](int oi) -> std::vector<int> {
         const int cls = prog.ops[prog.pass_op0[p] + oi].var / RB;
-        if (cls == 0) return {0, 5};
-        if (cls == 1) return {3, 7, 0, 4};
+        if (cls <= 1) return {1, 2};
         if (cls == 2) return {};
         return {0, 1, 2, 3, 4, 5, 6, 7};
     };
@@ -386,6 +408,26 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     };
     for (size_t i = 0; i < seq.size(); ++i)
         for (int k : coeffs(op_index(i))) o << "  double U" << i << "_" << k << ";\n";
+    // Rotations run in their unit form (split_rotation): an update takes one FMA per real number where
+    // the plain matrix takes a multiply and an FMA, and their factors f collect in F, common to psi,
+    // lambda and every element (gradients take F^2). The values in registers are 1 / F of what they
+    // stand for; where |F| has come below 2^-40 they are multiplied by it, looked at after every
+    // kScaledOps rotations (their f is 6e-17 at least, so F^2 stays in range) and before lambda is
+    // rounded to the state's precision at a group's end. FP64 issue is most of a reverse pass: with
+    // 16 + 16 + 32 instructions for an Rx on 8 amplitudes in place of 16 + 64, with no phase
+    // entries left among the scalar loads (they had spilled into vector lanes behind a wait each) and
+    // the group's sums through DPP adds instead of LDS permutes, the 20-qubit depth-20 sweep's twelve
+    // passes went from 737 to 636 us.
+    constexpr int kScaledOps = 8;
+    bool scaled = false;  // F may differ from 1
+    int nscaled = 0;
+    auto emit_rescale = [&]() {
+        o << "    if (scale_low(F)) {\n";
+        for (int r = 0; r < N; ++r)
+            o << "      x" << r << ".x *= F; x" << r << ".y *= F; y" << r << ".x *= F; y" << r << ".y *= F;\n";
+        o << "      F = 1.0;\n    }\n";
+        nscaled = 0;
+    };
     size_t si = 0, bi = 0;
     emit_loads(0);
     int buf = 0;
@@ -410,7 +452,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             }
         }
         o << "    const unsigned sw = swz(ethr);\n";
-        o << "    double* red = red0 + " << buf * std::max(1, maxslots) * E << ";\n";
+        if (red_lanes != 2) o << "    double* red = red0 + " << buf * std::max(1, maxslots) * E << ";\n";
         std::vector<int> perm(N);
         for (int r = 0; r < N; ++r) {
             perm[r] = r;
@@ -454,18 +496,20 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                 if ((cls == 2 || generic) && (er[a] & rm) != (op.cval & rm)) continue;
                 pairs.push_back(a);
             }
-            // Gradient from psi and lambda before the update.
+            // Gradient from psi and lambda before the update (both are 1 / F of what they stand for).
             if (op.slot >= 0) {
                 const int gen = cls == 0 ? GEN_X : cls == 1 ? GEN_Z : op.gen;
-                o << "      double g = 0.0;\n";
+                o << "      double g" << (pairs.empty() || cond ? " = 0.0" : "") << ";\n";
                 for (int a : pairs) {
                     const std::string e = grad_expr(gen, "x" + I(perm[a]), "x" + I(perm[a | (1 << J)]), "y" + I(perm[a]),
                                                     "y" + I(perm[a | (1 << J)]));
                     if (cond) o << "      g += pc ? " << e << " : 0.0;\n";
-                    else o << "      g += " << e << ";\n";
+                    else o << "      g " << (a == pairs.front() ? "= " : "+= ") << e << ";\n";
                 }
-                if (red_lanes == 2)
-                    o << "      g += dpp_f64<0xB1>(g);\n      if ((th & 1u) == 0) red[" << nslot * E << " + (th >> 1)] = g;\n";
+                if (scaled) o << "      g *= F * F;\n";
+                if (red_lanes == 2)  // both lanes of a pair hold the sum and write it
+                    o << "      g += dpp_f64<0xB1>(g);\n      *(LDS double*)(rad + " << (buf * std::max(1, maxslots) + nslot) * E * 8
+                      << "u) = g;\n";
                 else
                     o << "      g = row_sum16(g);\n      if ((th & 15u) == 0) red[" << nslot * E << " + (th >> 4)] = g;\n";
                 ++nslot;
@@ -488,13 +532,10 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                 for (const auto& pr : {std::make_pair(X, Y), std::make_pair(LX, LY)}) {
                     const std::string& A = pr.first;
                     const std::string& B = pr.second;
-                    if (cls == 0) {  // (c a + i s b, i s a + c b)
-                        o << "      { const double2 p = " << A << ", q = " << B << "; " << A
-                          << " = make_double2(u[0] * p.x - u[5] * q.y, u[0] * p.y + u[5] * q.x); " << B
-                          << " = make_double2(u[0] * q.x - u[5] * p.y, u[0] * q.y + u[5] * p.x); }\n";
-                    } else if (cls == 1) {  // diag(1, u3 + i u7); the first entry goes to the phase
-                        o << "      { const double2 q = " << B << "; " << B
-                          << " = make_double2(u[3] * q.x - u[7] * q.y, u[3] * q.y + u[7] * q.x); }\n";
+                    if (cls == 0) {  // f (a + i k b, i k a + b)
+                        o << "      rx_unit(" << A << ", " << B << ", u[1]);\n";
+                    } else if (cls == 1) {  // f (a + i k a, b - i k b)
+                        o << "      rz_unit(" << A << ", " << B << ", u[1]);\n";
                     } else {
                         const std::string np = "make_double2(u[0] * p.x - u[4] * p.y + u[1] * q.x - u[5] * q.y, u[0] * p.y + u[4] * p.x + u[1] * q.y + u[5] * q.x)";
                         const std::string nq = "make_double2(u[2] * p.x - u[6] * p.y + u[3] * q.x - u[7] * q.y, u[2] * p.y + u[6] * p.x + u[3] * q.y + u[7] * q.x)";
@@ -504,7 +545,11 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                     }
                 }
             }
-            if (cls == 1) o << "      { const double pr = phr * u[0] - phi * u[4]; phi = phr * u[4] + phi * u[0]; phr = pr; }\n";
+            if (cls <= 1) {
+                o << "      F *= u[2];\n";
+                scaled = true;
+                if (++nscaled == kScaledOps) emit_rescale();
+            }
             o << "    }\n";
             // The op's u[k] are the prefetched U<cur>_k.
             std::string body = o.str();
@@ -517,6 +562,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             o << body;
         }
         if (nslot != G.nslot) return "";  // the record's slots and the group's list disagree
+        if (scaled) emit_rescale();
         for (int r = 0; r < N; ++r)
             o << "    lp[sw ^ " << swz_host(er[r]) << "u] = x" << perm[r] << "; ll[sw ^ " << swz_host(er[r]) << "u] = make_"
               << VL << "((" << RL << ")y" << perm[r] << ".x, (" << RL << ")y" << perm[r] << ".y);\n";
@@ -527,14 +573,14 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             o << "    for (unsigned task = th; task < " << nslot * 16 << "u; task += " << nthr << "u) {\n";
             o << "      const unsigned s = task >> 4, j = task & 15u;\n      double v = 0.0;\n";
             o << "      for (unsigned e = j; e < " << E << "u; e += 16u) v += red[s * " << E << "u + e];\n";
-            o << "      for (int off = 8; off >= 1; off >>= 1) v += __shfl_xor(v, off, 16);\n";
+            o << "      v = row_sum16(v);\n";  // the 16 lanes of a task are one DPP row
             o << "      int slot = " << G.slots[0] << ";\n";
             for (int k = 1; k < nslot; ++k) o << "      if (s == " << k << "u) slot = " << G.slots[k] << ";\n";
             o << "      if (j == 0) gpart[(u64)slot * (u64)pstride + blockIdx.x] = v;\n    }\n  }\n";
             buf ^= 1;
         }
     }
-    // Store with the accumulated phase.
+    // Store with the accumulated scale.
     o << "  unsigned sth = 0;\n";
     for (int i = 0; i < t - RB; ++i) {
         const int src = pass.store_src.empty() ? i : pass.store_src[i];
@@ -547,9 +593,8 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             if ((r >> j) & 1) v |= 1u << (pass.store_src.empty() ? t - RB + j : pass.store_src[t - RB + j]);
         o << "  { const double2 v = lp[ssw ^ " << swz_host(v) << "u]; const " << VL << " w = ll[ssw ^ " << swz_host(v)
           << "u]; const double wx = (double)w.x, wy = (double)w.y;\n";
-        o << "    gp[toff | " << U(rofs[r]) << "] = make_double2(phr * v.x - phi * v.y, phr * v.y + phi * v.x);\n";
-        o << "    gl[toff | " << U(rofs[r]) << "] = make_" << VL << "((" << RL << ")(phr * wx - phi * wy), (" << RL
-          << ")(phr * wy + phi * wx)); }\n";
+        o << "    gp[toff | " << U(rofs[r]) << "] = make_double2(F * v.x, F * v.y);\n";
+        o << "    gl[toff | " << U(rofs[r]) << "] = make_" << VL << "((" << RL << ")(F * wx), (" << RL << ")(F * wy)); }\n";
     }
     o << "}\n";
     *nthr_out = nthr;

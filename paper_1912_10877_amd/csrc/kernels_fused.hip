@@ -1614,7 +1614,7 @@ __device__ void bind_one(POp* __restrict__ ops, const BindRec br, const BindFac*
             ai[e] = ni[e];
         }
     }
-    if (br.mode == 2) {  // U^dagger
+    if (br.mode >= 2) {  // U^dagger
         double t = ar[1];
         ar[1] = ar[2];
         ar[2] = t;
@@ -1636,7 +1636,11 @@ __device__ void bind_one(POp* __restrict__ ops, const BindRec br, const BindFac*
             op.u[e] = ar[e];
             op.u[4 + e] = ai[e];
         }
-        if (br.mode == 2 && op.var / kRegBitsBwd == 1) split_diag_phase(op.u);
+        if (br.mode == 3) {
+            split_rotation(op.u, op.u[4]);
+            split_diag_phase(op.u);
+        }
+        if (br.mode == 4) split_rotation(op.u, op.u[5]);
     }
 }
 

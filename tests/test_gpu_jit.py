@@ -176,3 +176,31 @@ def test_compiled_passes_inside_batch_units():
             assert np.abs(g[i] - g_ref[0]).max() <= 1e-4 * max(1.0, float(np.abs(g_ref[0]).max())), (rep, i)
             want = oracle.forward(c, params[i], w.zero_state(13))
             assert np.abs(states[i].download() - want).max() <= tol(0, len(c.gates)), (rep, i)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("which", ["pi", "mixed"])
+def test_compiled_reverse_at_half_turns(dtype, which):
+    """Rotations by pi, whose cosine is 6e-17: the reverse passes divide it out of every rotation and
+    multiply it back, so many in a row must keep range and precision. Same bounds as above."""
+    yb.set_options(jit=1, autotune=0, fuse_width=0)
+    n = 13
+    c = w.hea_circuit(n, 3)
+    H = w.heisenberg(n)
+    params = np.full(c.nparams, np.pi)
+    if which == "mixed":
+        special = [np.pi, -np.pi, np.pi + 1e-9, 0.0, 2 * np.pi, np.pi / 2, 5 * np.pi, 0.3, 2.9]
+        params = np.array(special)[np.random.default_rng(5).integers(0, len(special), c.nparams)]
+    circ, h = yb.Circuit.from_workload(c), yb.PauliSum.from_workload(H)
+    psi0 = w.random_state(n, 1, 77)
+    s = yb.State(n, 1, dtype)
+    s.upload(psi0)
+    psi0 = s.download().astype(np.complex128)
+    l0 = yb.jit_stats()["bwd_launches"]
+    e, g, drift = yb.backward(s, circ, params, h)
+    assert yb.jit_stats()["bwd_launches"] > l0, "the reverse sweep did not use the compiled passes"
+    e_ref, g_ref, _ = oracle.adjoint(H, c, params, psi0)
+    te, tg = (1e-5, 1e-4) if dtype == 0 else (1e-10, 1e-9)
+    assert abs(e[0] - e_ref[0]) <= te
+    assert np.abs(g.ravel() - g_ref[0]).max() <= tg * max(1.0, float(np.abs(g_ref[0]).max()))
+    assert drift <= (1e-5 if dtype == 0 else 1e-12)
