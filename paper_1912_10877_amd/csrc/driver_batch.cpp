@@ -191,11 +191,17 @@ const Plan& plan_for(const yao_circuit* c, int n, int dtype, bool bwd, int tq)
     return get_plan(c, 0, (int)c->gates.size(), 1, t, cb, L, bwd, dtype == YAO_C64 ? 8 : 16);
 }
 
-int reverse_stride(int n, int dtype, int tq)
+int reverse_stride(const Plan& P)
 {
-    int t, cb, L;
-    tile_geometry_tq(n, 1, dtype, true, tq, &t, &cb, &L);
-    return std::max(1 << (n - (t - cb)), adjoint_nblk(n, 1, 1));
+    return std::max(1 << (P.n - (P.t - P.c)), adjoint_nblk(P.n, 1, 1));
+}
+
+// A circuit whose passes were compiled by earlier calls of its own keeps them in a batch.
+void use_compiled(const Plan*& P, const BoundProgram*& bp)
+{
+    if (!bp->alt) return;
+    P = bp->alt_plan;
+    bp = bp->alt;
 }
 
 struct TrialBuffers {
@@ -251,7 +257,7 @@ int autotune(const yao_circuit* c, const double* params, yao_state* s, yao_pauli
     if (nslots == 0) return 0;
     TrialBuffers tb;
     size_t gp = 1;
-    for (int tq : tile_candidates(n, dt, true)) gp = std::max(gp, (size_t)nslots * reverse_stride(n, dt, tq));
+    for (int tq : tile_candidates(n, dt, true)) gp = std::max(gp, (size_t)nslots * reverse_stride(plan_for(c, n, dt, true, tq)));
     YAO_TRY(dev_alloc((void**)&tb.psi64, 16 * N));
     YAO_TRY(dev_alloc(&tb.lam, s->elem_bytes() * N));
     YAO_TRY(dev_alloc((void**)&tb.gpart, sizeof(double) * gp));
@@ -264,7 +270,7 @@ int autotune(const yao_circuit* c, const double* params, yao_state* s, yao_pauli
         YAO_TRY(build_program(P, c, params, true, dt, prog));
         TrialProgram tp;
         YAO_TRY(tp.load(prog));
-        const int W = reverse_stride(n, dt, tq);
+        const int W = reverse_stride(P);
         double ms = 0;
         YAO_TRY(launch_fill_basis(s->data, dt, n, 1));
         YAO_TRY(launch_convert(s->data, dt, tb.psi64, YAO_C128, N));
@@ -304,12 +310,14 @@ int build_programs(Cache& C, const double* const* params, bool first)
             if (it.bf && !used.insert(it.bf).second) it.bf = nullptr;
             if (it.bf) {
                 it.fwd = &pf;
+                use_compiled(it.fwd, it.bf);
                 it.fc = sc;
                 it.fc_version = sc->version;
             }
             it.bwd = &plan_for(it.c, it.s->n, dt, true, it.tune.tq_b);
             if (it.nslots) it.bb = bound_program(*it.bwd, it.c, true, dt, nullptr, nullptr);
             if (it.bb && !used.insert(it.bb).second) it.bb = nullptr;
+            if (it.bb) use_compiled(it.bwd, it.bb);
         }
         if (!it.bf) {
             const double* fp = nullptr;
@@ -331,6 +339,11 @@ int build_programs(Cache& C, const double* const* params, bool first)
         it.bytes_b = bb;
     }
     return 0;
+}
+
+bool same_geometry(const Plan* a, const Plan* b)
+{
+    return a == b || (a->t == b->t && a->reg_bits == b->reg_bits);
 }
 
 const Program& fwd_prog(const Item& it)
@@ -481,7 +494,7 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
     }
     YAO_TRY(build_programs(C, params, true));
     for (Item& it : C.items)
-        if (!it.small) it.W = reverse_stride(it.s->n, it.s->dtype, it.tune.tq_b);
+        if (!it.small) it.W = reverse_stride(*it.bwd);
 
     // Units: circuits of one structure with bound programs together (z units), every other
     // circuit alone; the small circuits stay outside the units.
@@ -503,7 +516,8 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
                 const Item& lead = C.items[members[v][0]];
                 if ((int)members[v].size() < kZUnitMax &&
                     z_item_bytes(lead) * (members[v].size() + 1) <= kZUnitBytes && lead.W == it.W &&
-                    lead.nslots == it.nslots && same_gates(lead.c, it.c) && same_observable(lead.h, it.h)) {
+                    lead.nslots == it.nslots && same_geometry(lead.fwd, it.fwd) && same_geometry(lead.bwd, it.bwd) &&
+                    same_gates(lead.c, it.c) && same_observable(lead.h, it.h)) {
                     u = v;
                     break;
                 }

@@ -638,6 +638,31 @@ int count_slots(const yao_circuit* c)
 
 }  // namespace
 
+// A bound program on the use on which its passes are compiled: the compiled form over its own
+// geometry takes the place of plan and program where there is one.
+static void compiled_form(const Plan*& P, const BoundProgram*& bp, const yao_circuit* sc,
+                          const std::vector<FusedPart>* parts, const yao_circuit* orig, bool bwd, int dtype, int n, int B)
+{
+    if (options().tile_qubits > 0 || !jit_due(bp, B)) return;
+    if (!bp->alt_tried) {
+        bp->alt_tried = true;
+        int t = P->t, rb = P->reg_bits, L = 0;
+        if (jit_geometry(n, dtype, bwd, &t, &rb, &L)) {
+            const int slots = bwd ? reverse_slot_limit(t, 0, dtype == YAO_C64 ? 8 : 16, rb) : kMaxGroupSlots;
+            const Plan& A = get_plan_ex(sc, 0, (int)sc->gates.size(), 1, t, 0, L, bwd, rb, kMaxPassOps, slots);
+            const BoundProgram* ab = A.valid ? bound_program(A, sc, bwd, dtype, parts, orig) : nullptr;
+            if (ab && jit_compile_all(ab, A, bwd, dtype, n)) {
+                bp->alt_plan = &A;
+                bp->alt = ab;
+            }
+        }
+    }
+    if (bp->alt) {
+        P = bp->alt_plan;
+        bp = bp->alt;
+    }
+}
+
 int forward_fused_range(void* data, int dtype, int n, int B, const yao_circuit* c, const double* params, int g0, int g1)
 {
     if (g1 <= g0) return 0;
@@ -667,15 +692,16 @@ int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, con
         // Bound on the device: the circuit itself (width 0) or the structure of its fused form.
         const std::vector<FusedPart>* parts = nullptr;
         const yao_circuit* sc = width > 0 ? fused_shape(c, width, &parts) : c;
-        const Plan& P = get_plan(sc, 0, (int)sc->gates.size(), B, t, cb, L, false);
-        const BoundProgram* bp = bound_program(P, sc, false, dtype, parts, width > 0 ? c : nullptr);
+        const Plan* P = &get_plan(sc, 0, (int)sc->gates.size(), B, t, cb, L, false);
+        const BoundProgram* bp = bound_program(*P, sc, false, dtype, parts, width > 0 ? c : nullptr);
         if (bp) {
+            if (tq <= 0) compiled_form(P, bp, sc, parts, width > 0 ? c : nullptr, false, dtype, n, B);
             if (!dparams && c->nparams > 0) {
                 dparams = upload_params(params, c->nparams);
                 if (!dparams) return YAO_ENOMEM;
             }
             YAO_TRY(bind_program(bp, dparams));
-            return launch_forward_passes(P, bp->prog, bp->d, data, dtype, n, B, sc, nullptr, bp);
+            return launch_forward_passes(*P, bp->prog, bp->d, data, dtype, n, B, sc, nullptr, bp);
         }
     }
     // Host-built program for these parameters (dense fused blocks, or gates the device cannot bind).
@@ -717,7 +743,10 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     hipStream_t st = stream();
     int t, cb, L;
     tile_geometry(n, B, s->dtype, true, &t, &cb, &L);
-    const int ntiles = 1 << (n - (t - cb));
+    const Plan* P = &get_plan(c, 0, G, B, t, cb, L, true, s->dtype == YAO_C64 ? 8 : 16);
+    const BoundProgram* bp = bound_program(*P, c, true, s->dtype, nullptr, nullptr);
+    if (bp) compiled_form(P, bp, c, nullptr, nullptr, true, s->dtype, n, B);
+    const int ntiles = 1 << (n - (P->t - P->c));
     const int W = std::max(ntiles, adjoint_nblk(n, 1, B));
     const int nslots = count_slots(c);
     double* psi = (double*)workspace(WS_PSI64, elems * 16);
@@ -739,10 +768,8 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     }
     YAO_TRY(forward_sweep(s->data, s->dtype, n, B, c, params, width, options().tile_qubits, dp));
 
-    const Plan& P = get_plan(c, 0, G, B, t, cb, L, true, s->dtype == YAO_C64 ? 8 : 16);
-    const BoundProgram* bp = bound_program(P, c, true, s->dtype, nullptr, nullptr);
     Program hprog;
-    if (!bp) YAO_TRY(build_program(P, c, params, true, s->dtype, hprog));
+    if (!bp) YAO_TRY(build_program(*P, c, params, true, s->dtype, hprog));
     YAO_TRY(launch_convert(s->data, s->dtype, psi, YAO_C128, elems));
     YAO_TRY(launch_hpsi_dev(s->data, s->dtype, lam, s->dtype, n, B, h, misc, edev));
     if (nslots) YAO_TRY(launch_fill(gpartial, (size_t)nslots * B * W, 0.0));
@@ -750,7 +777,7 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     if (bp) YAO_TRY(bind_program(bp, dp));
     else YAO_TRY(upload_program(hprog, hd, WS_MAT2));
     const Program& prog = bp ? bp->prog : hprog;
-    YAO_TRY(launch_backward_passes(P, prog, bp ? bp->d : hd, c, params, psi, lam, s->dtype, n, B, gpartial, W, bp));
+    YAO_TRY(launch_backward_passes(*P, prog, bp ? bp->d : hd, c, params, psi, lam, s->dtype, n, B, gpartial, W, bp));
     if (nslots) YAO_TRY(launch_row_sums(gpartial, nslots * B, W, sums));
     const size_t nres = (size_t)B + (size_t)nslots * B;
     double* hres = (double*)pinned(WS_PARTIAL, sizeof(double) * nres);

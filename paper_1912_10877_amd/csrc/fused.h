@@ -27,10 +27,10 @@ __host__ __device__ __forceinline__ int grad_entries(int nthr, int c)
 
 // Gradient-carrying ops per register group of a reverse pass, so that the two partial buffers
 // fit in the LDS a tile of 2^t elements of psi (FP64) and lambda (lam_bytes each) leaves.
-inline int reverse_slot_limit(int t, int c, int lam_bytes)
+inline int reverse_slot_limit(int t, int c, int lam_bytes, int reg_bits = kRegBitsBwd)
 {
     const long avail = 160L * 1024 - ((long)(16 + lam_bytes) << t);
-    const long per = 2L * (long)sizeof(double) * grad_entries(1 << (t - kRegBitsBwd), c);
+    const long per = 2L * (long)sizeof(double) * grad_entries(1 << (t - reg_bits), c);
     const long s = avail > 0 ? avail / per : 0;
     return (int)(s < 1 ? 1 : (s > kMaxGroupSlots ? kMaxGroupSlots : s));
 }
@@ -294,12 +294,25 @@ struct BoundProgram {
     mutable int uses = 0;
     mutable JitPasses* jit = nullptr;
     mutable bool jit_failed = false;
+    // The same circuit over the tiles and register bits that suit compiled passes (jit_geometry),
+    // every pass of it compiled; looked for on that same use.
+    mutable int alt_uses = 0;
+    mutable bool alt_tried = false;
+    mutable const Plan* alt_plan = nullptr;
+    mutable const BoundProgram* alt = nullptr;
 };
 // The run-time compiled passes of a bound program (compiled on its options().jit-th use),
 // or nullptr. jit_has: pass p has a compiled kernel. jit_launch_forward runs it on psi with
 // the program's records (op_first: the pass's first record), over the current z batch.
 const JitPasses* jit_passes(const BoundProgram* bp, const Plan& P, bool bwd, int dtype, int n, int B);
 bool jit_has(const JitPasses* J, int p);
+// Whether bp has come to the use on which programs are compiled (counts one use).
+bool jit_due(const BoundProgram* bp, int B);
+// Tile bits, register bits and low bits kept in every tile for a compiled plan of a single-slot
+// state, where they differ from the generic kernels' (t, their register bits, L); else false.
+bool jit_geometry(int n, int dtype, bool bwd, int* t, int* reg_bits, int* L);
+// Compile every pass of bp; false unless all of them can be.
+bool jit_compile_all(const BoundProgram* bp, const Plan& P, bool bwd, int dtype, int n);
 int jit_launch_forward(const JitPasses* J, int p, void* psi, const POp* ops, int op_first, double bytes,
                        double flops);
 void jit_free(JitPasses* J);

@@ -64,7 +64,7 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
     const HostPass& pass = P.passes[p];
     const int RB = P.reg_bits, N = 1 << RB, t = P.t;
     if (P.c != 0 || pass.standalone >= 0 || prog.pass_dmat_words[p] != 0) return "";
-    if (t - RB < 0 || t - RB > 9 || (int)pass.tile_qubits.size() != t) return "";
+    if (t - RB < 0 || t - RB > 10 || (int)pass.tile_qubits.size() != t) return "";
     const int g0 = prog.pass_group0[p], ng = (int)pass.groups.size();
     for (int g = 0; g < ng; ++g)
         if (prog.groups[g0 + g].lds) return "";
@@ -298,7 +298,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     const HostPass& pass = P.passes[p];
     const int RB = P.reg_bits, N = 1 << RB, t = P.t;
     if (P.c != 0 || pass.standalone >= 0) return "";
-    if (t - RB < 4 || t - RB > 9 || (int)pass.tile_qubits.size() != t) return "";
+    if (t - RB < 4 || t - RB > 10 || (int)pass.tile_qubits.size() != t) return "";
     const int g0 = prog.pass_group0[p], ng = (int)pass.groups.size();
     int maxslots = 0;
     for (int g = 0; g < ng; ++g) {
@@ -753,6 +753,62 @@ const JitPasses* jit_passes(const BoundProgram* bp, const Plan& P, bool bwd, int
     bp->jit = jit_compile(P, bp->prog, bwd, dtype, n);
     if (!bp->jit) bp->jit_failed = true;
     return bp->jit;
+}
+
+bool jit_due(const BoundProgram* bp, int B)
+{
+    if (!bp || B != 1) return false;
+    const int when = options().jit;
+    std::lock_guard<std::mutex> lk(g_jit_mu);
+    if (bp->alt) return true;
+    if (when <= 0 || g_suspend > 0 || recording()) return false;
+    return ++bp->alt_uses >= when;
+}
+
+bool jit_compile_all(const BoundProgram* bp, const Plan& P, bool bwd, int dtype, int n)
+{
+    std::lock_guard<std::mutex> lk(g_jit_mu);
+    if (!bp->jit && !bp->jit_failed) {
+        std::vector<std::string> src;
+        std::vector<int> nthr;
+        std::vector<size_t> lds;
+        if (jit_source(P, bp->prog, bwd, dtype, n, src, nthr, lds) == (int)P.passes.size())
+            bp->jit = jit_compile(P, bp->prog, bwd, dtype, n);
+        if (!bp->jit) bp->jit_failed = true;
+    }
+    return bp->jit != nullptr;
+}
+
+// Sizes of compiled plans, from sweeps over tile and register bits. Times are of all passes of one
+// sweep of the layered ansatz, in us.
+//
+// Reverse: a pass takes as long for one tile as for a tile on every CU, so while 2^10-element tiles
+// leave CUs idle they win over 2^12 although they take more passes (15 qubits, depth 10,
+// complex64: 131 in 6 passes against 196 in 4; 17 qubits: 197 / 283; 18 qubits: 222 / 297; 14 qubits
+// complex128: 126 / 140), and with 4 elements a thread a tile still has a wave on every SIMD (8
+// elements: 17 qubits 235; 2^11 tiles: 225). At 20 qubits the vector units are busy and the larger
+// tile's fewer passes win (636 against 724 for 2^11 and 795 for 2^10); 19 qubits lie between
+// (complex64: 2^10 320, 2^11 269, 2^12 359; complex128: 253, 276).
+//
+// Forward: 8 elements a thread give two waves per SIMD where 16 give one (20 qubits complex64: 237
+// against 291; 10 qubits complex128: 19 against 25). Above 20 qubits several tiles share a CU and
+// 16 elements, with fewer exchanges through LDS, win (24 qubits complex64: 708 against 744).
+// Complex128 tiles of 2^10 win up to 18 qubits (14 qubits: 68 against 95; 18 qubits: 110 / 143).
+bool jit_geometry(int n, int dtype, bool bwd, int* t, int* reg_bits, int* L)
+{
+    *L = dtype == YAO_C64 ? 4 : 3;
+    if (bwd) {
+        if (n > 19) return false;
+        const bool mid = n == 19 && dtype == YAO_C64;
+        *t = mid ? 11 : std::min(n, 10);
+        *reg_bits = mid ? 3 : n >= 8 ? 2 : 1;
+        return true;
+    }
+    if (n > 20) return false;
+    const bool small = dtype == YAO_C128 && n > 12 && n <= 18;
+    *t = std::min(n, small ? 10 : 12);
+    *reg_bits = small || n <= 8 ? 2 : 3;
+    return true;
 }
 
 bool jit_has(const JitPasses* J, int p)

@@ -204,3 +204,26 @@ def test_compiled_reverse_at_half_turns(dtype, which):
     assert abs(e[0] - e_ref[0]) <= te
     assert np.abs(g.ravel() - g_ref[0]).max() <= tg * max(1.0, float(np.abs(g_ref[0]).max()))
     assert drift <= (1e-5 if dtype == 0 else 1e-12)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n,depth", [(5, 4), (6, 3), (7, 3), (8, 3), (9, 3), (10, 3), (11, 2), (12, 2), (17, 1), (18, 1), (19, 1), (20, 1)])
+def test_compiled_geometries(n, depth, dtype):
+    """Where the tiles and register bits of compiled plans change: a state of one tile with one, two or
+    three register bits, 2^10, 2^11 and 2^12 tiles. Same bounds as the sweeps above."""
+    yb.set_options(jit=1, autotune=0, fuse_width=1)
+    c = w.hea_circuit(n, depth)
+    H = w.heisenberg(n)
+    circ, h = yb.Circuit.from_workload(c), yb.PauliSum.from_workload(H)
+    for rep in range(2):
+        params = w.angles(1500 + 31 * rep + n, c.nparams)
+        s = yb.State(n, 1, dtype)
+        l0 = yb.jit_stats()
+        e, g, _ = yb.backward(s, circ, params, h)
+        l1 = yb.jit_stats()
+        assert l1["bwd_launches"] > l0["bwd_launches"] and l1["fwd_launches"] > l0["fwd_launches"]
+        e_ref, g_ref, _ = oracle.adjoint(H, c, params, w.zero_state(n))
+        te, tg = (1e-5, 1e-4) if dtype == 0 else (1e-10, 1e-9)
+        assert abs(e[0] - e_ref[0]) <= te, rep
+        assert np.abs(g.ravel() - g_ref[0]).max() <= tg * max(1.0, float(np.abs(g_ref[0]).max())), rep
+        assert np.abs(s.download() - oracle.forward(c, params, w.zero_state(n))).max() <= tol(dtype, len(c.gates))
