@@ -54,8 +54,90 @@ typedef unsigned long long u64;
 #define GLB __attribute__((address_space(1)))
 #define CST __attribute__((address_space(4)))
 #define LDS __attribute__((address_space(3)))
+__device__ __forceinline__ float2 flip(float2 a, unsigned s)
+{
+    return make_float2(__builtin_bit_cast(float, __builtin_bit_cast(unsigned, a.x) ^ s),
+                       __builtin_bit_cast(float, __builtin_bit_cast(unsigned, a.y) ^ s));
+}
+__device__ __forceinline__ double2 flip(double2 a, unsigned s)
+{
+    return make_double2(__builtin_bit_cast(double, __builtin_bit_cast(u64, a.x) ^ ((u64)s << 32)),
+                        __builtin_bit_cast(double, __builtin_bit_cast(u64, a.y) ^ ((u64)s << 32)));
+}
 __device__ __forceinline__ unsigned swz(unsigned e) { return e ^ (((e >> 4) ^ (e >> 8)) & 15u); }
 )YAO";
+
+// How an op changes a pair (p, q), as expressions in its matrix entries u[0..7] (re[4], im[4]): the
+// structure class of its matrix says which entries are zero; an empty expression leaves the
+// amplitude alone. neg: q changes sign. fixed: the entries do not depend on parameters, so d0 = 1 and
+// d1 = -1 of a diagonal can be relied on (Z, S, T and phase gates under any controls).
+struct PairUpdate {
+    std::string p, q;
+    bool neg = false;
+    std::vector<int> entries;  // entries of u that p and q read
+};
+PairUpdate pair_update(int type, const std::string& MK, const double* u, bool fixed)
+{
+    PairUpdate x;
+    switch (type) {
+    case OT_SWAP:
+        x.p = "q";
+        x.q = "p";
+        break;
+    case OT_DIAG:
+        if (!(fixed && u[0] == 1 && u[4] == 0)) {
+            x.p = MK + "(u[0] * p.x - u[4] * p.y, u[0] * p.y + u[4] * p.x)";
+            x.entries = {0, 4};
+        }
+        if (fixed && u[3] == -1 && u[7] == 0) {
+            x.neg = true;
+        } else {
+            x.q = MK + "(u[3] * q.x - u[7] * q.y, u[3] * q.y + u[7] * q.x)";
+            x.entries.insert(x.entries.end(), {3, 7});
+        }
+        break;
+    case OT_REAL:
+        x.p = MK + "(u[0] * p.x + u[1] * q.x, u[0] * p.y + u[1] * q.y)";
+        x.q = MK + "(u[2] * p.x + u[3] * q.x, u[2] * p.y + u[3] * q.y)";
+        x.entries = {0, 1, 2, 3};
+        break;
+    case OT_RX:  // (c a + i s b, i s a + c b), c = u[0], s = u[5]
+        x.p = MK + "(u[0] * p.x - u[5] * q.y, u[0] * p.y + u[5] * q.x)";
+        x.q = MK + "(u[0] * q.x - u[5] * p.y, u[0] * q.y + u[5] * p.x)";
+        x.entries = {0, 5};
+        break;
+    default:
+        x.p = MK + "(u[0] * p.x - u[4] * p.y + u[1] * q.x - u[5] * q.y, u[0] * p.y + u[4] * p.x + u[1] * q.y + u[5] * q.x)";
+        x.q = MK + "(u[2] * p.x - u[6] * p.y + u[3] * q.x - u[7] * q.y, u[2] * p.y + u[6] * p.x + u[3] * q.y + u[7] * q.x)";
+        x.entries = {0, 1, 2, 3, 4, 5, 6, 7};
+        break;
+    }
+    return x;
+}
+
+// The statement that applies x to registers A and B of type V, under the lane or tile predicate pc
+// when cond (sm: the sign bit where pc holds).
+std::string pair_code(const PairUpdate& x, const std::string& V, const std::string& A, const std::string& B, bool cond)
+{
+    std::string o = "      { const " + V + " p = " + A + ", q = " + B + "; ";
+    if (!x.p.empty()) o += A + " = " + (cond ? "pc ? " + x.p + " : p; " : x.p + "; ");
+    if (x.neg) o += cond ? B + " = flip(q, sm); " : B + ".x = -q.x; " + B + ".y = -q.y; ";
+    else if (!x.q.empty()) o += B + " = " + (cond ? "pc ? " + x.q + " : q; " : x.q + "; ");
+    return o + "}\n";
+}
+
+// The matrix entries of a record as doubles, in program order whatever its precision, and whether
+// parameters write them.
+void record_entries(const POp& op, bool floats, double* u)
+{
+    for (int e = 0; e < 8; ++e) u[e] = floats ? (double)((const float*)op.u)[e] : op.u[e];
+}
+std::vector<char> bound_ops(const Program& prog)
+{
+    std::vector<char> b(prog.ops.size(), 0);
+    for (const BindRec& r : prog.binds) b[r.op] = 1;
+    return b;
+}
 
 // Code of one forward pass, or an empty string when the pass is not supported.
 std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, int dtype, const std::string& name,
@@ -74,6 +156,7 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
     const int nthr = 1 << (t - RB);
     const std::string V = c64 ? "float2" : "double2", R = c64 ? "float" : "double";
     const std::string MK = c64 ? "make_float2" : "make_double2";
+    const std::vector<char> bound = bound_ops(prog);
     std::ostringstream o;
     o << "extern \"C\" __global__ void __launch_bounds__(" << nthr << ") " << name
       << "(void* psi_, const char* ops_, const char* zs_, int op_first) {\n";
@@ -155,44 +238,28 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
             const uint32_t tm = op.cmask & ~rmask, rm = op.cmask & rmask;
             // Generic class: the outer controls decide per tile; fast classes have none.
             const bool outer = cls >= kFwdGenericClass && op.omask != 0;
-            const bool swap = cls == 3;
-            const bool lane_pred = (cls == 3 || cls >= kFwdGenericClass) && tm != 0;
+            const bool lane_pred = cls >= 3 && tm != 0;
             const bool cond = lane_pred || outer;
+            double uv[8];
+            record_entries(op, c64, uv);
+            const PairUpdate pu = pair_update(op.type, MK, uv, !bound[prog.pass_op0[p] + oi]);
             o << "    {\n";
-            if (!swap) o << "      const " << R << "* u = um + " << oi * 8 << ";\n";
+            if (!pu.entries.empty()) o << "      const " << R << "* u = um + " << oi * 8 << ";\n";
             if (cond) {
                 o << "      const bool pc = true";
                 if (lane_pred) o << " && ((ethr & " << tm << "u) == " << (op.cval & tm) << "u)";
                 if (outer) o << " && ((base & " << U(op.omask) << ") == " << U(op.oval) << ")";
                 o << ";\n";
+                if (pu.neg) o << "      const unsigned sm = pc ? 0x80000000u : 0u;\n";
             }
             for (int a = 0; a < N; ++a) {
                 if ((a >> J) & 1) continue;
-                if ((cls == 3 || cls >= kFwdGenericClass) && (er[a] & rm) != (op.cval & rm)) continue;
-                const std::string X = "x" + I(perm[a]), Y = "x" + I(perm[a | (1 << J)]);
-                if (swap) {
-                    if (!cond) {
-                        std::swap(perm[a], perm[a | (1 << J)]);
-                    } else {
-                        o << "      { const " << V << " p = " << X << ", q = " << Y << "; " << X << " = pc ? q : p; " << Y
-                          << " = pc ? p : q; }\n";
-                    }
+                if (cls >= 3 && (er[a] & rm) != (op.cval & rm)) continue;
+                if (op.type == OT_SWAP && !cond) {
+                    std::swap(perm[a], perm[a | (1 << J)]);
                     continue;
                 }
-                std::string np, nq;
-                if (cls == 0) {  // (c a + i s b, i s a + c b), c = u[0], s = u[5]
-                    np = MK + "(u[0] * p.x - u[5] * q.y, u[0] * p.y + u[5] * q.x)";
-                    nq = MK + "(u[0] * q.x - u[5] * p.y, u[0] * q.y + u[5] * p.x)";
-                } else if (cls == 1) {  // diag(u0 + i u4, u3 + i u7)
-                    np = MK + "(u[0] * p.x - u[4] * p.y, u[0] * p.y + u[4] * p.x)";
-                    nq = MK + "(u[3] * q.x - u[7] * q.y, u[3] * q.y + u[7] * q.x)";
-                } else {  // dense: mr = u[0..3], mi = u[4..7], row-major
-                    np = MK + "(u[0] * p.x - u[4] * p.y + u[1] * q.x - u[5] * q.y, u[0] * p.y + u[4] * p.x + u[1] * q.y + u[5] * q.x)";
-                    nq = MK + "(u[2] * p.x - u[6] * p.y + u[3] * q.x - u[7] * q.y, u[2] * p.y + u[6] * p.x + u[3] * q.y + u[7] * q.x)";
-                }
-                o << "      { const " << V << " p = " << X << ", q = " << Y << "; ";
-                if (cond) o << X << " = pc ? " << np << " : p; " << Y << " = pc ? " << nq << " : q; }\n";
-                else o << X << " = " << np << "; " << Y << " = " << nq << "; }\n";
+                o << pair_code(pu, V, "x" + I(perm[a]), "x" + I(perm[a | (1 << J)]), cond);
             }
             o << "    }\n";
         }
@@ -369,7 +436,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     if (red_lanes == 2)
         o << "  unsigned rad = (unsigned)(u64)(LDS double*)red0 + (th >> 1) * 8u;\n  asm volatile(\"\" : \"+v\"(rad));\n";
     // Matrix entries each op reads (cls 0 and 1: k and f as u1, u2;
-    // swaps none; generic: all eight). They come through the scalar cache a batch ahead:
+    // others what their class needs). They come through the scalar cache a batch ahead:
     // batches of up to 8 consecutive ops (at most 16 entries); at the first op of batch b the
     // kernel waits for batch b's loads and issues batch b + 1's, so records that miss the
     // scalar cache are fetched while batch b computes. The loads are volatile so that the
@@ -377,11 +444,15 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     std::vector<std::pair<int, int>> seq;  // (group, op within group) in pass order
     for (int g = 0; g < ng; ++g)
         for (int i = 0; i < prog.groups[g0 + g].nops; ++i) seq.push_back({g, i});
+    const std::vector<char> bound = bound_ops(prog);
+    auto reverse_update = [&](int oi) {
+        const POp& op = prog.ops[prog.pass_op0[p] + oi];
+        return pair_update(op.type, "make_double2", op.u, !bound[prog.pass_op0[p] + oi]);
+    };
     auto coeffs = [&](int oi) -> std::vector<int> {
         const int cls = prog.ops[prog.pass_op0[p] + oi].var / RB;
         if (cls <= 1) return {1, 2};
-        if (cls == 2) return {};
-        return {0, 1, 2, 3, 4, 5, 6, 7};
+        return reverse_update(oi).entries;
     };
     auto op_index = [&](size_t i) { return prog.groups[g0 + seq[i].first].op0 + seq[i].second; };
     std::vector<size_t> batch_first;  // first op (in seq) of each batch
@@ -478,6 +549,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                 o << "    __builtin_amdgcn_sched_barrier(0);\n";
             }
             const size_t cur = si++;
+            const PairUpdate pu = reverse_update(oi);
             std::ostringstream enclosing;
             std::swap(o, enclosing);  // the op's code goes to its own stream first
             o << "    {\n";
@@ -488,6 +560,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                 if (lane_pred) o << " && ((ethr & " << tm << "u) == " << (op.cval & tm) << "u)";
                 if (outer) o << " && ((base & " << U(op.omask) << ") == " << U(op.oval) << ")";
                 o << ";\n";
+                if (pu.neg) o << "      const unsigned sm = pc ? 0x80000000u : 0u;\n";
             }
             // Pairs whose register-bit controls hold.
             std::vector<int> pairs;
@@ -517,7 +590,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             for (int a : pairs) {
                 const std::string X = "x" + I(perm[a]), Y = "x" + I(perm[a | (1 << J)]);
                 const std::string LX = "y" + I(perm[a]), LY = "y" + I(perm[a | (1 << J)]);
-                if (cls == 2) {
+                if (op.type == OT_SWAP && (cls == 2 || !cond)) {
                     if (!cond) {
                         std::swap(perm[a], perm[a | (1 << J)]);
                     } else {
@@ -537,11 +610,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                     } else if (cls == 1) {  // f (a + i k a, b - i k b)
                         o << "      rz_unit(" << A << ", " << B << ", u[1]);\n";
                     } else {
-                        const std::string np = "make_double2(u[0] * p.x - u[4] * p.y + u[1] * q.x - u[5] * q.y, u[0] * p.y + u[4] * p.x + u[1] * q.y + u[5] * q.x)";
-                        const std::string nq = "make_double2(u[2] * p.x - u[6] * p.y + u[3] * q.x - u[7] * q.y, u[2] * p.y + u[6] * p.x + u[3] * q.y + u[7] * q.x)";
-                        o << "      { const double2 p = " << A << ", q = " << B << "; ";
-                        if (cond) o << A << " = pc ? " << np << " : p; " << B << " = pc ? " << nq << " : q; }\n";
-                        else o << A << " = " << np << "; " << B << " = " << nq << "; }\n";
+                        o << pair_code(pu, "double2", A, B, cond);
                     }
                 }
             }

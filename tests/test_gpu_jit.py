@@ -227,3 +227,36 @@ def test_compiled_geometries(n, depth, dtype):
         assert abs(e[0] - e_ref[0]) <= te, rep
         assert np.abs(g.ravel() - g_ref[0]).max() <= tg * max(1.0, float(np.abs(g_ref[0]).max())), rep
         assert np.abs(s.download() - oracle.forward(c, params, w.zero_state(n))).max() <= tol(dtype, len(c.gates))
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n", [9, 14, 21])
+def test_compiled_structure_classes(n, dtype):
+    """Every kind the device binds, fixed or with an angle, with no control and with one of either value
+    near, far and (14 and 21 qubits) outside the tile, in one circuit: the compiled code of each matrix
+    class under each kind of predicate. Same bounds as the sweeps above."""
+    yb.set_options(jit=1, autotune=0, fuse_width=0)
+    gates, p = [], 0
+    for i, kind in enumerate(["X", "Y", "Z", "H", "S", "Sdag", "T", "Tdag", "Rx", "Ry", "Rz", "shift"]):
+        for j, far in enumerate([None, 1, 4, n - 1]):
+            q = (3 * i + j) % n
+            ctrls = () if far is None else ((q + far) % n,)
+            with_angle = kind in ("Rx", "Ry", "Rz", "shift")
+            gates.append(w.Gate(kind, (q,), ctrls, tuple((i + j) % 2 for _ in ctrls), param=p if with_angle else -1))
+            p += with_angle
+    c = w.Circuit(n, gates, p)
+    params = w.angles(41, p)
+    psi0 = w.random_state(n, 1, 42)
+    H = w.heisenberg(n)
+    circ, h = yb.Circuit.from_workload(c), yb.PauliSum.from_workload(H)
+    s = yb.State(n, 1, dtype)
+    s.upload(psi0)
+    l0 = yb.jit_stats()
+    e, g, _ = yb.backward(s, circ, params, h)
+    l1 = yb.jit_stats()
+    assert l1["bwd_launches"] > l0["bwd_launches"] and l1["fwd_launches"] > l0["fwd_launches"]
+    e_ref, g_ref, _ = oracle.adjoint(H, c, params, psi0)
+    te, tg = (1e-5, 1e-4) if dtype == 0 else (1e-10, 1e-9)
+    assert abs(e[0] - e_ref[0]) <= te
+    assert np.abs(g.ravel() - g_ref[0]).max() <= tg * max(1.0, float(np.abs(g_ref[0]).max()))
+    assert np.abs(s.download() - oracle.forward(c, params, psi0)).max() <= tol(dtype, len(gates))
