@@ -524,6 +524,7 @@ static std::mutex g_bound_mu;
 static void free_bound(BoundProgram* b)
 {
     jit_free(b->jit);
+    delete b->alt_plan;
     if (b->dev) (void)hipFree(b->dev);
     if (b->dbinds) (void)hipFree(b->dbinds);
     if (b->dfacs) (void)hipFree(b->dfacs);
@@ -557,6 +558,7 @@ const BoundProgram* bound_program(const Plan& P, const yao_circuit* c, bool bwd,
     b->circ = orig ? orig : c;
     g_bound[key] = b;
     if (build_program(P, c, nullptr, bwd, dtype, b->prog, parts, orig) != 0 || !b->prog.bindable) return nullptr;
+    if (P.compiled && !bwd && dtype == YAO_C64) use_real_forms(P, b->prog);
     const size_t bytes = program_blob_bytes(b->prog);
     std::vector<char> host(bytes);
     const size_t nb = std::max<size_t>(1, b->prog.binds.size()), nf = std::max<size_t>(1, b->prog.facs.size());
@@ -649,12 +651,11 @@ static void compiled_form(const Plan*& P, const BoundProgram*& bp, const yao_cir
         int t = P->t, rb = P->reg_bits, L = 0;
         if (jit_geometry(n, dtype, bwd, &t, &rb, &L)) {
             const int slots = bwd ? reverse_slot_limit(t, 0, dtype == YAO_C64 ? 8 : 16, rb) : kMaxGroupSlots;
-            const Plan& A = get_plan_ex(sc, 0, (int)sc->gates.size(), 1, t, 0, L, bwd, rb, kMaxPassOps, slots);
+            bp->alt_plan = new Plan(get_plan_ex(sc, 0, (int)sc->gates.size(), 1, t, 0, L, bwd, rb, kMaxPassOps, slots));
+            bp->alt_plan->compiled = true;
+            const Plan& A = *bp->alt_plan;
             const BoundProgram* ab = A.valid ? bound_program(A, sc, bwd, dtype, parts, orig) : nullptr;
-            if (ab && jit_compile_all(ab, A, bwd, dtype, n)) {
-                bp->alt_plan = &A;
-                bp->alt = ab;
-            }
+            if (ab && jit_compile_all(ab, A, bwd, dtype, n)) bp->alt = ab;
         }
     }
     if (bp->alt) {

@@ -96,6 +96,19 @@ __host__ __device__ inline void split_rotation(double* u, double s)
     u[2] = c;
 }
 
+// A 2 x 2 complex matrix (re[4], im[4], row-major) on a pair (p, q) as the real 4 x 4 matrix on (re p,
+// im p, re q, im q), row-major.
+__host__ __device__ inline void real_form(const double* re, const double* im, float* w)
+{
+    for (int i = 0; i < 2; ++i)
+        for (int k = 0; k < 2; ++k) {
+            float* b = w + 8 * i + 2 * k;
+            b[0] = b[5] = (float)re[2 * i + k];
+            b[1] = (float)-im[2 * i + k];
+            b[4] = (float)im[2 * i + k];
+        }
+}
+
 struct PGroupDesc {
     int rpos[kMaxRegBits];  // tile-bit positions of the register bits, ascending
     int lds;             // 1: a single OT_LDSK op applied in LDS; 2: a single dense block, a
@@ -143,6 +156,7 @@ struct Plan {
     bool reverse = false;
     bool valid = true;   // false: the layout could not be put back (never expected)
     int max_slots = kMaxGroupSlots;  // gradient-carrying ops per register group
+    bool compiled = false;  // for compiled passes alone, which read some records in forms of their own
     std::vector<HostOp> ops;        // in application order (reverse order of gates if reverse)
     std::vector<HostPass> passes;
 };
@@ -163,7 +177,8 @@ void tile_geometry_tq(int n, int B, int dtype, bool backward, int tq, int* t, in
 // its angle from params[param] (param >= 0) or theta. mode 0: U as float[8] (forward,
 // complex64), 1: U as double[8] (forward, complex128), 2: U^dagger as double[8] (reverse), 3: the
 // same for the Z-generator diagonal class (entry 3 as d1 / d0, entries 1 and 2 the unit form), 4:
-// the same for the X-generator Rx-like class (entries 1 and 2 the unit form; split_rotation).
+// the same for the X-generator Rx-like class (entries 1 and 2 the unit form; split_rotation), 5: the
+// real 4 x 4 form of U as float[16] (compiled complex64 forward plans; real_form).
 struct BindRec {
     int op, f0, nf, mode;
 };
@@ -298,7 +313,7 @@ struct BoundProgram {
     // every pass of it compiled; looked for on that same use.
     mutable int alt_uses = 0;
     mutable bool alt_tried = false;
-    mutable const Plan* alt_plan = nullptr;
+    mutable Plan* alt_plan = nullptr;  // owned
     mutable const BoundProgram* alt = nullptr;
 };
 // The run-time compiled passes of a bound program (compiled on its options().jit-th use),
@@ -308,8 +323,12 @@ const JitPasses* jit_passes(const BoundProgram* bp, const Plan& P, bool bwd, int
 bool jit_has(const JitPasses* J, int p);
 // Whether bp has come to the use on which programs are compiled (counts one use).
 bool jit_due(const BoundProgram* bp, int B);
+// Uncontrolled dense ops of a compiled complex64 forward plan get their records in real form.
+bool takes_real_form(const Plan& P, const POp& op);
+void use_real_forms(const Plan& P, Program& prog);
 // Tile bits, register bits and low bits kept in every tile for a compiled plan of a single-slot
-// state, where they differ from the generic kernels' (t, their register bits, L); else false.
+// state; t and reg_bits come in as the generic kernels'. False where a plan of its own would be no
+// different.
 bool jit_geometry(int n, int dtype, bool bwd, int* t, int* reg_bits, int* L);
 // Compile every pass of bp; false unless all of them can be.
 bool jit_compile_all(const BoundProgram* bp, const Plan& P, bool bwd, int dtype, int n);

@@ -54,6 +54,7 @@ typedef unsigned long long u64;
 #define GLB __attribute__((address_space(1)))
 #define CST __attribute__((address_space(4)))
 #define LDS __attribute__((address_space(3)))
+typedef float v4f __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ float2 flip(float2 a, unsigned s)
 {
     return make_float2(__builtin_bit_cast(float, __builtin_bit_cast(unsigned, a.x) ^ s),
@@ -140,6 +141,15 @@ std::vector<char> bound_ops(const Program& prog)
 }
 
 // Code of one forward pass, or an empty string when the pass is not supported.
+//
+// Vector issue bounds complex64 passes of a few gates a qubit (8 instructions an amplitude for a
+// merged gate; the 25-qubit depth-20 ansatz needs 3.4 ms of them). An uncontrolled dense gate of a
+// compiled plan runs on the matrix cores instead, as the real 4 x 4 product of v_mfma_f32_4x4x1: a
+// lane's own pair (re p, im p, re q, im q) is its column of B and D, so no amplitude moves, and 4
+// instructions of 8 cycles replace 16 of 4. (Rx-like and diagonal gates cost both the same. Two gates
+// as one complex 4 x 4 product cost the same as two real ones, and counters show the matrix and
+// vector instructions of a SIMD's waves taking turns.) 25 qubits, depth 20: 4.52 to 4.30 ms, now bound
+// by the exchanges through LDS; the 20-qubit sweep 237 to 219 us.
 std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, int dtype, const std::string& name,
                              int* nthr_out, size_t* lds_out)
 {
@@ -158,14 +168,18 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
     const std::string MK = c64 ? "make_float2" : "make_double2";
     const std::vector<char> bound = bound_ops(prog);
     std::ostringstream o;
-    o << "extern \"C\" __global__ void __launch_bounds__(" << nthr << ") " << name
+    // With at most 256 registers a lane the compiler gives matrix instructions vector registers (with
+    // accumulation registers every result is moved before its use).
+    const std::string waves = c64 && P.compiled ? "__attribute__((amdgpu_waves_per_eu(" + I(RB > 3 ? 3 : 4) + "))) " : "";
+    o << "extern \"C\" __global__ void __launch_bounds__(" << nthr << ") " << waves << name
       << "(void* psi_, const char* ops_, const char* zs_, int op_first) {\n";
     // LDS sized at compile time (static allocations may exceed the 64 KiB of a dynamic one):
     // the tile, and the pass's one-qubit matrices (8 entries per record), copied in with the
     // tile so that the ops read them from LDS instead of waiting on a scalar load each.
     const int nrec = prog.pass_nops[p];
+    const int UM = c64 && P.compiled ? 16 : 8;  // reals of a record's matrix in LDS
     o << "  __shared__ __align__(16) " << V << " lp[" << (1 << t) << "];\n";
-    o << "  __shared__ __align__(16) " << R << " um[" << std::max(1, nrec) * 8 << "];\n";
+    o << "  __shared__ __align__(16) " << R << " um[" << std::max(1, nrec) * UM << "];\n";
     o << "  const unsigned th = threadIdx.x;\n";
     o << "  GLB " << V << "* gp = (GLB " << V << "*)psi_;\n  const CST char* ops = (const CST char*)ops_;\n";
     o << "  if (zs_) { const CST u64* z = (const CST u64*)(zs_ + 32 * blockIdx.z); gp = (GLB " << V
@@ -196,7 +210,7 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
     o << "  {\n";
     for (int r = 0; r < N; ++r) o << "    const " << V << " v" << r << " = gp[toff | " << U(rofs[r]) << "];\n";
     {
-        const int W = c64 ? 8 : 16;  // dwords of a record's matrix
+        const int W = c64 ? UM : 16;  // dwords of a record's matrix
         o << "    { const CST unsigned* src = (const CST unsigned*)ops; unsigned* dst = (unsigned*)um;\n"
           << "      for (unsigned i = th; i < " << nrec * W << "u; i += " << nthr << "u) dst[i] = src[(i / " << W << "u) * "
           << sizeof(POp) / 4 << "u + " << offsetof(POp, u) / 4 << "u + i % " << W << "u]; }\n";
@@ -236,6 +250,22 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
             const int J = op.rpos;
             const int cls = op.var / RB;
             const uint32_t tm = op.cmask & ~rmask, rm = op.cmask & rmask;
+            if (c64 && takes_real_form(P, op)) {
+                o << "    {\n      const v4f w = *(const v4f*)(um + " << oi * UM << " + (th & 3u) * 4u);\n";
+                std::vector<std::pair<int, int>> pr;
+                for (int a = 0; a < N; ++a)
+                    if (!((a >> J) & 1)) pr.push_back({perm[a], perm[a | (1 << J)]});
+                for (size_t q = 0; q < pr.size(); ++q) o << "      v4f r" << q << " = {0.f, 0.f, 0.f, 0.f};\n";
+                for (int k = 0; k < 4; ++k)
+                    for (size_t q = 0; q < pr.size(); ++q)
+                        o << "      r" << q << " = __builtin_amdgcn_mfma_f32_4x4x1f32(w[" << k << "], x"
+                          << (k < 2 ? pr[q].first : pr[q].second) << (k & 1 ? ".y" : ".x") << ", r" << q << ", 0, 0, 0);\n";
+                for (size_t q = 0; q < pr.size(); ++q)
+                    o << "      x" << pr[q].first << " = make_float2(r" << q << "[0], r" << q << "[1]); x" << pr[q].second
+                      << " = make_float2(r" << q << "[2], r" << q << "[3]);\n";
+                o << "    }\n";
+                continue;
+            }
             // Generic class: the outer controls decide per tile; fast classes have none.
             const bool outer = cls >= kFwdGenericClass && op.omask != 0;
             const bool lane_pred = cls >= 3 && tm != 0;
@@ -244,7 +274,7 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
             record_entries(op, c64, uv);
             const PairUpdate pu = pair_update(op.type, MK, uv, !bound[prog.pass_op0[p] + oi]);
             o << "    {\n";
-            if (!pu.entries.empty()) o << "      const " << R << "* u = um + " << oi * 8 << ";\n";
+            if (!pu.entries.empty()) o << "      const " << R << "* u = um + " << oi * UM << ";\n";
             if (cond) {
                 o << "      const bool pc = true";
                 if (lane_pred) o << " && ((ethr & " << tm << "u) == " << (op.cval & tm) << "u)";
@@ -686,6 +716,25 @@ void report_failure(const char* what, const std::string& detail)
 
 }  // namespace
 
+bool takes_real_form(const Plan& P, const POp& op)
+{
+    // Whole waves; class 2: dense without controls.
+    return P.compiled && P.t - P.reg_bits >= 6 && op.k == 1 && op.var / P.reg_bits == 2;
+}
+
+void use_real_forms(const Plan& P, Program& prog)
+{
+    std::vector<char> bound = bound_ops(prog);
+    for (size_t i = 0; i < prog.ops.size(); ++i) {
+        POp& op = prog.ops[i];
+        if (!takes_real_form(P, op) || bound[i]) continue;
+        const double* m = prog.mats.data() + op.mat;  // the pool keeps the FP64 entries: re[4], im[4]
+        real_form(m, m + 4, (float*)op.u);
+    }
+    for (BindRec& b : prog.binds)
+        if (takes_real_form(P, prog.ops[b.op])) b.mode = 5;
+}
+
 struct JitPasses {
     std::vector<hipModule_t> mod;   // per pass
     std::vector<hipFunction_t> fn;  // per pass; null: the generic kernel
@@ -873,7 +922,7 @@ bool jit_geometry(int n, int dtype, bool bwd, int* t, int* reg_bits, int* L)
         *reg_bits = mid ? 3 : n >= 8 ? 2 : 1;
         return true;
     }
-    if (n > 20) return false;
+    if (n > 20) return dtype == YAO_C64;  // the generic kernels' sizes, records in real form
     const bool small = dtype == YAO_C128 && n > 12 && n <= 18;
     *t = std::min(n, small ? 10 : 12);
     *reg_bits = small || n <= 8 ? 2 : 3;
@@ -914,11 +963,13 @@ int jit_selfcheck(const yao_circuit* c, int dtype, int reverse, int tile_qubits,
     int t, cb, L;
     tile_geometry_tq(n, 1, dtype, bwd, tile_qubits, &t, &cb, &L);
     if (t - cb < kMaxRegBits + 1) return set_error(YAO_EINVAL, "circuit too small for tile passes");
-    const Plan& P = get_plan(c, 0, (int)c->gates.size(), 1, t, cb, L, bwd, dtype == YAO_C64 ? 8 : 16);
+    Plan P = get_plan(c, 0, (int)c->gates.size(), 1, t, cb, L, bwd, dtype == YAO_C64 ? 8 : 16);
     if (!P.valid) return set_error(YAO_EINVAL, "pass plan could not restore the qubit layout");
+    P.compiled = true;
     Program prog;
     YAO_TRY(build_program(P, c, nullptr, bwd, dtype, prog));
     if (!prog.bindable) return set_error(YAO_EINVAL, "circuit cannot be bound on the device");
+    if (!bwd && dtype == YAO_C64) use_real_forms(P, prog);
     std::vector<std::string> src, logs;
     std::vector<int> nthr;
     std::vector<size_t> lds;

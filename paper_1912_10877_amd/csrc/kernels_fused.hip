@@ -1614,7 +1614,7 @@ __device__ void bind_one(POp* __restrict__ ops, const BindRec br, const BindFac*
             ai[e] = ni[e];
         }
     }
-    if (br.mode >= 2) {  // U^dagger
+    if (br.mode >= 2 && br.mode <= 4) {  // U^dagger
         double t = ar[1];
         ar[1] = ar[2];
         ar[2] = t;
@@ -1625,6 +1625,10 @@ __device__ void bind_one(POp* __restrict__ ops, const BindRec br, const BindFac*
         ai[3] = -ai[3];
     }
     POp& op = ops[br.op];
+    if (br.mode == 5) {
+        real_form(ar, ai, (float*)op.u);
+        return;
+    }
     if (br.mode == 0) {
         float* u = (float*)op.u;
         for (int e = 0; e < 4; ++e) {

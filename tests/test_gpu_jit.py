@@ -260,3 +260,33 @@ def test_compiled_structure_classes(n, dtype):
     assert abs(e[0] - e_ref[0]) <= te
     assert np.abs(g.ravel() - g_ref[0]).max() <= tg * max(1.0, float(np.abs(g_ref[0]).max()))
     assert np.abs(s.download() - oracle.forward(c, params, psi0)).max() <= tol(dtype, len(gates))
+
+
+@pytest.mark.parametrize("n", [9, 10, 13, 21])
+def test_compiled_dense_gates_on_matrix_cores(n):
+    """Merged (angle-dependent) and fixed dense gates of complex64 forward passes as real 4 x 4 products:
+    tiles of one wave (9 qubits, 8 amplitudes a thread) and more, with entries of every sign. Unitarity
+    and the amplitudes to the bound above."""
+    yb.set_options(jit=1, autotune=0, fuse_width=1)
+    rng = np.random.default_rng(7)
+    gates, p = [], 0
+    for layer in range(3):
+        for q in range(n):
+            if (q + layer) % 2:
+                gates.append(w.Gate("dense", (q,), G=w.haar_su2(rng) * np.exp(1j * rng.uniform(0, 6))))
+            else:
+                for kind in ("Ry", "Rz", "Rx"):
+                    gates.append(w.Gate(kind, (q,), param=p))
+                    p += 1
+        gates += [w.Gate("X", ((q + 1) % n,), (q,)) for q in range(n)]
+    c = w.Circuit(n, gates, p)
+    circ = yb.Circuit.from_workload(c)
+    psi0 = w.random_state(n, 1, 5)
+    for rep in range(2):
+        params = w.angles(50 + rep, p)
+        s = yb.State(n, 1, 0)
+        s.upload(psi0)
+        l0 = yb.jit_stats()["fwd_launches"]
+        yb.forward(s, circ, params)
+        assert yb.jit_stats()["fwd_launches"] > l0
+        assert np.abs(s.download() - oracle.forward(c, params, psi0)).max() <= tol(0, len(gates))
