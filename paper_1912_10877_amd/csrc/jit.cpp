@@ -40,11 +40,85 @@ std::string U(unsigned long long v)
     return std::to_string(v) + "ull";
 }
 
-// Bank swizzle of LDS tile rows, the generic kernels' layout (linear over GF(2): the swizzle
-// of a ^ b is the XOR of the swizzles).
+// Bank swizzle of the LDS tile, linear over GF(2): row e lies at e with its low 5 bits (the banks of
+// 8-byte rows; the low 4 are those of 16-byte rows) XORed with a column per high bit. The columns were
+// searched so that the tile bits outside a register group, any 2 to 4 bits taken out of 12 (780 of
+// 781 choices), hold 5 whose images are independent: lane_order puts those on the lowest lanes, so
+// that a wave's accesses meet every bank once. With the generic kernels' swizzle and the tile bits in
+// order, 41 % of the LDS cycles of a 25-qubit forward pass were bank conflicts.
 uint32_t swz_host(uint32_t e)
 {
-    return e ^ (((e >> 4) ^ (e >> 8)) & 15u);
+    static const uint32_t col[8] = {26, 7, 22, 21, 3, 28, 13, 19};
+    uint32_t v = e;
+    for (int b = 5; b < 13; ++b)
+        if ((e >> b) & 1) v ^= col[b - 5];
+    return v;
+}
+
+int gf2_rank(std::vector<uint32_t> v)
+{
+    int r = 0;
+    for (size_t i = 0; i < v.size(); ++i) {
+        if (!v[i]) continue;
+        ++r;
+        const uint32_t low = v[i] & (0u - v[i]);
+        for (size_t j = i + 1; j < v.size(); ++j)
+            if (v[j] & low) v[j] ^= v[i];
+    }
+    return r;
+}
+
+// The tile bits outside the mask regs in the order of the thread bits that address them: 4 whose
+// images are independent in the low 4 bits, then one that adds the fifth bank bit, then the rest (the
+// choice of most independent images where no such 5 exist).
+std::vector<int> lane_order(int t, uint32_t regs)
+{
+    std::vector<int> bits;
+    for (int b = 0; b < t; ++b)
+        if (!((regs >> b) & 1)) bits.push_back(b);
+    const int m = (int)bits.size();
+    if (m < 4) return bits;
+    std::vector<int> best = bits;
+    int best_rank = -1;
+    for (uint32_t pick = 0; pick < (1u << m) && best_rank < 9; ++pick) {
+        if (__builtin_popcount(pick) != 4) continue;
+        std::vector<int> order;
+        std::vector<uint32_t> low4, low5;
+        for (int i = 0; i < m; ++i)
+            if ((pick >> i) & 1) {
+                order.push_back(bits[i]);
+                low4.push_back(swz_host(1u << bits[i]) & 15u);
+                low5.push_back(swz_host(1u << bits[i]) & 31u);
+            }
+        const int r4 = gf2_rank(low4);
+        int fifth = -1, r5 = gf2_rank(low5);
+        for (int i = 0; i < m && fifth < 0; ++i) {
+            if ((pick >> i) & 1) continue;
+            std::vector<uint32_t> v = low5;
+            v.push_back(swz_host(1u << bits[i]) & 31u);
+            if (gf2_rank(v) > r5) fifth = bits[i];
+        }
+        if (fifth >= 0) {
+            order.push_back(fifth);
+            ++r5;
+        }
+        if (r4 + r5 <= best_rank) continue;
+        best_rank = r4 + r5;
+        for (int b : bits)
+            if (std::find(order.begin(), order.end(), b) == order.end()) order.push_back(b);
+        best = order;
+    }
+    return best;
+}
+
+// Code that declares `name` as the LDS position of the thread's tile bits: thread bit k on tile bit at[k].
+std::string thread_position(const std::string& name, const std::vector<int>& at)
+{
+    std::string o = "unsigned " + name + " = 0;";
+    for (size_t k = 0; k < at.size(); ++k)
+        o += " " + name + " ^= (0u - ((th >> " + std::to_string(k) + ") & 1u)) & " +
+             std::to_string(swz_host(1u << at[k])) + "u;";
+    return o + "\n";
 }
 
 // Pointers in the generated code carry their address space: global memory for states and
@@ -65,7 +139,6 @@ __device__ __forceinline__ double2 flip(double2 a, unsigned s)
     return make_double2(__builtin_bit_cast(double, __builtin_bit_cast(u64, a.x) ^ ((u64)s << 32)),
                         __builtin_bit_cast(double, __builtin_bit_cast(u64, a.y) ^ ((u64)s << 32)));
 }
-__device__ __forceinline__ unsigned swz(unsigned e) { return e ^ (((e >> 4) ^ (e >> 8)) & 15u); }
 )YAO";
 
 // How an op changes a pair (p, q), as expressions in its matrix entries u[0..7] (re[4], im[4]): the
@@ -215,7 +288,15 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
           << "      for (unsigned i = th; i < " << nrec * W << "u; i += " << nthr << "u) dst[i] = src[(i / " << W << "u) * "
           << sizeof(POp) / 4 << "u + " << offsetof(POp, u) / 4 << "u + i % " << W << "u]; }\n";
     }
-    for (int r = 0; r < N; ++r) o << "    lp[swz(th + " << r * nthr << "u)] = v" << r << ";\n";
+    std::vector<int> thread_bits(t - RB);
+    for (int k = 0; k < t - RB; ++k) thread_bits[k] = k;
+    // Positions are kept in bytes, one XOR an access.
+    const int es = c64 ? 8 : 16;
+    auto at = [&](const std::string& pos, uint32_t e) {
+        return "*(LDS " + V + "*)((LDS char*)lp + (" + pos + " ^ " + I((long long)swz_host(e) * es) + "u))";
+    };
+    o << "    " << thread_position("lpos", thread_bits) << "    lpos *= " << es << "u;\n";
+    for (int r = 0; r < N; ++r) o << "    " << at("lpos", (uint32_t)r * nthr) << " = v" << r << ";\n";
     o << "  }\n  __syncthreads();\n";
     // Register groups (records are addressed relative to the pass's first record).
     for (int g = 0; g < ng; ++g) {
@@ -229,20 +310,14 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
                 if ((r >> j) & 1) e |= 1u << G.rpos[j];
             er[r] = e;
         }
+        const std::vector<int> lanes = lane_order(t, rmask);
         o << "  {\n    unsigned ethr = 0;\n";
-        {
-            int k = 0;
-            for (int b = 0; b < t; ++b) {
-                if ((rmask >> b) & 1) continue;
-                o << "    ethr |= ((th >> " << k << ") & 1u) << " << b << ";\n";
-                ++k;
-            }
-        }
-        o << "    const unsigned sw = swz(ethr);\n";
+        for (size_t k = 0; k < lanes.size(); ++k) o << "    ethr |= ((th >> " << k << ") & 1u) << " << lanes[k] << ";\n";
+        o << "    " << thread_position("sw", lanes) << "    sw *= " << es << "u;\n";
         std::vector<int> perm(N);
         for (int r = 0; r < N; ++r) {
             perm[r] = r;
-            o << "    " << V << " x" << r << " = lp[sw ^ " << swz_host(er[r]) << "u];\n";
+            o << "    " << V << " x" << r << " = " << at("sw", er[r]) << ";\n";
         }
         for (int i = 0; i < G.nops; ++i) {
             const int oi = G.op0 + i;
@@ -293,22 +368,18 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
             }
             o << "    }\n";
         }
-        for (int r = 0; r < N; ++r) o << "    lp[sw ^ " << swz_host(er[r]) << "u] = x" << perm[r] << ";\n";
+        for (int r = 0; r < N; ++r) o << "    " << at("sw", er[r]) << " = x" << perm[r] << ";\n";
         o << "  }\n  __syncthreads();\n";
     }
     // Store: element e = th + r * nthr of the stored tile comes from LDS tile element
     // sth | sreg[r], thread bit i moving to tile bit store_src[i].
-    o << "  unsigned sth = 0;\n";
-    for (int i = 0; i < t - RB; ++i) {
-        const int src = pass.store_src.empty() ? i : pass.store_src[i];
-        o << "  sth |= ((th >> " << i << ") & 1u) << " << src << ";\n";
-    }
-    o << "  const unsigned ssw = swz(sth);\n";
+    for (int k = 0; k < t - RB; ++k) thread_bits[k] = pass.store_src.empty() ? k : pass.store_src[k];
+    o << "  " << thread_position("ssw", thread_bits) << "  ssw *= " << es << "u;\n";
     for (int r = 0; r < N; ++r) {
         uint32_t v = 0;
         for (int j = 0; j < RB; ++j)
             if ((r >> j) & 1) v |= 1u << (pass.store_src.empty() ? t - RB + j : pass.store_src[t - RB + j]);
-        o << "  gp[toff | " << U(rofs[r]) << "] = lp[ssw ^ " << swz_host(v) << "u];\n";
+        o << "  gp[toff | " << U(rofs[r]) << "] = " << at("ssw", v) << ";\n";
     }
     o << "}\n";
     *nthr_out = nthr;
@@ -426,7 +497,20 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
       << "(void* psi_, void* lam_, const char* ops_, const double* mats, double* gpart_, const char* zs_, int op_first, "
          "int pstride) {\n";
     o << "  __shared__ __align__(16) unsigned char smem[" << lds << "];\n";
-    o << "  double2* lp = (double2*)smem;\n  " << VL << "* ll = (" << VL << "*)(smem + " << (16 << t) << ");\n";
+    // Lambda, psi, partials, in this order: the first two within the offsets of an LDS instruction.
+    // Positions are kept in units of 8 bytes' lambda (or 16 bytes') and psi's by a factor, one XOR an access.
+    auto at_psi = [&](const std::string& pos, uint32_t e) {
+        return "*(LDS double2*)((LDS char*)smem + " + I((long long)lb << t) + " + (" + pos + "p ^ " + I((long long)swz_host(e) * 16) + "u))";
+    };
+    auto at_lam = [&](const std::string& pos, uint32_t e) {
+        return "*(LDS " + VL + "*)((LDS char*)smem + (" + pos + "l ^ " + I((long long)swz_host(e) * lb) + "u))";
+    };
+    auto positions = [&](const std::string& name, const std::vector<int>& bits) {
+        return thread_position(name, bits) + "    const unsigned " + name + "p = " + name + " * 16u, " + name + "l = " + name +
+               " * " + I(lb) + "u;\n";
+    };
+    std::vector<int> thread_bits(t - RB);
+    for (int k = 0; k < t - RB; ++k) thread_bits[k] = k;
     o << "  double* red0 = (double*)(smem + " << ((16 + lb) << t) << ");\n";
     o << "  const unsigned th = threadIdx.x;\n";
     o << "  GLB double2* gp = (GLB double2*)psi_;\n  GLB " << VL << "* gl = (GLB " << VL << "*)lam_;\n";
@@ -458,8 +542,10 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     for (int r = 0; r < N; ++r)
         o << "    const double2 v" << r << " = gp[toff | " << U(rofs[r]) << "]; const " << VL << " w" << r << " = gl[toff | "
           << U(rofs[r]) << "];\n";
+    o << "    " << positions("lpos", thread_bits);
     for (int r = 0; r < N; ++r)
-        o << "    lp[swz(th + " << r * nthr << "u)] = v" << r << "; ll[swz(th + " << r * nthr << "u)] = w" << r << ";\n";
+        o << "    " << at_psi("lpos", (uint32_t)r * nthr) << " = v" << r << "; " << at_lam("lpos", (uint32_t)r * nthr) << " = w"
+          << r << ";\n";
     o << "  }\n  __syncthreads();\n";
     o << "  double F = 1.0;\n";
     // LDS address of a lane pair's first partial, kept in a register: the partials' own offsets are immediates.
@@ -543,22 +629,16 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                 if ((r >> j) & 1) e |= 1u << G.rpos[j];
             er[r] = e;
         }
+        const std::vector<int> lanes = lane_order(t, rmask);
         o << "  {\n    unsigned ethr = 0;\n";
-        {
-            int k = 0;
-            for (int b = 0; b < t; ++b) {
-                if ((rmask >> b) & 1) continue;
-                o << "    ethr |= ((th >> " << k << ") & 1u) << " << b << ";\n";
-                ++k;
-            }
-        }
-        o << "    const unsigned sw = swz(ethr);\n";
+        for (size_t k = 0; k < lanes.size(); ++k) o << "    ethr |= ((th >> " << k << ") & 1u) << " << lanes[k] << ";\n";
+        o << "    " << positions("sw", lanes);
         if (red_lanes != 2) o << "    double* red = red0 + " << buf * std::max(1, maxslots) * E << ";\n";
         std::vector<int> perm(N);
         for (int r = 0; r < N; ++r) {
             perm[r] = r;
-            o << "    double2 x" << r << " = lp[sw ^ " << swz_host(er[r]) << "u]; double2 y" << r << "; { const " << VL
-              << " q = ll[sw ^ " << swz_host(er[r]) << "u]; y" << r << " = make_double2((double)q.x, (double)q.y); }\n";
+            o << "    double2 x" << r << " = " << at_psi("sw", er[r]) << "; double2 y" << r << "; { const " << VL << " q = "
+              << at_lam("sw", er[r]) << "; y" << r << " = make_double2((double)q.x, (double)q.y); }\n";
         }
         int nslot = 0;
         for (int i = 0; i < G.nops; ++i) {
@@ -663,7 +743,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
         if (nslot != G.nslot) return "";  // the record's slots and the group's list disagree
         if (scaled) emit_rescale();
         for (int r = 0; r < N; ++r)
-            o << "    lp[sw ^ " << swz_host(er[r]) << "u] = x" << perm[r] << "; ll[sw ^ " << swz_host(er[r]) << "u] = make_"
+            o << "    " << at_psi("sw", er[r]) << " = x" << perm[r] << "; " << at_lam("sw", er[r]) << " = make_"
               << VL << "((" << RL << ")y" << perm[r] << ".x, (" << RL << ")y" << perm[r] << ".y);\n";
         o << "  }\n  __syncthreads();\n";
         if (nslot > 0) {
@@ -680,18 +760,14 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
         }
     }
     // Store with the accumulated scale.
-    o << "  unsigned sth = 0;\n";
-    for (int i = 0; i < t - RB; ++i) {
-        const int src = pass.store_src.empty() ? i : pass.store_src[i];
-        o << "  sth |= ((th >> " << i << ") & 1u) << " << src << ";\n";
-    }
-    o << "  const unsigned ssw = swz(sth);\n";
+    for (int k = 0; k < t - RB; ++k) thread_bits[k] = pass.store_src.empty() ? k : pass.store_src[k];
+    o << "  " << positions("ssw", thread_bits);
     for (int r = 0; r < N; ++r) {
         uint32_t v = 0;
         for (int j = 0; j < RB; ++j)
             if ((r >> j) & 1) v |= 1u << (pass.store_src.empty() ? t - RB + j : pass.store_src[t - RB + j]);
-        o << "  { const double2 v = lp[ssw ^ " << swz_host(v) << "u]; const " << VL << " w = ll[ssw ^ " << swz_host(v)
-          << "u]; const double wx = (double)w.x, wy = (double)w.y;\n";
+        o << "  { const double2 v = " << at_psi("ssw", v) << "; const " << VL << " w = " << at_lam("ssw", v)
+          << "; const double wx = (double)w.x, wy = (double)w.y;\n";
         o << "    gp[toff | " << U(rofs[r]) << "] = make_double2(F * v.x, F * v.y);\n";
         o << "    gl[toff | " << U(rofs[r]) << "] = make_" << VL << "((" << RL << ")(F * wx), (" << RL << ")(F * wy)); }\n";
     }
