@@ -101,11 +101,11 @@ enum yao_grad_mode { YAO_GRAD_REVERSIBLE = 0, YAO_GRAD_CHECKPOINT = 1, YAO_GRAD_
  *                    tile_qubits are taken as given.
  *   jit              0: off. N >= 1 (default 3): when a device-bound program (a circuit
  *                    whose matrices are bound from the parameters on the device) runs its
- *                    N-th forward sweep on a single-slot state, its passes are compiled at run
+ *                    N-th forward sweep on a state, its passes are compiled at run
  *                    time (hipRTC) into straight-line kernels that read the same op records,
  *                    so later parameter changes need no recompile. Passes outside the
- *                    compiled form (batched states, LDS-applied ops, dense blocks, tiles over
- *                    64 KiB), autotuner trials and graph recording keep the generic kernels; a
+ *                    compiled form (LDS-applied ops, dense blocks), autotuner trials and graph
+ *                    recording keep the generic kernels; a
  *                    failed compile leaves the program on them. Compiling takes ~0.4 s per
  *                    pass family of ~70 ops, once per program. */
 typedef struct {

@@ -645,13 +645,13 @@ int count_slots(const yao_circuit* c)
 static void compiled_form(const Plan*& P, const BoundProgram*& bp, const yao_circuit* sc,
                           const std::vector<FusedPart>* parts, const yao_circuit* orig, bool bwd, int dtype, int n, int B)
 {
-    if (options().tile_qubits > 0 || !jit_due(bp, B)) return;
+    if (options().tile_qubits > 0 || !jit_due(bp)) return;
     if (!bp->alt_tried) {
         bp->alt_tried = true;
         int t = P->t, rb = P->reg_bits, L = 0;
-        if (jit_geometry(n, dtype, bwd, &t, &rb, &L)) {
-            const int slots = bwd ? reverse_slot_limit(t, 0, dtype == YAO_C64 ? 8 : 16, rb) : kMaxGroupSlots;
-            bp->alt_plan = new Plan(get_plan_ex(sc, 0, (int)sc->gates.size(), 1, t, 0, L, bwd, rb, kMaxPassOps, slots));
+        if (jit_geometry(n, B, dtype, bwd, &t, &rb, &L)) {
+            const int slots = bwd ? reverse_slot_limit(t, P->c, dtype == YAO_C64 ? 8 : 16, rb) : kMaxGroupSlots;
+            bp->alt_plan = new Plan(get_plan_ex(sc, 0, (int)sc->gates.size(), B, t, P->c, L, bwd, rb, kMaxPassOps, slots));
             bp->alt_plan->compiled = true;
             const Plan& A = *bp->alt_plan;
             const BoundProgram* ab = A.valid ? bound_program(A, sc, bwd, dtype, parts, orig) : nullptr;

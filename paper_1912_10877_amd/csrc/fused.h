@@ -322,14 +322,14 @@ struct BoundProgram {
 const JitPasses* jit_passes(const BoundProgram* bp, const Plan& P, bool bwd, int dtype, int n, int B);
 bool jit_has(const JitPasses* J, int p);
 // Whether bp has come to the use on which programs are compiled (counts one use).
-bool jit_due(const BoundProgram* bp, int B);
+bool jit_due(const BoundProgram* bp);
 // Uncontrolled dense ops of a compiled complex64 forward plan get their records in real form.
 bool takes_real_form(const Plan& P, const POp& op);
 void use_real_forms(const Plan& P, Program& prog);
-// Tile bits, register bits and low bits kept in every tile for a compiled plan of a single-slot
-// state; t and reg_bits come in as the generic kernels'. False where a plan of its own would be no
-// different.
-bool jit_geometry(int n, int dtype, bool bwd, int* t, int* reg_bits, int* L);
+// Tile bits, register bits and low bits kept in every tile for a compiled plan of a state of n qubits
+// and batch B; t and reg_bits come in as the generic kernels'. False where a plan of its own would
+// be no different.
+bool jit_geometry(int n, int B, int dtype, bool bwd, int* t, int* reg_bits, int* L);
 // Compile every pass of bp; false unless all of them can be.
 bool jit_compile_all(const BoundProgram* bp, const Plan& P, bool bwd, int dtype, int n);
 int jit_launch_forward(const JitPasses* J, int p, void* psi, const POp* ops, int op_first, double bytes,

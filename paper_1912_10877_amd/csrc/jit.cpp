@@ -9,7 +9,7 @@
 // controls are register bits is a renaming of registers at compile time (no instructions),
 // and the matrix entries are read from the records at constant offsets.
 //
-// Supported: single-slot states (B = 1), passes whose groups are all register groups (no
+// Supported: passes whose groups are all register groups (no
 // LDS-applied k = 2, 3 ops and no dense blocks); the LDS of a compiled pass is a static
 // allocation of the sizes the pass needs. Any other pass of the program runs the generic
 // kernel. A compile failure switches the program back to the generic kernels for good.
@@ -71,7 +71,8 @@ int gf2_rank(std::vector<uint32_t> v)
 // The tile bits outside the mask regs in the order of the thread bits that address them: 4 whose
 // images are independent in the low 4 bits, then one that adds the fifth bank bit, then the rest (the
 // choice of most independent images where no such 5 exist).
-std::vector<int> lane_order(int t, uint32_t regs)
+// The c batch bits, the tile's lowest and their own images, stay on the lowest lanes.
+std::vector<int> lane_order(int t, int c, uint32_t regs)
 {
     std::vector<int> bits;
     for (int b = 0; b < t; ++b)
@@ -81,7 +82,7 @@ std::vector<int> lane_order(int t, uint32_t regs)
     std::vector<int> best = bits;
     int best_rank = -1;
     for (uint32_t pick = 0; pick < (1u << m) && best_rank < 9; ++pick) {
-        if (__builtin_popcount(pick) != 4) continue;
+        if (__builtin_popcount(pick) != 4 || (pick & ((1u << c) - 1)) != (1u << c) - 1) continue;
         std::vector<int> order;
         std::vector<uint32_t> low4, low5;
         for (int i = 0; i < m; ++i)
@@ -213,6 +214,33 @@ std::vector<char> bound_ops(const Program& prog)
     return b;
 }
 
+// Code that declares base (the index bits outside the tile), toff (the element of the thread's register
+// 0) and, for batches, b0 and bl (the tile's first slot and the thread's place among them), and the
+// element offset of each register. Thread bits: the c batch bits, then tile qubits; register bits: the
+// next tile qubits. Slots past the batch read its last slot.
+std::string tile_code(const Plan& P, const HostPass& pass, int n, std::vector<uint64_t>& rofs)
+{
+    const int RB = P.reg_bits, N = 1 << RB, t = P.t, c = P.c;
+    uint64_t T = 0;
+    for (int q : pass.tile_qubits) T |= uint64_t(1) << q;
+    std::ostringstream o;
+    o << "  const u64 tid = blockIdx.x;\n  u64 base = 0;\n";
+    int j = 0;
+    for (int q = 0; q < n; ++q)
+        if (!((T >> q) & 1)) o << "  base |= ((tid >> " << j++ << ") & 1ull) << " << q << ";\n";
+    o << "  u64 toff = base;\n";
+    for (int k = 0; k < t - RB - c; ++k)
+        o << "  toff |= (u64)((th >> " << c + k << ") & 1u) << " << pass.tile_qubits[k] << ";\n";
+    if (P.B > 1)
+        o << "  const unsigned b0 = blockIdx.y << " << c << ", bl = th & " << (1 << c) - 1 << "u;\n"
+          << "  toff = toff * " << P.B << "ull + (b0 + bl < " << P.B << "u ? b0 + bl : " << P.B - 1 << "u);\n";
+    rofs.assign(N, 0);
+    for (int r = 0; r < N; ++r)
+        for (int b = 0; b < RB; ++b)
+            if ((r >> b) & 1) rofs[r] += (uint64_t(1) << pass.tile_qubits[t - RB - c + b]) * (uint64_t)P.B;
+    return o.str();
+}
+
 // Code of one forward pass, or an empty string when the pass is not supported.
 //
 // Vector issue bounds complex64 passes of a few gates a qubit (8 instructions an amplitude for a
@@ -228,8 +256,8 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
 {
     const HostPass& pass = P.passes[p];
     const int RB = P.reg_bits, N = 1 << RB, t = P.t;
-    if (P.c != 0 || pass.standalone >= 0 || prog.pass_dmat_words[p] != 0) return "";
-    if (t - RB < 0 || t - RB > 10 || (int)pass.tile_qubits.size() != t) return "";
+    if (pass.standalone >= 0 || prog.pass_dmat_words[p] != 0) return "";
+    if (t - RB < P.c || t - RB > 10 || (int)pass.tile_qubits.size() != t - P.c) return "";
     const int g0 = prog.pass_group0[p], ng = (int)pass.groups.size();
     for (int g = 0; g < ng; ++g)
         if (prog.groups[g0 + g].lds) return "";
@@ -257,31 +285,10 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
     o << "  GLB " << V << "* gp = (GLB " << V << "*)psi_;\n  const CST char* ops = (const CST char*)ops_;\n";
     o << "  if (zs_) { const CST u64* z = (const CST u64*)(zs_ + 32 * blockIdx.z); gp = (GLB " << V
       << "*)z[0]; ops = (const CST char*)z[2] + (u64)op_first * " << sizeof(POp) << "; }\n";
-    // Tile base: the tile index bits on the qubits outside the tile, ascending.
-    uint64_t T = 0;
-    for (int q : pass.tile_qubits) T |= uint64_t(1) << q;
-    o << "  const u64 tid = blockIdx.x;\n  u64 base = 0;\n";
-    {
-        int j = 0;
-        for (int q = 0; q < n; ++q) {
-            if ((T >> q) & 1) continue;
-            o << "  base |= ((tid >> " << j << ") & 1ull) << " << q << ";\n";
-            ++j;
-        }
-    }
-    // Load mapping: element e = th + r * nthr; bits of th on tile qubits 0 .. t-RB-1, bits of r
-    // on the next RB tile qubits.
-    o << "  u64 toff = base;\n";
-    for (int j = 0; j < t - RB; ++j) o << "  toff |= (u64)((th >> " << j << ") & 1u) << " << pass.tile_qubits[j] << ";\n";
-    std::vector<uint64_t> rofs(N);
-    for (int r = 0; r < N; ++r) {
-        uint64_t d = 0;
-        for (int b = 0; b < RB; ++b)
-            if ((r >> b) & 1) d |= uint64_t(1) << pass.tile_qubits[t - RB + b];
-        rofs[r] = d;
-    }
+    std::vector<uint64_t> rofs;
+    o << tile_code(P, pass, n, rofs);
     o << "  {\n";
-    for (int r = 0; r < N; ++r) o << "    const " << V << " v" << r << " = gp[toff | " << U(rofs[r]) << "];\n";
+    for (int r = 0; r < N; ++r) o << "    const " << V << " v" << r << " = gp[toff + " << U(rofs[r]) << "];\n";
     {
         const int W = c64 ? UM : 16;  // dwords of a record's matrix
         o << "    { const CST unsigned* src = (const CST unsigned*)ops; unsigned* dst = (unsigned*)um;\n"
@@ -310,7 +317,7 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
                 if ((r >> j) & 1) e |= 1u << G.rpos[j];
             er[r] = e;
         }
-        const std::vector<int> lanes = lane_order(t, rmask);
+        const std::vector<int> lanes = lane_order(t, P.c, rmask);
         o << "  {\n    unsigned ethr = 0;\n";
         for (size_t k = 0; k < lanes.size(); ++k) o << "    ethr |= ((th >> " << k << ") & 1u) << " << lanes[k] << ";\n";
         o << "    " << thread_position("sw", lanes) << "    sw *= " << es << "u;\n";
@@ -375,12 +382,14 @@ std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, i
     // sth | sreg[r], thread bit i moving to tile bit store_src[i].
     for (int k = 0; k < t - RB; ++k) thread_bits[k] = pass.store_src.empty() ? k : pass.store_src[k];
     o << "  " << thread_position("ssw", thread_bits) << "  ssw *= " << es << "u;\n";
+    if (P.B > 1) o << "  if (b0 + bl < " << P.B << "u) {\n";
     for (int r = 0; r < N; ++r) {
         uint32_t v = 0;
         for (int j = 0; j < RB; ++j)
             if ((r >> j) & 1) v |= 1u << (pass.store_src.empty() ? t - RB + j : pass.store_src[t - RB + j]);
-        o << "  gp[toff | " << U(rofs[r]) << "] = " << at("ssw", v) << ";\n";
+        o << "  gp[toff + " << U(rofs[r]) << "] = " << at("ssw", v) << ";\n";
     }
+    if (P.B > 1) o << "  }\n";
     o << "}\n";
     *nthr_out = nthr;
     *lds_out = lds;
@@ -410,12 +419,13 @@ template <int CTRL> __device__ __forceinline__ double dpp_f64(double v)
     const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(b >> 32), CTRL, 0xF, 0xF, false);
     return __builtin_bit_cast(double, ((u64)hi << 32) | lo);
 }
-// Sum over the 16 lanes of a DPP row (single-slot tiles): lane 0 of the row holds it.
-__device__ __forceinline__ double row_sum16(double v)
+// Sum over the lanes of a 16-lane DPP row that share their low C bits (a batch slot): lanes 0 .. 2^C - 1
+// of the row hold them.
+template <int C> __device__ __forceinline__ double row_sum16(double v)
 {
-    v += dpp_f64<0xB1>(v);
-    v += dpp_f64<0x4E>(v);
-    v += dpp_f64<0x124>(v);
+    if (C < 1) v += dpp_f64<0xB1>(v);
+    if (C < 2) v += dpp_f64<0x4E>(v);
+    if (C < 3) v += dpp_f64<0x124>(v);
     v += dpp_f64<0x128>(v);
     return v;
 }
@@ -465,8 +475,8 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
 {
     const HostPass& pass = P.passes[p];
     const int RB = P.reg_bits, N = 1 << RB, t = P.t;
-    if (P.c != 0 || pass.standalone >= 0) return "";
-    if (t - RB < 4 || t - RB > 10 || (int)pass.tile_qubits.size() != t) return "";
+    if (pass.standalone >= 0) return "";
+    if (t - RB < 4 || t - RB > 10 || (int)pass.tile_qubits.size() != t - P.c) return "";
     const int g0 = prog.pass_group0[p], ng = (int)pass.groups.size();
     int maxslots = 0;
     for (int g = 0; g < ng; ++g) {
@@ -476,14 +486,15 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     const bool c64 = dtype == YAO_C64;
     const int nthr = 1 << (t - RB);
     const int lb = c64 ? 8 : 16;
-    // Gradient partials: each gradient is summed over lane pairs (one DPP step) and the pair sums
-    // go to LDS, E = nthr / 2 entries per gradient, two buffers of the group's gradients; when
-    // that does not fit, over rows of 16 lanes (E = nthr / 16).
+    // Gradient partials: each gradient is summed over lane pairs (one DPP step; lanes 8 apart in a
+    // batch, whose slots are the low c <= 3 lane bits) and the pair sums go to LDS, E = nthr / 2
+    // entries per gradient, two buffers of the group's gradients; when that does not fit, per slot
+    // over rows of 16 lanes (E = 2^c nthr / 16).
     auto lds_for = [&](int e) {
         return ((size_t)(16 + lb) << t) + sizeof(double) * 2 * (size_t)std::max(1, maxslots) * e;
     };
     const int red_lanes = lds_for(nthr >> 1) <= 160 * 1024 ? 2 : 16;
-    const int E = nthr / red_lanes;
+    const int E = red_lanes == 2 ? nthr / 2 : (nthr / 16) << P.c;
     const size_t lds = lds_for(E);
     if (lds > 160 * 1024) return "";
     const std::string VL = c64 ? "float2" : "double2", RL = c64 ? "float" : "double";
@@ -518,29 +529,11 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     o << "  if (zs_) { const CST u64* z = (const CST u64*)(zs_ + 32 * blockIdx.z); gp = (GLB double2*)z[0]; gl = (GLB "
       << VL << "*)z[1]; ops = (const CST char*)z[2] + (u64)op_first * " << sizeof(POp)
       << "; gpart = (GLB double*)z[3]; }\n";
-    uint64_t T = 0;
-    for (int q : pass.tile_qubits) T |= uint64_t(1) << q;
-    o << "  const u64 tid = blockIdx.x;\n  u64 base = 0;\n";
-    {
-        int j = 0;
-        for (int q = 0; q < n; ++q) {
-            if ((T >> q) & 1) continue;
-            o << "  base |= ((tid >> " << j << ") & 1ull) << " << q << ";\n";
-            ++j;
-        }
-    }
-    o << "  u64 toff = base;\n";
-    for (int j = 0; j < t - RB; ++j) o << "  toff |= (u64)((th >> " << j << ") & 1u) << " << pass.tile_qubits[j] << ";\n";
-    std::vector<uint64_t> rofs(N);
-    for (int r = 0; r < N; ++r) {
-        uint64_t d = 0;
-        for (int b = 0; b < RB; ++b)
-            if ((r >> b) & 1) d |= uint64_t(1) << pass.tile_qubits[t - RB + b];
-        rofs[r] = d;
-    }
+    std::vector<uint64_t> rofs;
+    o << tile_code(P, pass, n, rofs);
     o << "  {\n";
     for (int r = 0; r < N; ++r)
-        o << "    const double2 v" << r << " = gp[toff | " << U(rofs[r]) << "]; const " << VL << " w" << r << " = gl[toff | "
+        o << "    const double2 v" << r << " = gp[toff + " << U(rofs[r]) << "]; const " << VL << " w" << r << " = gl[toff + "
           << U(rofs[r]) << "];\n";
     o << "    " << positions("lpos", thread_bits);
     for (int r = 0; r < N; ++r)
@@ -550,7 +543,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     o << "  double F = 1.0;\n";
     // LDS address of a lane pair's first partial, kept in a register: the partials' own offsets are immediates.
     if (red_lanes == 2)
-        o << "  unsigned rad = (unsigned)(u64)(LDS double*)red0 + (th >> 1) * 8u;\n  asm volatile(\"\" : \"+v\"(rad));\n";
+        o << "  unsigned rad = (unsigned)(u64)(LDS double*)red0 + " << (P.c ? "((th >> 4) * 8u + (th & 7u))" : "(th >> 1)") << " * 8u;\n  asm volatile(\"\" : \"+v\"(rad));\n";
     // Matrix entries each op reads (cls 0 and 1: k and f as u1, u2;
     // others what their class needs). They come through the scalar cache a batch ahead:
     // batches of up to 8 consecutive ops (at most 16 entries); at the first op of batch b the
@@ -629,7 +622,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                 if ((r >> j) & 1) e |= 1u << G.rpos[j];
             er[r] = e;
         }
-        const std::vector<int> lanes = lane_order(t, rmask);
+        const std::vector<int> lanes = lane_order(t, P.c, rmask);
         o << "  {\n    unsigned ethr = 0;\n";
         for (size_t k = 0; k < lanes.size(); ++k) o << "    ethr |= ((th >> " << k << ") & 1u) << " << lanes[k] << ";\n";
         o << "    " << positions("sw", lanes);
@@ -691,10 +684,11 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
                 }
                 if (scaled) o << "      g *= F * F;\n";
                 if (red_lanes == 2)  // both lanes of a pair hold the sum and write it
-                    o << "      g += dpp_f64<0xB1>(g);\n      *(LDS double*)(rad + " << (buf * std::max(1, maxslots) + nslot) * E * 8
+                    o << "      g += dpp_f64<" << (P.c ? "0x128" : "0xB1") << ">(g);\n      *(LDS double*)(rad + " << (buf * std::max(1, maxslots) + nslot) * E * 8
                       << "u) = g;\n";
                 else
-                    o << "      g = row_sum16(g);\n      if ((th & 15u) == 0) red[" << nslot * E << " + (th >> 4)] = g;\n";
+                    o << "      g = row_sum16<" << P.c << ">(g);\n      if ((th & 15u) < " << (1 << P.c) << "u) red[" << nslot * E
+                      << " + ((th >> 4) << " << P.c << ") + (th & 15u)] = g;\n";
                 ++nslot;
             }
             for (int a : pairs) {
@@ -752,25 +746,30 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             o << "    for (unsigned task = th; task < " << nslot * 16 << "u; task += " << nthr << "u) {\n";
             o << "      const unsigned s = task >> 4, j = task & 15u;\n      double v = 0.0;\n";
             o << "      for (unsigned e = j; e < " << E << "u; e += 16u) v += red[s * " << E << "u + e];\n";
-            o << "      v = row_sum16(v);\n";  // the 16 lanes of a task are one DPP row
+            o << "      v = row_sum16<" << P.c << ">(v);\n";  // the 16 lanes of a task are one DPP row
             o << "      int slot = " << G.slots[0] << ";\n";
             for (int k = 1; k < nslot; ++k) o << "      if (s == " << k << "u) slot = " << G.slots[k] << ";\n";
-            o << "      if (j == 0) gpart[(u64)slot * (u64)pstride + blockIdx.x] = v;\n    }\n  }\n";
+            if (P.B == 1) o << "      if (j == 0) gpart[(u64)slot * (u64)pstride + blockIdx.x] = v;\n    }\n  }\n";
+            else
+                o << "      if (j < " << (1 << P.c) << "u && b0 + j < " << P.B << "u) gpart[((u64)slot * " << P.B
+                  << "ull + b0 + j) * (u64)pstride + blockIdx.x] = v;\n    }\n  }\n";
             buf ^= 1;
         }
     }
     // Store with the accumulated scale.
     for (int k = 0; k < t - RB; ++k) thread_bits[k] = pass.store_src.empty() ? k : pass.store_src[k];
     o << "  " << positions("ssw", thread_bits);
+    if (P.B > 1) o << "  if (b0 + bl < " << P.B << "u) {\n";
     for (int r = 0; r < N; ++r) {
         uint32_t v = 0;
         for (int j = 0; j < RB; ++j)
             if ((r >> j) & 1) v |= 1u << (pass.store_src.empty() ? t - RB + j : pass.store_src[t - RB + j]);
         o << "  { const double2 v = " << at_psi("ssw", v) << "; const " << VL << " w = " << at_lam("ssw", v)
           << "; const double wx = (double)w.x, wy = (double)w.y;\n";
-        o << "    gp[toff | " << U(rofs[r]) << "] = make_double2(F * v.x, F * v.y);\n";
-        o << "    gl[toff | " << U(rofs[r]) << "] = make_" << VL << "((" << RL << ")(F * wx), (" << RL << ")(F * wy)); }\n";
+        o << "    gp[toff + " << U(rofs[r]) << "] = make_double2(F * v.x, F * v.y);\n";
+        o << "    gl[toff + " << U(rofs[r]) << "] = make_" << VL << "((" << RL << ")(F * wx), (" << RL << ")(F * wy)); }\n";
     }
+    if (P.B > 1) o << "  }\n";
     o << "}\n";
     *nthr_out = nthr;
     *lds_out = lds;
@@ -816,7 +815,7 @@ struct JitPasses {
     std::vector<hipFunction_t> fn;  // per pass; null: the generic kernel
     std::vector<int> nthr;
     std::vector<size_t> lds;
-    std::vector<int> ntiles;
+    std::vector<int> ntiles, nslots;  // grid x and y
 };
 
 void jit_suspend(bool on)
@@ -920,6 +919,7 @@ static JitPasses* jit_compile(const Plan& P, const Program& prog, bool bwd, int 
     J->nthr = nthr;
     J->lds = lds;
     J->ntiles.assign(P.passes.size(), 0);
+    J->nslots.assign(P.passes.size(), 1);
     for (size_t p = 0; p < P.passes.size(); ++p) {
         if (code[p].empty()) continue;
         hipError_t e = hipModuleLoadData(&J->mod[p], code[p].data());
@@ -929,7 +929,8 @@ static JitPasses* jit_compile(const Plan& P, const Program& prog, bool bwd, int 
             jit_free(J);
             return nullptr;
         }
-        J->ntiles[p] = 1 << (n - P.t);
+        J->ntiles[p] = 1 << (n - (P.t - P.c));
+        J->nslots[p] = (P.B + (1 << P.c) - 1) >> P.c;
         ++g_compiled_passes;
     }
     ++g_compiled_programs;
@@ -938,7 +939,7 @@ static JitPasses* jit_compile(const Plan& P, const Program& prog, bool bwd, int 
 
 const JitPasses* jit_passes(const BoundProgram* bp, const Plan& P, bool bwd, int dtype, int n, int B)
 {
-    if (!bp || B != 1) return nullptr;
+    if (!bp || B != P.B) return nullptr;
     const int when = options().jit;
     std::lock_guard<std::mutex> lk(g_jit_mu);
     if (bp->jit || bp->jit_failed) return bp->jit;
@@ -949,9 +950,9 @@ const JitPasses* jit_passes(const BoundProgram* bp, const Plan& P, bool bwd, int
     return bp->jit;
 }
 
-bool jit_due(const BoundProgram* bp, int B)
+bool jit_due(const BoundProgram* bp)
 {
-    if (!bp || B != 1) return false;
+    if (!bp) return false;
     const int when = options().jit;
     std::lock_guard<std::mutex> lk(g_jit_mu);
     if (bp->alt) return true;
@@ -987,10 +988,18 @@ bool jit_compile_all(const BoundProgram* bp, const Plan& P, bool bwd, int dtype,
 // Forward: 8 elements a thread give two waves per SIMD where 16 give one (20 qubits complex64: 237
 // against 291; 10 qubits complex128: 19 against 25). Above 20 qubits several tiles share a CU and
 // 16 elements, with fewer exchanges through LDS, win (24 qubits complex64: 708 against 744).
+// Batches keep the generic sizes (20 qubits, 64 slots, depth 20: reverse passes 39.6 ms in 2^12 tiles,
+// 41.1 in 2^11; with the generic kernels 74 ms) but for small ones (10 qubits, 100 slots: 63 / 80).
 // Complex128 tiles of 2^10 win up to 18 qubits (14 qubits: 68 against 95; 18 qubits: 110 / 143).
-bool jit_geometry(int n, int dtype, bool bwd, int* t, int* reg_bits, int* L)
+bool jit_geometry(int n, int B, int dtype, bool bwd, int* t, int* reg_bits, int* L)
 {
     *L = dtype == YAO_C64 ? 4 : 3;
+    if (B > 1) {
+        *L = std::max(0, *L - std::min(3, ilog2_ceil((uint64_t)B)));
+        if (!bwd) return dtype == YAO_C64;
+        *t = std::min(*t, 11);
+        return dtype == YAO_C64 && n + ilog2_ceil((uint64_t)B) <= 18;
+    }
     if (bwd) {
         if (n > 19) return false;
         const bool mid = n == 19 && dtype == YAO_C64;
@@ -1026,7 +1035,7 @@ int jit_launch_forward(const JitPasses* J, int p, void* psi, const POp* ops, int
     void* cfg[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &args, HIP_LAUNCH_PARAM_BUFFER_SIZE, &asz, HIP_LAUNCH_PARAM_END};
     ++g_launches_fwd;
     const int pi = prof_begin(YAO_KF_PASS_FWD);
-    YAO_HIP(hipModuleLaunchKernel(J->fn[p], (unsigned)J->ntiles[p], 1, (unsigned)nz, (unsigned)J->nthr[p], 1, 1, 0,
+    YAO_HIP(hipModuleLaunchKernel(J->fn[p], (unsigned)J->ntiles[p], (unsigned)J->nslots[p], (unsigned)nz, (unsigned)J->nthr[p], 1, 1, 0,
                                   stream(), nullptr, cfg));
     prof_end(pi, bytes * nz, flops * nz);
     return 0;
@@ -1079,7 +1088,7 @@ int jit_launch_backward(const JitPasses* J, int p, double* psi, void* lam, const
     void* cfg[] = {HIP_LAUNCH_PARAM_BUFFER_POINTER, &args, HIP_LAUNCH_PARAM_BUFFER_SIZE, &asz, HIP_LAUNCH_PARAM_END};
     ++g_launches_bwd;
     const int pi = prof_begin(YAO_KF_PASS_BWD);
-    YAO_HIP(hipModuleLaunchKernel(J->fn[p], (unsigned)J->ntiles[p], 1, (unsigned)nz, (unsigned)J->nthr[p], 1, 1, 0,
+    YAO_HIP(hipModuleLaunchKernel(J->fn[p], (unsigned)J->ntiles[p], (unsigned)J->nslots[p], (unsigned)nz, (unsigned)J->nthr[p], 1, 1, 0,
                                   stream(), nullptr, cfg));
     prof_end(pi, bytes * nz, flops * nz);
     return 0;

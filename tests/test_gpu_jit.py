@@ -290,3 +290,38 @@ def test_compiled_dense_gates_on_matrix_cores(n):
         yb.forward(s, circ, params)
         assert yb.jit_stats()["fwd_launches"] > l0
         assert np.abs(s.download() - oracle.forward(c, params, psi0)).max() <= tol(0, len(gates))
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n,B", [(6, 2), (9, 3), (10, 5), (11, 64), (13, 8), (14, 17)])
+def test_compiled_passes_of_a_batch(n, B, dtype):
+    """Batches through the compiled passes: one, two and three batch bits in a tile, the last block of
+    slots full or not, tiles that hold all qubits or not; every slot its own state, energies, gradients
+    (per slot and summed) and output states. Same bounds as the sweeps above."""
+    yb.set_options(jit=1, autotune=0, fuse_width=1)
+    base = random_bindable(n, 30, seed=60 + n)
+    hea = w.hea_circuit(n, 2)
+    gates = list(hea.gates) + [w.Gate(g.kind, g.locs, g.ctrls, g.cvals, g.param + hea.nparams if g.param >= 0 else -1)
+                               for g in base.gates]
+    c = w.Circuit(n, gates, hea.nparams + base.nparams)
+    H = w.heisenberg(n)
+    circ, h = yb.Circuit.from_workload(c), yb.PauliSum.from_workload(H)
+    psi0 = w.random_state(n, B, 3)
+    params = w.angles(61, c.nparams)
+    s = yb.State(n, B, dtype)
+    s.upload(psi0)
+    psi0 = s.download().astype(np.complex128)
+    l0 = yb.jit_stats()
+    e, g, drift = yb.backward(s, circ, params, h)
+    l1 = yb.jit_stats()
+    assert l1["bwd_launches"] > l0["bwd_launches"] and l1["fwd_launches"] > l0["fwd_launches"]
+    e_ref, g_ref, _ = oracle.adjoint(H, c, params, psi0)
+    te, tg = (1e-5, 1e-4) if dtype == 0 else (1e-10, 1e-9)
+    scale = max(1.0, float(np.abs(g_ref).max()))
+    assert np.abs(e - e_ref).max() <= te
+    assert np.abs(g - g_ref).max() <= tg * scale
+    assert np.abs(s.download() - oracle.forward(c, params, psi0)).max() <= tol(dtype, len(gates))
+    assert drift <= (1e-5 if dtype == 0 else 1e-12)
+    s.upload(psi0)
+    _, total, _ = yb.backward(s, circ, params, h, reduce_batch=True)
+    assert np.abs(total - g_ref.sum(0)).max() <= tg * scale * B
