@@ -101,6 +101,26 @@ struct GateRec {
     std::vector<double> G;  // 2 * 4^k doubles for ROT / DENSE
 };
 
+// The sum of part[0 .. n), for every thread of a workgroup of at most 256, in an order that depends on
+// the workgroup's size alone. red: 256 doubles of LDS, free again after the next barrier.
+__device__ __forceinline__ double block_total(const double* __restrict__ part, int n, double* red)
+{
+    double s = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) s += part[i];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        s = 0;
+        for (int i = threadIdx.x; i < (int)blockDim.x; i += 64) s += red[i];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (threadIdx.x == 0) red[0] = s;
+    }
+    __syncthreads();
+    s = red[0];
+    __syncthreads();
+    return s;
+}
+
 }  // namespace yao
 
 struct yao_state {

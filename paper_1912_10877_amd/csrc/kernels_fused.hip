@@ -1550,6 +1550,63 @@ __global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather(PassArgs a, co
     }
 }
 
+// A step of the Lanczos recurrence as one launch: v = src / |src|, out = H v and the partials of
+// <v|H v>, where |src|^2 comes as the nn partials that the step before left. Every workgroup adds them up
+// for itself, in one order, so no launch stands between; workgroup 0 leaves |src| in *norm. The
+// partners' values are divided as they are read (src and out are different buffers). A vanished src
+// gives v = 0 (the Krylov space closed).
+template <typename R, int RB>
+__global__ __launch_bounds__(kObsGatherThreads) void k_lanczos_hv(const vec2_t<R>* __restrict__ src,
+                                                                  vec2_t<R>* __restrict__ v, vec2_t<R>* __restrict__ out,
+                                                                  int n, const ObsRec* __restrict__ recs, int nrec,
+                                                                  const double* __restrict__ npart, int nn,
+                                                                  double* __restrict__ norm, double* __restrict__ partial)
+{
+    constexpr int N = 1 << RB;
+    using V = vec2_t<R>;
+    __shared__ double red[kObsGatherThreads];
+    const int th = threadIdx.x;
+    const uint32_t gid = blockIdx.x * blockDim.x + (uint32_t)th;
+    const int top = n - RB;
+    V own[N];
+#pragma unroll
+    for (int r = 0; r < N; ++r) own[r] = src[gid | ((uint32_t)r << top)];
+    const double nrm = sqrt(block_total(npart, nn, red));
+    if (gid == 0) *norm = nrm;
+    const R inv = nrm > 1e-300 ? (R)(1.0 / nrm) : R(0);
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        own[r].x *= inv;
+        own[r].y *= inv;
+        v[gid | ((uint32_t)r << top)] = own[r];
+    }
+    double orr[N], oi[N];
+    obs_terms<RB, true, V>(cptr(recs), nrec, gid, 0,
+                           [&](uint32_t x, V (&q)[N]) __attribute__((always_inline)) {
+#pragma unroll
+                               for (int r = 0; r < N; ++r) {
+                                   q[r] = src[(gid ^ x) ^ ((uint32_t)r << top)];
+                                   q[r].x *= inv;
+                                   q[r].y *= inv;
+                               }
+                           },
+                           orr, oi);
+    double acc = 0;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+        acc += (double)own[r].x * orr[r] + (double)own[r].y * oi[r];
+        out[gid | ((uint32_t)r << top)] = mkv<V, R>((R)orr[r], (R)oi[r]);
+    }
+    red[th] = acc;
+    __syncthreads();
+    if (th < 64) {
+        double t = 0;
+        for (int i = th; i < (int)blockDim.x; i += 64) t += red[i];
+        for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+        if (th == 0) partial[blockIdx.x] = t;
+    }
+}
+
 // Raise each pass kernel's dynamic LDS limit to the CU's 160 KiB, once per kernel.
 template <typename K> int set_lds_limit(K kernel)
 {
@@ -2039,6 +2096,37 @@ int obs_tile_qubits(const yao_pauli_sum* h, int n, int B, int dtype)
 {
     const ObsPlan* P = obs_plan(h, n, B, dtype, OBS_TILES);
     return P && P->ok ? P->t - P->c : 0;
+}
+
+bool obs_one_launch(const yao_pauli_sum* h, int n, int B, int dtype)
+{
+    if (n < kObsRegBits + 1) return false;
+    const ObsPlan* P = obs_plan(h, n, B, dtype, OBS_VECTOR);
+    return P && P->ok && P->gather;
+}
+
+int launch_lanczos_hv(const void* src, void* v, void* out, int dtype, int n, const yao_pauli_sum* h, const double* npart,
+                      int nn, double* norm, double* partial)
+{
+    const ObsPlan* P = obs_plan(h, n, 1, dtype, OBS_VECTOR);
+    if (!P) return YAO_ENOMEM;
+    if (!P->ok || !P->gather) return set_error(YAO_EINVAL, "observable takes more than one launch");
+    const ObsRec* recs = P->drecs;
+    const int nrec = P->passes[0].r1, grid = obs_columns(P, n), nthr = obs_gather_threads(n);
+#define YAO_LANCZOS(R, RB)                                                                                        \
+    k_lanczos_hv<R, RB><<<grid, nthr, 0, stream()>>>((const vec2_t<R>*)src, (vec2_t<R>*)v, (vec2_t<R>*)out, n, recs, nrec, \
+                                                      npart, nn, norm, partial)
+    const bool one = obs_gather_reg_bits(n) == 1;
+    if (dtype == YAO_C64) {
+        if (one) YAO_LANCZOS(float, 1);
+        else YAO_LANCZOS(float, 2);
+    } else {
+        if (one) YAO_LANCZOS(double, 1);
+        else YAO_LANCZOS(double, 2);
+    }
+#undef YAO_LANCZOS
+    YAO_HIP(hipGetLastError());
+    return 0;
 }
 
 size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype, int use)

@@ -132,6 +132,12 @@ size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype, int 
 int obs_tile_qubits(const yao_pauli_sum* h, int n, int B, int dtype);
 int launch_obs_passes(const void* psi, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
                       double* partial, int* W, int use);
+// Whether H psi of such a state is one launch (its partials: obs_partial_doubles columns), and that launch
+// as a Lanczos step: v = src / |src| with |src|^2 = the sum of npart[0 .. nn), out = H v (another buffer),
+// *norm = |src| and the partials of <v|H v>.
+bool obs_one_launch(const yao_pauli_sum* h, int n, int B, int dtype);
+int launch_lanczos_hv(const void* src, void* v, void* out, int dtype, int n, const yao_pauli_sum* h, const double* npart,
+                      int nn, double* norm, double* partial);
 void drop_obs_plans(const yao_pauli_sum* h);
 int launch_hpsi_dev(const void* data, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
                     double* partial, double* energy_dev);

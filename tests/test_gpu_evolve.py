@@ -104,3 +104,22 @@ def test_time_evolution_eigenstate_and_validation():
         yb.time_evolve(s, yb.PauliSum.from_workload(w.heisenberg(n)), float("nan"))
     with pytest.raises(yb.YaoError):
         yb.time_evolve(s, yb.PauliSum.from_workload(w.heisenberg(n)), 0.1, krylov_dim=100)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n,t", [(4, 7.0), (9, -2.5), (12, 3.0), (18, -0.1)])
+def test_single_slot_substeps(n, t, dtype):
+    """Single-slot states whose substeps are chosen on the device: more time than one substep covers (the
+    host then halves it), negative times, two and four amplitudes a thread. Per substep the bounds of the
+    tests above, 1e-10 and 2e-5 an amplitude."""
+    from paper_1912_10877_amd import binding as yb
+
+    yb.init()
+    H = w.heisenberg(n)
+    psi = w.random_state(n, 1, n + 3)
+    s = yb.State(n, 1, dtype)
+    s.upload(psi)
+    psi = s.download().astype(np.complex128)
+    steps = yb.time_evolve(s, yb.PauliSum.from_workload(H), t)
+    assert steps >= (2 if abs(t) > 2 and n > 4 else 1)  # 4 qubits: the Krylov space closes before 30 vectors
+    assert np.abs(s.download() - oracle.time_evolve(H, psi, t)).max() <= (1e-10 if dtype == 1 else 2e-5) * steps
