@@ -684,8 +684,9 @@ int forward_fused(void* data, int dtype, int n, int B, const yao_circuit* c, con
 }
 
 int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, const double* params, int width, int tq,
-                  const double* dparams)
+                  const double* dparams, const BoundProgram* also, bool* also_bound)
 {
+    if (also_bound) *also_bound = false;
     if (c->gates.empty()) return 0;
     int t, cb, L;
     tile_geometry_tq(n, B, dtype, false, tq, &t, &cb, &L);
@@ -701,7 +702,15 @@ int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, con
                 dparams = upload_params(params, c->nparams);
                 if (!dparams) return YAO_ENOMEM;
             }
-            YAO_TRY(bind_program(bp, dparams));
+            if (also) {
+                auto job = [&](const BoundProgram* b) {
+                    return BindJob{b->d.ops, b->dbinds, b->dfacs, dparams, (int)b->prog.binds.size(), 0};
+                };
+                YAO_TRY(launch_bind_pair(job(bp), job(also)));
+                *also_bound = true;
+            } else {
+                YAO_TRY(bind_program(bp, dparams));
+            }
             return launch_forward_passes(*P, bp->prog, bp->d, data, dtype, n, B, sc, nullptr, bp);
         }
     }
@@ -741,23 +750,23 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     const int n = s->n, B = s->batch;
     const size_t elems = s->elems();
     const int G = (int)c->gates.size();
-    hipStream_t st = stream();
     int t, cb, L;
     tile_geometry(n, B, s->dtype, true, &t, &cb, &L);
     const Plan* P = &get_plan(c, 0, G, B, t, cb, L, true, s->dtype == YAO_C64 ? 8 : 16);
     const BoundProgram* bp = bound_program(*P, c, true, s->dtype, nullptr, nullptr);
     if (bp) compiled_form(P, bp, c, nullptr, nullptr, true, s->dtype, n, B);
+    // Partial columns: a tile pass writes one per tile of every gradient it carries, a standalone gate its
+    // blocks; where both happen the rest are cleared first.
     const int ntiles = 1 << (n - (P->t - P->c));
-    const int W = std::max(ntiles, adjoint_nblk(n, 1, B));
+    bool tiles_only = true;
+    for (const HostPass& pass : P->passes) tiles_only &= pass.standalone < 0;
+    const int W = tiles_only ? ntiles : std::max(ntiles, adjoint_nblk(n, 1, B));
     const int nslots = count_slots(c);
     double* psi = (double*)workspace(WS_PSI64, elems * 16);
     void* lam = workspace(WS_LAM, s->bytes());
     double* gpartial = (double*)workspace(WS_PARTIAL, sizeof(double) * (size_t)std::max(1, nslots) * B * W);
-    const size_t hp = hpsi_partial_doubles(h, n, B, s->dtype);
-    double* misc = (double*)workspace(WS_MISC, sizeof(double) * (hp + (size_t)B + (size_t)std::max(1, nslots) * B));
-    if (!psi || !lam || !gpartial || !misc) return YAO_ENOMEM;
-    double* edev = misc + hp;
-    double* sums = edev + B;
+    double* epartial = (double*)workspace(WS_MISC, sizeof(double) * std::max((size_t)B, hpsi_partial_doubles(h, n, B, s->dtype)));
+    if (!psi || !lam || !gpartial || !epartial) return YAO_ENOMEM;
 
     YAO_TRY(pauli_upload(h));
     int width = 0;
@@ -767,27 +776,24 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
         dp = upload_params(params, c->nparams);
         if (!dp) return YAO_ENOMEM;
     }
-    YAO_TRY(forward_sweep(s->data, s->dtype, n, B, c, params, width, options().tile_qubits, dp));
+    bool bound = false;
+    YAO_TRY(forward_sweep(s->data, s->dtype, n, B, c, params, width, options().tile_qubits, dp, bp, &bound));
 
     Program hprog;
     if (!bp) YAO_TRY(build_program(*P, c, params, true, s->dtype, hprog));
-    YAO_TRY(launch_convert(s->data, s->dtype, psi, YAO_C128, elems));
-    YAO_TRY(launch_hpsi_dev(s->data, s->dtype, lam, s->dtype, n, B, h, misc, edev));
-    if (nslots) YAO_TRY(launch_fill(gpartial, (size_t)nslots * B * W, 0.0));
+    int we = 0;
+    YAO_TRY(launch_seed(s->data, s->dtype, psi, lam, n, B, h, epartial, &we));
+    if (nslots && !tiles_only) YAO_TRY(launch_fill(gpartial, (size_t)nslots * B * W, 0.0));
     DevProgram hd;
-    if (bp) YAO_TRY(bind_program(bp, dp));
-    else YAO_TRY(upload_program(hprog, hd, WS_MAT2));
+    if (!bp) YAO_TRY(upload_program(hprog, hd, WS_MAT2));
+    else if (!bound) YAO_TRY(bind_program(bp, dp));
     const Program& prog = bp ? bp->prog : hprog;
     YAO_TRY(launch_backward_passes(*P, prog, bp ? bp->d : hd, c, params, psi, lam, s->dtype, n, B, gpartial, W, bp));
-    if (nslots) YAO_TRY(launch_row_sums(gpartial, nslots * B, W, sums));
-    const size_t nres = (size_t)B + (size_t)nslots * B;
-    double* hres = (double*)pinned(WS_PARTIAL, sizeof(double) * nres);
-    if (!hres) return YAO_ENOMEM;
-    YAO_HIP(hipMemcpyAsync(hres, edev, sizeof(double) * nres, hipMemcpyDeviceToHost, st));
+    const double *eh = nullptr, *sums = nullptr;
     double dend = 0;
-    YAO_TRY(launch_maxdiff(psi, YAO_C128, psi0, s->dtype, elems, &dend));  // synchronises the stream
-    for (int b = 0; b < B; ++b) energy[b] = hres[b];
-    gather_gradients(c, prog.slot_of_gate, hres + B, B, reduce_batch, grad);
+    YAO_TRY(launch_finish(epartial, B, we, gpartial, nslots * B, W, psi, psi0, s->dtype, elems, &eh, &sums, &dend));
+    for (int b = 0; b < B; ++b) energy[b] = eh[b];
+    gather_gradients(c, prog.slot_of_gate, sums, B, reduce_batch, grad);
     if (drift) *drift = dend;
     if (check_drift && options().drift_tol > 0 && dend > options().drift_tol)
         return set_error(YAO_EDRIFT, "uncomputed input differs from the input by %.3g > %.3g", dend,

@@ -259,8 +259,11 @@ int launch_backward_passes(const Plan& P, const Program& prog, const DevProgram&
 int forward_fused(void* data, int dtype, int n, int B, const yao_circuit* c, const double* params);
 // Forward sweep at fusion width `width` (0: none) over tiles of tq qubits (<= 0: default);
 // dparams: c's parameters already on the device, or null.
+// also: another program of c to bind in the same launch; *also_bound tells whether that happened (a
+// sweep from a host-built program binds nothing).
+struct BoundProgram;
 int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, const double* params, int width, int tq,
-                  const double* dparams);
+                  const double* dparams, const BoundProgram* also = nullptr, bool* also_bound = nullptr);
 // Device-bound programs (built once per plan; see BindRec).
 // One circuit of a batch whose whole state fits one tile, run start to end by one workgroup
 // (k_small_circuit): forward program, then H psi and the energy, then the reverse program
@@ -291,6 +294,7 @@ struct BindJob {
     int nb, pad;
 };
 int launch_bind_jobs(const BindJob* jobs, int njobs, int max_nb);
+int launch_bind_pair(const BindJob& a, const BindJob& b);
 // count circuits of n qubits each, one workgroup apiece.
 int launch_small_circuits(const SmallCircuit* items, int count, int n);
 constexpr int kSmallMaxQubits = 12;  // psi and lambda in FP64: 32 B x 2^12 = 128 KiB of LDS

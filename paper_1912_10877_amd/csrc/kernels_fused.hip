@@ -1512,7 +1512,8 @@ __global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsRec* __re
 constexpr int kObsGatherThreads = 256;
 template <typename RP, typename RO, bool OUT, int RB>
 __global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather(PassArgs a, const ObsRec* __restrict__ recs, int nrec,
-                                                                  double* __restrict__ partial)
+                                                                  double* __restrict__ partial,
+                                                                  double2* __restrict__ psi64)
 {
     constexpr int N = 1 << RB;
     using VP = vec2_t<RP>;
@@ -1527,6 +1528,11 @@ __global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather(PassArgs a, co
     VP own[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) own[r] = gp[gid | ((uint32_t)r << top)];
+    if (psi64) {  // the state widened, for the reverse sweep that starts from H psi
+#pragma unroll
+        for (int r = 0; r < N; ++r)
+            psi64[gid | ((uint32_t)r << top)] = make_double2((double)own[r].x, (double)own[r].y);
+    }
     double orr[N], oi[N];
     obs_terms<RB, true, VP>(cptr(recs), nrec, gid, 0,
                       [&](uint32_t x, VP (&q)[N]) __attribute__((always_inline)) {
@@ -1713,6 +1719,15 @@ __global__ void k_bind(POp* __restrict__ ops, const BindRec* __restrict__ binds,
     bind_one(ops, binds[b], facs, params);
 }
 
+// Two programs for one set of parameters (a step's forward and reverse sweep).
+__global__ void k_bind_pair(BindJob a, BindJob b)
+{
+    const BindJob& j = blockIdx.y ? b : a;
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= j.nb) return;
+    bind_one(j.ops, j.binds[k], j.facs, j.params);
+}
+
 // Many programs at once: job blockIdx.y, record blockIdx.x * blockDim.x + threadIdx.x.
 __global__ void k_bind_jobs(const BindJob* __restrict__ jobs)
 {
@@ -1748,6 +1763,15 @@ int launch_bind(POp* ops, const BindRec* binds, int nbinds, const BindFac* facs,
 {
     if (nbinds <= 0) return 0;
     k_bind<<<(nbinds + 255) / 256, 256, 0, stream()>>>(ops, binds, nbinds, facs, params);
+    YAO_HIP(hipGetLastError());
+    return 0;
+}
+
+int launch_bind_pair(const BindJob& a, const BindJob& b)
+{
+    const int nb = std::max(a.nb, b.nb);
+    if (nb <= 0) return 0;
+    k_bind_pair<<<dim3((nb + 255) / 256, 2), 256, 0, stream()>>>(a, b);
     YAO_HIP(hipGetLastError());
     return 0;
 }
@@ -2139,11 +2163,12 @@ size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype, int 
 // H psi into out (out == nullptr: the energy only) and the partials of the energy in
 // partial[b * W + column]; *W receives the row length (OBS_TILES: per pass and tile, in tile order).
 int launch_obs_passes(const void* psi, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
-                      double* partial, int* W, int use)
+                      double* partial, int* W, int use, double* psi64)
 {
     const ObsPlan* P = obs_plan(h, n, B, dtype, use);
     if (!P) return YAO_ENOMEM;
     if (!P->ok) return set_error(YAO_EINVAL, "observable has an X mask wider than a tile");
+    if (psi64 && !P->gather) return set_error(YAO_EINVAL, "tile passes do not widen the state");
     *W = obs_columns(P, n);
     const int nz = g_zbatch.zs ? g_zbatch.nz : 1;
     PassArgs a;
@@ -2159,9 +2184,9 @@ int launch_obs_passes(const void* psi, int dtype, void* out, int out_dtype, int 
             using RO = decltype(ro);
             constexpr bool OUT = decltype(with)::value;
             if (obs_gather_reg_bits(n) == 1)
-                k_obs_gather<RP, RO, OUT, 1><<<grid, obs_gather_threads(n), 0, stream()>>>(a, P->drecs, P->passes[0].r1, partial);
+                k_obs_gather<RP, RO, OUT, 1><<<grid, obs_gather_threads(n), 0, stream()>>>(a, P->drecs, P->passes[0].r1, partial, (double2*)psi64);
             else
-                k_obs_gather<RP, RO, OUT, 2><<<grid, obs_gather_threads(n), 0, stream()>>>(a, P->drecs, P->passes[0].r1, partial);
+                k_obs_gather<RP, RO, OUT, 2><<<grid, obs_gather_threads(n), 0, stream()>>>(a, P->drecs, P->passes[0].r1, partial, (double2*)psi64);
             YAO_HIP(hipGetLastError());
             return 0;
         });

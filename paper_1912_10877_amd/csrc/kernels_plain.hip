@@ -262,6 +262,45 @@ __global__ __launch_bounds__(256) void k_row_sums(const double* __restrict__ par
     if (lane == 0) sums[r] = s;
 }
 
+// The end of a reverse sweep in one launch: ne + ng row sums (energy partials, rows of we; gradient
+// partials, rows of wg) by a wave each, as k_row_sums, into out[0 .. ne + ng), and the workgroups behind
+// those the maxima of |a - b| over their elements, one each, into the entries that follow.
+template <typename RB>
+__global__ __launch_bounds__(kThreads) void k_finish(const double* __restrict__ e, int ne, int we,
+                                                     const double* __restrict__ g, int ng, int wg, int nrows,
+                                                     const double2* __restrict__ a, const vec2_t<RB>* __restrict__ b,
+                                                     uint64_t elems, double* __restrict__ out)
+{
+    __shared__ double red[kThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if ((int)blockIdx.x < nrows) {
+        const int r = blockIdx.x * (kThreads / 64) + wave;
+        if (r >= ne + ng) return;
+        const int n = r < ne ? we : wg;
+        const double* row = r < ne ? e + (uint64_t)r * we : g + (uint64_t)(r - ne) * wg;
+        double s = 0;
+        for (int j = lane; j < n; j += 64) s += row[j];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (lane == 0) out[r] = s;
+        return;
+    }
+    const unsigned blk = blockIdx.x - nrows, nb = gridDim.x - nrows;
+    double m = 0;
+    for (uint64_t i = (uint64_t)blk * kThreads + threadIdx.x; i < elems; i += (uint64_t)nb * kThreads) {
+        const double2 u = a[i];
+        const vec2_t<RB> v = b[i];
+        const double dr = u.x - (double)v.x, di = u.y - (double)v.y;
+        m = fmax(m, sqrt(dr * dr + di * di));
+    }
+    for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off, 64));
+    if (lane == 0) red[wave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int k = 1; k < kThreads / 64; ++k) m = fmax(m, red[k]);
+        out[ne + ng + blk] = m;
+    }
+}
+
 // The same for rows too long for one wave (a 25-qubit energy has 24576 partials: 128 us with a
 // wave, bound by the latency of its 384 dependent loads): a workgroup per row, each thread a
 // strided sum, then a fixed tree.
@@ -788,6 +827,23 @@ int launch_hpsi_dev(const void* data, int dtype, void* out, int out_dtype, int n
     return launch_row_sums(partial, B, nbx, energy_dev);
 }
 
+// H psi, its energy partials (partial[b * *W + column], hpsi_partial_doubles of them; not summed) and psi in
+// FP64: one launch where H psi is one, else the conversion, H psi and, outside the tile passes, its sums.
+int launch_seed(const void* data, int dtype, double* psi64, void* lam, int n, int B, const yao_pauli_sum* h,
+                double* partial, int* W)
+{
+    const bool one = obs_one_launch(h, n, B, dtype);
+    if (!one) YAO_TRY(launch_convert(data, dtype, psi64, YAO_C128, (size_t(1) << n) * (size_t)B));
+    if (obs_passes_ok(h, n, B, dtype, OBS_VECTOR))
+        return launch_obs_passes(data, dtype, lam, dtype, n, B, h, partial, W, OBS_VECTOR, one ? psi64 : nullptr);
+    double* sums = (double*)workspace(WS_PARTIAL2, sizeof(double) * (size_t)B);
+    if (!sums) return YAO_ENOMEM;
+    YAO_TRY(launch_hpsi_dev(data, dtype, lam, dtype, n, B, h, partial, sums));
+    YAO_HIP(hipMemcpyAsync(partial, sums, sizeof(double) * (size_t)B, hipMemcpyDeviceToDevice, stream()));
+    *W = 1;
+    return 0;
+}
+
 int launch_convert(const void* src, int src_dtype, void* dst, int dst_dtype, size_t elems)
 {
     unsigned nb = (unsigned)std::min<uint64_t>((elems + kThreads - 1) / kThreads, 65536);
@@ -853,6 +909,49 @@ int launch_maxdiff(const void* a, int a_dtype, const void* b, int b_dtype, size_
     double m = 0;
     for (unsigned t = 0; t < nb; ++t) m = hs[t] > m ? hs[t] : m;
     *out = m;
+    return 0;
+}
+
+// Row sums of the energy and gradient partials and the largest |psi - psi0| of a reverse sweep, to the
+// host: energy[ne], sums[ng] (pinned memory the caller reads until its next call) and *drift. Rows
+// over kLongRow entries are summed by launches of their own.
+int launch_finish(const double* e, int ne, int we, const double* g, int ng, int wg, const double* psi, const void* psi0,
+                  int dtype, size_t elems, const double** energy, const double** sums, double* drift)
+{
+    const int nb = (int)std::min<size_t>(512, (elems + 4 * kThreads - 1) / (4 * kThreads));
+    const size_t nres = (size_t)ne + ng + nb;
+    double* tmp = (double*)workspace(WS_PARTIAL2, sizeof(double) * (nres + ne + ng));
+    double* host = (double*)pinned(WS_PARTIAL, sizeof(double) * nres);
+    if (!tmp || !host) return YAO_ENOMEM;
+    if (we > kLongRow) {
+        YAO_TRY(launch_row_sums(e, ne, we, tmp + nres));
+        e = tmp + nres;
+        we = 1;
+    }
+    if (wg > kLongRow && ng > 0) {
+        YAO_TRY(launch_row_sums(g, ng, wg, tmp + nres + ne));
+        g = tmp + nres + ne;
+        wg = 1;
+    }
+    // A few results go straight to the pinned buffer; a copy of many is cheaper than their single writes.
+    const bool direct = nres <= 512;
+    double* out = direct ? host : tmp;
+    const int nrows = (ne + ng + kThreads / 64 - 1) / (kThreads / 64);
+    hipStream_t st = stream();
+    if (dtype == YAO_C64)
+        k_finish<float><<<nrows + nb, kThreads, 0, st>>>(e, ne, we, g, ng, wg, nrows, (const double2*)psi,
+                                                         (const float2*)psi0, elems, out);
+    else
+        k_finish<double><<<nrows + nb, kThreads, 0, st>>>(e, ne, we, g, ng, wg, nrows, (const double2*)psi,
+                                                          (const double2*)psi0, elems, out);
+    YAO_HIP(hipGetLastError());
+    if (!direct) YAO_HIP(hipMemcpyAsync(host, tmp, sizeof(double) * nres, hipMemcpyDeviceToHost, st));
+    YAO_HIP(hipStreamSynchronize(st));
+    *energy = host;
+    *sums = host + ne;
+    double m = 0;
+    for (int k = 0; k < nb; ++k) m = host[ne + ng + k] > m ? host[ne + ng + k] : m;
+    *drift = m;
     return 0;
 }
 

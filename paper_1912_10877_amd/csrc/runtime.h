@@ -131,7 +131,7 @@ size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype, int 
 // Qubits of each observable pass's tile (the non-tile qubits index the tiles, ascending).
 int obs_tile_qubits(const yao_pauli_sum* h, int n, int B, int dtype);
 int launch_obs_passes(const void* psi, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
-                      double* partial, int* W, int use);
+                      double* partial, int* W, int use, double* psi64 = nullptr);
 // Whether H psi of such a state is one launch (its partials: obs_partial_doubles columns), and that launch
 // as a Lanczos step: v = src / |src| with |src|^2 = the sum of npart[0 .. nn), out = H v (another buffer),
 // *norm = |src| and the partials of <v|H v>.
@@ -141,6 +141,10 @@ int launch_lanczos_hv(const void* src, void* v, void* out, int dtype, int n, con
 void drop_obs_plans(const yao_pauli_sum* h);
 int launch_hpsi_dev(const void* data, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
                     double* partial, double* energy_dev);
+int launch_seed(const void* data, int dtype, double* psi64, void* lam, int n, int B, const yao_pauli_sum* h,
+                double* partial, int* W);
+int launch_finish(const double* e, int ne, int we, const double* g, int ng, int wg, const double* psi, const void* psi0,
+                  int dtype, size_t elems, const double** energy, const double** sums, double* drift);
 // Precision conversion / copies between states of equal shape.
 int launch_convert(const void* src, int src_dtype, void* dst, int dst_dtype, size_t elems);
 // <a_b|b_b> per batch slot (host results), FP64 accumulation.
