@@ -379,7 +379,7 @@ def measure(state: State, locs, u) -> np.ndarray:
     u = np.ascontiguousarray(np.asarray(u, np.float64).reshape(state.batch, -1))
     out = np.zeros(u.shape, np.uint64)
     _check(lib().yao_measure(state.h, _ptr(l), len(l), u.shape[1], _ptr(u), _ptr(out)))
-    return out.astype(np.int64)
+    return out.view(np.int64)  # outcomes stay below 2^30
 
 
 def measure_collapse(state: State, locs, u):

@@ -16,6 +16,7 @@
 //   4. measure! keeps the amplitudes whose locs read the outcome and divides them by
 //      sqrt(P[b][x_b]); the others become 0.
 #include <algorithm>
+#include <type_traits>
 
 #include "runtime.h"
 
@@ -81,8 +82,23 @@ __global__ __launch_bounds__(kMThreads) void k_sum_chunks(const double* __restri
 // thread i then scans the 8 consecutive values 8i..8i+7 (one padding slot per 32 values keeps
 // those reads on distinct banks), the 256 thread sums are scanned in LDS (Hillis-Steele, fixed
 // order), and each thread adds its prefix.
-__global__ __launch_bounds__(kMThreads) void k_scan_chunks(const double* p, double* q, uint64_t len, int nchunks,
-                                                           double* __restrict__ tot)
+// The last Q of every 16 and of every 128 outcomes go to tables of their own (len a multiple of
+// kChunk), which the sampling reads before the 16 outcomes themselves. T: double, probabilities; or the
+// amplitudes of a single-slot state whose outcomes are its indices: then |psi|^2 is taken here (as in
+// k_marginal) and the probabilities are neither written nor read (24 qubits complex128: 78 us where
+// the two kernels took 129).
+__device__ __forceinline__ double probability(double v)
+{
+    return v;
+}
+template <typename V> __device__ __forceinline__ double probability(const V& a)
+{
+    return (double)a.x * a.x + (double)a.y * a.y;
+}
+template <typename T>
+__global__ __launch_bounds__(kMThreads) void k_scan_chunks(const T* p, double* q, uint64_t len, int nchunks,
+                                                           double* __restrict__ tot, double* __restrict__ q16,
+                                                           double* __restrict__ q128)
 {
     __shared__ double vals[kChunk + kChunk / 32];
     __shared__ double sh[2][kMThreads];
@@ -93,7 +109,7 @@ __global__ __launch_bounds__(kMThreads) void k_scan_chunks(const double* p, doub
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int e = threadIdx.x + kMThreads * i;
-        vals[slot(e)] = (uint64_t)e < lim ? p[base + e] : 0.0;
+        vals[slot(e)] = (uint64_t)e < lim ? probability(p[base + e]) : 0.0;
     }
     __syncthreads();
     double v[8];
@@ -122,6 +138,11 @@ __global__ __launch_bounds__(kMThreads) void k_scan_chunks(const double* p, doub
         if ((uint64_t)e < lim) q[base + e] = vals[slot(e)];
     }
     if (threadIdx.x == kMThreads - 1) tot[(uint64_t)b * nchunks + blockIdx.x] = sh[cur][kMThreads - 1];
+    if (nchunks > 1) {
+        if (threadIdx.x < kChunk / 16) q16[base / 16 + threadIdx.x] = vals[slot(threadIdx.x * 16 + 15)];
+        else if (threadIdx.x < kChunk / 16 + kChunk / 128)
+            q128[base / 128 + threadIdx.x - kChunk / 16] = vals[slot((threadIdx.x - kChunk / 16) * 128 + 127)];
+    }
 }
 
 // Exclusive scan of the chunk totals of slot b = blockIdx.x: thread i scans a contiguous
@@ -164,12 +185,16 @@ __global__ __launch_bounds__(kMThreads) void k_scan_totals(double* __restrict__ 
 
 // Shots s of slot b: smallest x with C[b][x] > u * C[b][last], C[x] = Q[x] + O[x / kChunk]
 // (chunk 0: Q[x]). First the chunk: the smallest c whose last entry C exceeds the target; then
-// the entry inside it. Each thread takes kShots shots of one slot whose searches run level by
-// level together, so their loads are in flight at once.
+// the entry inside it, by the tables of every 128th and every 16th entry: each of the three steps
+// reads one line of memory whose entries are compared at once, where a binary search over the chunk's
+// 16 KiB read eight (a million shots of 24 qubits: 194 us, at 5.5 TB/s of lines mostly unused; 78 us now). Each
+// thread takes kShots shots of one slot whose searches run level by level together, so their loads
+// are in flight at once.
 constexpr int kShots = 2;
 __global__ __launch_bounds__(kMThreads) void k_sample(const double* __restrict__ q, const double* __restrict__ off,
                                                       uint64_t len, int nchunks, int B, int nshots,
-                                                      const double* __restrict__ u, uint64_t* __restrict__ out)
+                                                      const double* __restrict__ u, uint64_t* __restrict__ out,
+                                                      const double* __restrict__ q16, const double* __restrict__ q128)
 {
     const int per = (nshots + kShots - 1) / kShots;
     const uint64_t t = (uint64_t)blockIdx.x * kMThreads + threadIdx.x;
@@ -213,18 +238,42 @@ __global__ __launch_bounds__(kMThreads) void k_sample(const double* __restrict__
         hi[i] = (end < len ? end : len) - 1;
         o[i] = clo[i] > 0 ? O[clo[i]] : 0.0;
     }
-    for (int step = 0; step < 32; ++step) {
-        bool any = false;
+    if (nchunks > 1) {
+        // Entries of the run of N at tab + at whose C does not exceed the target, the last one left out.
+        auto before = [&](const double* tab, uint64_t at, auto n, int i) __attribute__((always_inline)) {
+            constexpr int N = decltype(n)::value;
+            double v[N];
 #pragma unroll
-        for (int i = 0; i < kShots; ++i)
-            if (lo[i] < hi[i]) {
-                any = true;
-                const uint64_t mid = (lo[i] + hi[i]) >> 1;
-                const double c = clo[i] > 0 ? Q[mid] + o[i] : Q[mid];
-                if (c > target[i]) hi[i] = mid;
-                else lo[i] = mid + 1;
-            }
-        if (!any) break;
+            for (int e = 0; e < N - 1; ++e) v[e] = tab[at + e];
+            int cnt = 0;
+#pragma unroll
+            for (int e = 0; e < N - 1; ++e) cnt += (clo[i] > 0 ? v[e] + o[i] : v[e]) > target[i] ? 0 : 1;
+            return cnt;
+        };
+        uint64_t at[kShots];
+#pragma unroll
+        for (int i = 0; i < kShots; ++i) {
+            at[i] = (b * len + lo[i]) / 128;
+            at[i] = (at[i] + before(q128, at[i], std::integral_constant<int, 16>(), i)) * 8;
+        }
+#pragma unroll
+        for (int i = 0; i < kShots; ++i) at[i] = (at[i] + before(q16, at[i], std::integral_constant<int, 8>(), i)) * 16;
+#pragma unroll
+        for (int i = 0; i < kShots; ++i) lo[i] = at[i] + before(q, at[i], std::integral_constant<int, 16>(), i) - b * len;
+    } else {
+        for (int step = 0; step < 32; ++step) {
+            bool any = false;
+#pragma unroll
+            for (int i = 0; i < kShots; ++i)
+                if (lo[i] < hi[i]) {
+                    any = true;
+                    const uint64_t mid = (lo[i] + hi[i]) >> 1;
+                    const double c = clo[i] > 0 ? Q[mid] + o[i] : Q[mid];
+                    if (c > target[i]) hi[i] = mid;
+                    else lo[i] = mid + 1;
+                }
+            if (!any) break;
+        }
     }
 #pragma unroll
     for (int i = 0; i < kShots; ++i)
@@ -333,12 +382,18 @@ int launch_outcome_probs(const yao_state* s, const int* locs, int k, double* pro
 
 // Cumulative sums of each slot's row of len = 2^k doubles, p -> q (q may be p); tot: B * nchunks
 // doubles.
-int launch_cdf(const double* p, double* q, int k, int B, double* tot)
+static int scan_cdf(const void* p, int type, double* q, int k, int B, double* tot)
 {
     const uint64_t len = uint64_t(1) << k;
     const int nchunks = (int)((len + kChunk - 1) / kChunk);
+    double* q16 = tot + 2 * (size_t)B * nchunks;
+    double* q128 = q16 + (size_t)B * (len / 16);
     const int pi = prof_begin(YAO_KF_MEASURE);
-    k_scan_chunks<<<dim3(nchunks, B), kMThreads, 0, stream()>>>(p, q, len, nchunks, tot);
+    const dim3 grid(nchunks, B);
+    hipStream_t st = stream();
+    if (type == YAO_C64) k_scan_chunks<float2><<<grid, kMThreads, 0, st>>>((const float2*)p, q, len, nchunks, tot, q16, q128);
+    else if (type == YAO_C128) k_scan_chunks<double2><<<grid, kMThreads, 0, st>>>((const double2*)p, q, len, nchunks, tot, q16, q128);
+    else k_scan_chunks<double><<<grid, kMThreads, 0, st>>>((const double*)p, q, len, nchunks, tot, q16, q128);
     YAO_HIP(hipGetLastError());
     if (nchunks > 1) {
         k_scan_totals<<<B, kMThreads, 0, stream()>>>(tot, nchunks, q, len);
@@ -348,9 +403,26 @@ int launch_cdf(const double* p, double* q, int k, int B, double* tot)
     return 0;
 }
 
+int launch_cdf(const double* p, double* q, int k, int B, double* tot)
+{
+    return scan_cdf(p, -1, q, k, B, tot);
+}
+
+// The cumulative sums of the outcomes of locs straight from the state where they are the indices of a
+// single-slot state; false where they are not (then by way of launch_outcome_probs).
+bool cdf_from_state(const yao_state* s, const int* locs, int k)
+{
+    return s->batch == 1 && k == s->n && locs_are_low(locs, k);
+}
+int launch_cdf_state(const yao_state* s, double* q, double* tot)
+{
+    return scan_cdf(s->data, s->dtype, q, s->n, 1, tot);
+}
+
 size_t cdf_tot_doubles(int k, int B)
 {
-    return 2 * (size_t)B * (((uint64_t(1) << k) + kChunk - 1) / kChunk);
+    const size_t len = size_t(1) << k;
+    return (size_t)B * (2 * ((len + kChunk - 1) / kChunk) + len / 16 + len / 128);
 }
 
 int launch_sample(const double* cdf, const double* tot, int k, int B, int nshots, const double* u, uint64_t* out)
@@ -360,8 +432,9 @@ int launch_sample(const double* cdf, const double* tot, int k, int B, int nshots
     const int nchunks = (int)((len + kChunk - 1) / kChunk);
     const uint64_t threads = (uint64_t)B * ((nshots + kShots - 1) / kShots);
     const int pi = prof_begin(YAO_KF_MEASURE);
-    k_sample<<<(unsigned)((threads + kMThreads - 1) / kMThreads), kMThreads, 0, stream()>>>(cdf, tot, len, nchunks, B,
-                                                                                            nshots, u, out);
+    const double* q16 = tot + 2 * (size_t)B * nchunks;
+    k_sample<<<(unsigned)((threads + kMThreads - 1) / kMThreads), kMThreads, 0, stream()>>>(
+        cdf, tot, len, nchunks, B, nshots, u, out, q16, q16 + (size_t)B * (len / 16));
     prof_end(pi, 16.0 * total + 8.0 * k * total, 0.0);
     YAO_HIP(hipGetLastError());
     return 0;

@@ -210,6 +210,8 @@ int time_evolve(yao_state* s, yao_pauli_sum* h, double t, double tol, int krylov
 // and prob (device, B each). locs_dev: the k locs in device memory.
 int launch_outcome_probs(const yao_state* s, const int* locs, int k, double* prob);
 int launch_cdf(const double* p, double* q, int k, int B, double* tot);
+bool cdf_from_state(const yao_state* s, const int* locs, int k);
+int launch_cdf_state(const yao_state* s, double* q, double* tot);
 size_t cdf_tot_doubles(int k, int B);
 int launch_sample(const double* cdf, const double* tot, int k, int B, int nshots, const double* u, uint64_t* out);
 int launch_collapse(yao_state* s, const double* probs, const int* locs_dev, const int* locs, int k, const uint64_t* x,

@@ -120,3 +120,35 @@ def test_measure_validation():
         yb.measure(s, [0], np.ones((2, 1)))          # u must be < 1
     with pytest.raises(yb.YaoError):
         yb.measure(s, [0], np.full((2, 1), -0.1))
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n,B,k,shots", [(11, 1, 11, 131072), (12, 1, 12, 131073), (13, 1, 13, 1), (13, 2, 12, 65537), (12, 3, 12, 300)])
+def test_chunked_tables_and_pieces(dtype, n, B, k, shots):
+    """One chunk (no tables) and more, outcomes straight from the state or by way of the probabilities,
+    shots at and over the size of a transfer's piece; targets at both ends and on plateaus of
+    zero probability. The rule and bounds above; an invalid number past the first piece is refused and
+    named."""
+    psi = w.random_state(n, B, 7 + n)
+    psi[5:900] = 0
+    psi[(1 << n) - 300:] = 0
+    psi /= np.sqrt(np.sum(np.abs(psi) ** 2, axis=0, keepdims=True))
+    s = yb.State(n, B, dtype)
+    s.upload(psi)
+    psi = s.download().astype(np.complex128)
+    u = np.random.default_rng(n + shots).random((B, shots))
+    u[:, 0] = 0.0
+    u[:, -1] = np.nextafter(1.0, 0.0)
+    got = yb.measure(s, list(range(k)), u)
+    assert got.dtype == np.int64
+    # The oracle reads the register's own amplitudes. The last shot's target is the total to within its
+    # rounding: on the plateau that ends the register it may fall anywhere.
+    bad = check_samples(got[:, :-1], psi, n, list(range(k)), u[:, :-1], 1) if shots > 1 else 0
+    assert bad <= got.size // 1000
+    cdf = np.cumsum(oracle.probs(psi, n, list(range(k))), axis=1)
+    for b in range(B):
+        assert cdf[b, int(got[b, -1])] >= u[b, -1] * cdf[b, -1] - 1e-12
+    if shots > 131072:
+        u[0, shots - 1] = 1.0
+        with pytest.raises(yb.YaoError, match=rf"u\[{shots - 1}\] = 1 is not in"):
+            yb.measure(s, list(range(k)), u)
