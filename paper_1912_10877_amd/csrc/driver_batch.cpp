@@ -31,10 +31,11 @@ constexpr int kBanks = 16;  // streams of the graph
 // Circuits are recorded in phases by state size, each phase waiting for the previous one on
 // every stream: a pass over a tile takes about as long whatever the state size, so a small
 // circuit's one-tile passes running beside a large circuit's passes (hundreds of tiles) hold
-// CUs that the large pass waits for. Phases: >= 2^19 amplitudes, 2^16 .. 2^18, smaller.
+// CUs that the large pass waits for. Phases: >= 2^19 amplitudes (with the level units, whose tiles fill the
+// chip, and states of up to 2^8, whose blocks are too small to hold a CU), 2^16 .. 2^18, smaller.
 int batch_phase(int n)
 {
-    return n >= 19 ? 0 : (n >= 16 ? 1 : 2);
+    return n >= 19 || n < 9 ? 0 : (n >= 16 ? 1 : 2);
 }
 
 struct Tune {
@@ -74,13 +75,29 @@ struct Item {
 // same observable, the same state shape) whose programs are bound on the device: every launch
 // of the unit runs over all of them at once (grid z), each with its own state, records and
 // scratch slice. Any other circuit is a unit of its own, recorded launch by launch.
+//
+// A level unit holds mid-size circuits of any structure (9 to 20 qubits) whose tiles have the same
+// sizes: step i of the unit is pass i of every circuit, one launch whose blocks are told their circuit
+// and tile by a table. Launched circuit by circuit their passes (2 to 64 tiles, 30 to 90 us whatever the
+// number) ran 1.7 at a time however many streams the graph had: of 96 circuits of 8 to 20 qubits
+// half of the 24.9 ms went to passes of at most 64 tiles; in level units the list takes 16.1 ms.
 struct Unit {
     int first = 0, count = 0;  // its items: C.items[first .. first + count)
     bool z = false;
+    int level = -1;            // index in C.levels
     int bank = 0, phase = 0;
     double cost = 0;
     size_t zf = 0, zo = 0, zb = 0;  // its slot tables in C.d_zs (forward, H psi, reverse)
     size_t sp = 0;                  // its state pointers in C.d_ptrs
+};
+
+struct Level {
+    int dtype = 0;
+    int count = 0;
+    void* const* states = nullptr;
+    const int* n = nullptr;
+    std::vector<ManyStep> fwd, bwd;
+    ManyStep obs[2], rows;  // H psi with 1 and 2 register bits; energy and gradient sums
 };
 
 using Key = std::vector<std::tuple<const yao_circuit*, uint64_t, const yao_state*, const yao_pauli_sum*, int>>;
@@ -115,6 +132,8 @@ struct Cache {
     BindJob* d_jobs = nullptr;
     int njobs = 0, max_nb = 0;
     std::vector<Unit> units;  // recording order
+    std::vector<Level> levels;
+    std::vector<void*> level_mem;
     ZSlot* d_zs = nullptr;
     void** d_ptrs = nullptr;
 };
@@ -142,6 +161,7 @@ void free_cache(Cache* c)
     if (c->d_jobs) (void)hipFree(c->d_jobs);
     if (c->d_zs) (void)hipFree(c->d_zs);
     if (c->d_ptrs) (void)hipFree(c->d_ptrs);
+    for (void* p : c->level_mem) (void)hipFree(p);
     if (c->h_params) (void)hipHostFree(c->h_params);
     for (int b = 0; b < kBanks; ++b) {
         if (c->psi64[b]) (void)hipFree(c->psi64[b]);
@@ -406,6 +426,35 @@ bool z_capable(const Item& it)
     return obs_passes_ok(it.h, it.s->n, 1, it.s->dtype, OBS_VECTOR);
 }
 
+// A circuit that a level unit takes: gradients, every gate a tile pass takes, H psi one launch of full
+// blocks (9 to 20 qubits). Its programs may be bound on the device or built on the host.
+bool level_candidate(const Item& it)
+{
+    const int n = it.s->n;
+    if (it.small || n < 9 || n > 20 || it.nslots == 0) return false;
+    for (const GateRec& g : it.c->gates)
+        if (g.k > kMaxFusedK) return false;
+    return obs_one_launch(it.h, n, 1, it.s->dtype);
+}
+// With its plans: tile passes of the generic kernels.
+bool level_capable(const Item& it)
+{
+    if (!level_candidate(it) || it.fwd->c != 0 || it.bwd->c != 0) return false;
+    if ((it.bf && it.bf->jit) || (it.bb && it.bb->jit)) return false;
+    for (const Plan* P : {it.fwd, it.bwd}) {
+        if (!P->valid) return false;
+        for (const HostPass& p : P->passes)
+            if (p.standalone >= 0) return false;
+    }
+    return true;
+}
+// The reverse tiles of level units, where they make a block a CU at least: tuned alone a 20-qubit circuit
+// takes 12 qubits (a 512-thread block a CU), but with other circuits' tiles at hand three
+// 256-thread blocks a CU hide each other's loads (96 circuits of 8 to 20 qubits, complex64: 17.0 ms against
+// 16.1; 40 of 9 to 18, complex128: 2.28 against 1.95; 10 qubits 16.1 and 2.05).
+constexpr int kLevelTile = 11;
+constexpr uint64_t kLevelTiles = 256;
+
 // Scratch of one circuit of a z unit: psi in FP64, lambda, reverse and H psi partial sums.
 size_t z_item_bytes(const Item& it)
 {
@@ -415,6 +464,102 @@ size_t z_item_bytes(const Item& it)
 }
 constexpr size_t kZUnitBytes = size_t(2) << 30;  // scratch of one z unit at most
 constexpr int kZUnitMax = 1024;                   // circuits of one z unit at most
+
+// Device copy of a table, freed with the batch.
+template <typename T> int level_table(Cache& C, const std::vector<T>& v, const T** out)
+{
+    void* p = nullptr;
+    YAO_TRY(dev_alloc(&p, sizeof(T) * v.size()));
+    C.level_mem.push_back(p);
+    if (!v.empty()) YAO_HIP(hipMemcpy(p, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice));
+    *out = (const T*)p;
+    return 0;
+}
+
+// The tables of a level unit over its bank's scratch. Every partial column is written by a pass, and the
+// rows are as long as there are tiles. The longest passes come first in a launch.
+int build_level(Cache& C, const Unit& U)
+{
+    Level& L = C.levels[U.level];
+    L.dtype = C.items[U.first].s->dtype;
+    L.count = U.count;
+    std::vector<void*> states;
+    std::vector<int> ns;
+    std::vector<ManyObs> obs[2];
+    std::vector<uint2> obs_blocks[2], row_blocks;
+    std::vector<ManyRows> rows;
+    std::vector<double*> psi, gp;
+    std::vector<void*> lam;
+    size_t amps = 0, g = 0, e = 0, nf = 0, nb = 0;
+    for (int j = 0; j < U.count; ++j) {
+        const Item& it = C.items[U.first + j];
+        const int n = it.s->n;
+        psi.push_back(C.psi64[U.bank] + 2 * amps);
+        lam.push_back((char*)C.lam[U.bank] + it.s->elem_bytes() * amps);
+        gp.push_back(C.gpart[U.bank] + g);
+        double* hp = C.hpart[U.bank] + e;
+        const size_t cols = hpsi_partial_doubles(it.h, n, 1, L.dtype);
+        amps += size_t(1) << n;
+        g += (size_t)it.nslots * it.W;
+        e += cols;
+        nf = std::max(nf, it.fwd->passes.size());
+        nb = std::max(nb, it.bwd->passes.size());
+        states.push_back(it.s->data);
+        ns.push_back(n);
+        ManyObs o;
+        int rb = 0, blocks = 0;
+        YAO_TRY(many_obs(o, &rb, &blocks, it.s->data, lam.back(), psi.back(), L.dtype, n, it.h, hp));
+        for (int b = 0; b < blocks; ++b) obs_blocks[rb - 1].push_back(make_uint2((unsigned)obs[rb - 1].size(), (unsigned)b));
+        obs[rb - 1].push_back(o);
+        for (const ManyRows& r : {ManyRows{hp, C.d_out + it.out_e, 1, (int)cols}, ManyRows{gp.back(), C.d_out + it.out_g, it.nslots, it.W}}) {
+            for (int b = 0; b < (r.rows + 3) / 4; ++b) row_blocks.push_back(make_uint2((unsigned)rows.size(), (unsigned)b));
+            rows.push_back(r);
+        }
+    }
+    YAO_TRY(level_table(C, states, (void* const**)&L.states));
+    YAO_TRY(level_table(C, ns, &L.n));
+    for (int k = 0; k < 2; ++k) {
+        YAO_TRY(level_table(C, obs[k], (const ManyObs**)&L.obs[k].items));
+        YAO_TRY(level_table(C, obs_blocks[k], &L.obs[k].blocks));
+        L.obs[k].nblocks = (int)obs_blocks[k].size();
+    }
+    YAO_TRY(level_table(C, rows, (const ManyRows**)&L.rows.items));
+    YAO_TRY(level_table(C, row_blocks, &L.rows.blocks));
+    L.rows.nblocks = (int)row_blocks.size();
+    for (int dir = 0; dir < 2; ++dir) {
+        for (size_t p = 0; p < (dir ? nb : nf); ++p) {
+            std::vector<int> in;
+            for (int j = 0; j < U.count; ++j) {
+                const Item& it = C.items[U.first + j];
+                if (p < (dir ? it.bwd : it.fwd)->passes.size()) in.push_back(j);
+            }
+            auto nops = [&](int j) {
+                const Item& it = C.items[U.first + j];
+                return (dir ? bwd_prog(it) : fwd_prog(it)).pass_nops[p];
+            };
+            std::stable_sort(in.begin(), in.end(), [&](int a, int b) { return nops(a) > nops(b); });
+            ManyStep st;
+            std::vector<char> items(many_pass_bytes() * in.size());
+            std::vector<uint2> blocks;
+            for (size_t k = 0; k < in.size(); ++k) {
+                const Item& it = C.items[U.first + in[k]];
+                int ntiles = 0, threads = 0;
+                size_t lds = 0;
+                YAO_TRY(many_pass(items.data() + many_pass_bytes() * k, dir ? *it.bwd : *it.fwd, dir ? bwd_prog(it) : fwd_prog(it),
+                                  dir ? it.db : it.df, (int)p, L.dtype, dir ? (void*)psi[in[k]] : it.s->data,
+                                  dir ? lam[in[k]] : nullptr, dir ? gp[in[k]] : nullptr, dir ? it.W : 0, &ntiles, &threads, &lds));
+                st.threads = std::max(st.threads, threads);
+                st.lds = std::max(st.lds, lds);
+                for (int b = 0; b < ntiles; ++b) blocks.push_back(make_uint2((unsigned)k, (unsigned)b));
+            }
+            YAO_TRY(level_table(C, items, (const char**)&st.items));
+            YAO_TRY(level_table(C, blocks, &st.blocks));
+            st.nblocks = (int)blocks.size();
+            (dir ? L.bwd : L.fwd).push_back(st);
+        }
+    }
+    return 0;
+}
 
 int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit* const* circs,
                 const double* const* params, yao_pauli_sum* const* h)
@@ -492,19 +637,40 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         for (Item& it : C.items)
             if (!it.small && it.s->n == kv.first.first && it.s->dtype == kv.first.second) it.tune = t;
     }
+    if (C.opt.tile_qubits == 0) {
+        uint64_t tiles = 0;
+        for (const Item& it : C.items)
+            if (level_candidate(it)) tiles += (uint64_t(1) << it.s->n) >> std::min(it.s->n, kLevelTile);
+        for (Item& it : C.items)
+            if (tiles >= kLevelTiles && level_candidate(it)) it.tune.tq_b = kLevelTile;
+    }
     YAO_TRY(build_programs(C, params, true));
     for (Item& it : C.items)
-        if (!it.small) it.W = reverse_stride(*it.bwd);
+        if (!it.small) it.W = level_capable(it) ? 1 << (it.bwd->n - (it.bwd->t - it.bwd->c)) : reverse_stride(*it.bwd);
 
     // Units: circuits of one structure with bound programs together (z units), every other
     // circuit alone; the small circuits stay outside the units.
     std::vector<std::vector<int>> members;
-    std::vector<bool> zunit;
+    std::vector<bool> zunit, levelunit;
     {
+        std::map<std::tuple<int, int, int>, std::pair<int, size_t>> levels;  // (dtype, tiles) -> unit, its scratch
         std::map<std::pair<int, int>, std::vector<int>> open;  // (n, dtype) -> z units
         for (int i = 0; i < (int)C.items.size(); ++i) {
             const Item& it = C.items[i];
             if (it.small) continue;
+            if (level_capable(it)) {
+                const size_t bytes = z_item_bytes(it);
+                auto& u = levels[std::make_tuple(it.s->dtype, it.fwd->t, it.bwd->t)];
+                if (u.second == 0 || u.second + bytes > kZUnitBytes) {
+                    u = {(int)members.size(), 0};
+                    members.emplace_back();
+                    zunit.push_back(false);
+                }
+                u.second += bytes;
+                members[u.first].push_back(i);
+                C.items[i].phase = 0;
+                continue;
+            }
             if (!z_capable(it)) {
                 members.push_back({i});
                 zunit.push_back(false);
@@ -531,6 +697,8 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
             members[u].push_back(i);
         }
     }
+    levelunit.assign(members.size(), false);
+    for (size_t u = 0; u < members.size(); ++u) levelunit[u] = level_capable(C.items[members[u][0]]);
     // By phase, then largest units first, each on the least loaded stream of its phase; the
     // items are reordered so that each unit's circuits follow each other (their energies and
     // gradient sums then sit in consecutive output entries).
@@ -554,6 +722,10 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
             U.first = (int)sorted.size();
             U.count = (int)members[u].size();
             U.z = zunit[u];
+            if (levelunit[u]) {
+                U.level = (int)C.levels.size();
+                C.levels.emplace_back();
+            }
             U.phase = C.items[members[u][0]].phase;
             U.cost = ucost[u];
             for (int i : members[u]) {
@@ -585,10 +757,24 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         load[best] += U.cost;
         const Item& lead = C.items[U.first];
         const size_t N = size_t(1) << lead.s->n, nz = (size_t)U.count;
-        psi_b[best] = std::max(psi_b[best], nz * 16 * N);
-        lam_b[best] = std::max(lam_b[best], nz * lead.s->elem_bytes() * N);
-        gp_b[best] = std::max(gp_b[best], nz * sizeof(double) * (size_t)std::max(1, lead.nslots) * lead.W);
-        hp_b[best] = std::max(hp_b[best], nz * sizeof(double) * hpsi_partial_doubles(lead.h, lead.s->n, 1, lead.s->dtype));
+        if (U.level >= 0) {
+            size_t amps = 0, g = 0, e = 0;
+            for (int j = 0; j < U.count; ++j) {
+                const Item& it = C.items[U.first + j];
+                amps += size_t(1) << it.s->n;
+                g += (size_t)it.nslots * it.W;
+                e += hpsi_partial_doubles(it.h, it.s->n, 1, it.s->dtype);
+            }
+            psi_b[best] = std::max(psi_b[best], 16 * amps);
+            lam_b[best] = std::max(lam_b[best], lead.s->elem_bytes() * amps);
+            gp_b[best] = std::max(gp_b[best], sizeof(double) * g);
+            hp_b[best] = std::max(hp_b[best], sizeof(double) * e);
+        } else {
+            psi_b[best] = std::max(psi_b[best], nz * 16 * N);
+            lam_b[best] = std::max(lam_b[best], nz * lead.s->elem_bytes() * N);
+            gp_b[best] = std::max(gp_b[best], nz * sizeof(double) * (size_t)std::max(1, lead.nslots) * lead.W);
+            hp_b[best] = std::max(hp_b[best], nz * sizeof(double) * hpsi_partial_doubles(lead.h, lead.s->n, 1, lead.s->dtype));
+        }
         if (U.z) {
             U.zf = nzs;
             U.zo = nzs + nz;
@@ -655,6 +841,8 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         YAO_HIP(hipMemcpy(C.d_zs, zs.data(), sizeof(ZSlot) * nzs, hipMemcpyHostToDevice));
         YAO_HIP(hipMemcpy(C.d_ptrs, ptrs.data(), sizeof(void*) * nptr, hipMemcpyHostToDevice));
     }
+    for (const Unit& U : C.units)
+        if (U.level >= 0) YAO_TRY(build_level(C, U));
     // Descriptors and bind jobs of the small circuits, by qubit count.
     {
         std::vector<const Item*> sm;
@@ -693,9 +881,9 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
                 C.max_nb = std::max(C.max_nb, nb);
             }
         }
-        // The z units' circuits bind here too: one launch binds every such program.
+        // The z and level units' circuits bind here too: one launch binds every such program.
         for (const Unit& U : C.units) {
-            if (!U.z) continue;
+            if (!U.z && U.level < 0) continue;
             for (int j = 0; j < U.count; ++j) {
                 const Item& it = C.items[U.first + j];
                 for (const BoundProgram* b : {it.bf, it.nslots ? it.bb : nullptr}) {
@@ -766,6 +954,15 @@ int record_z_unit(Cache& C, const Unit& U)
     return launch_row_sums(C.gpart[bk], nz * it.nslots, it.W, C.d_out + it.out_g);
 }
 
+int record_level(const Level& L)
+{
+    YAO_TRY(launch_many_resets(L.dtype, L.states, L.n, L.count));
+    for (const ManyStep& s : L.fwd) YAO_TRY(launch_many_passes(false, L.dtype, s));
+    for (int k = 0; k < 2; ++k) YAO_TRY(launch_many_obs(L.dtype, k + 1, L.obs[k]));
+    for (const ManyStep& s : L.bwd) YAO_TRY(launch_many_passes(true, L.dtype, s));
+    return launch_many_rows(L.rows);
+}
+
 int record_item(Cache& C, Item& it)
 {
     const int n = it.s->n, dt = it.s->dtype, bk = it.bank;
@@ -803,11 +1000,16 @@ int record(Cache& C)
         for (int b = 0; b < kBanks && !rc; ++b)
             if (hipStreamWaitEvent(g_bank[b], g_fork, 0) != hipSuccess) rc = set_error(YAO_EHIP, "fork wait");
         if (rc) break;
-        // The small circuits: one launch per qubit count.
-        for (const Cache::SmallLaunch& l : C.small_launches)
+        // The small circuits: one launch per qubit count, on the last streams of the first phase. A launch
+        // is one block a circuit for 400 to 600 us (up to 12 qubits, 16 layers), which leaves the chip
+        // to the others; one after the other and ahead of them they took 2.5 ms.
+        int last = kBanks;
+        for (const Cache::SmallLaunch& l : C.small_launches) {
+            set_stream(g_bank[--last]);
             if ((rc = launch_small_circuits(C.d_small + l.first, l.count, l.n))) break;
+        }
         if (rc) break;
-        int phase = -1;
+        int phase = C.units.empty() ? 0 : C.units.front().phase;
         for (const Unit& U : C.units) {
             if (U.phase != phase) {
                 // Every stream finishes the previous phase before any starts this one.
@@ -821,7 +1023,8 @@ int record(Cache& C)
                 if (rc) break;
             }
             set_stream(g_bank[U.bank]);
-            if (U.z) rc = record_z_unit(C, U);
+            if (U.level >= 0) rc = record_level(C.levels[U.level]);
+            else if (U.z) rc = record_z_unit(C, U);
             else rc = record_item(C, C.items[U.first]);
             if (rc) break;
         }

@@ -255,6 +255,38 @@ int launch_backward_passes(const Plan& P, const Program& prog, const DevProgram&
                            const double* params, double* psi, void* lam, int lam_dtype, int n, int B, double* gpartial,
                            int W, const BoundProgram* bp = nullptr);
 
+// Launches over several circuits of different structure at once, each block told its item and its place
+// in it by a table (single-slot states; all arrays in device memory).
+struct ManyStep {
+    const void* items = nullptr;
+    const uint2* blocks = nullptr;  // (item, tile or block of the item)
+    int nblocks = 0, threads = 0;
+    size_t lds = 0;
+};
+struct ManyObs {  // H psi: psi (and its FP64 copy), the output, partials and the observable's records
+    const void* psi;
+    void* lam;
+    double* psi64;
+    double* partial;
+    const void* recs;
+    int nrec, n;
+};
+struct ManyRows {  // rows sums of W entries each
+    const double* partial;
+    double* out;
+    int rows, W;
+};
+// The device form of pass p of a plan (many_pass_bytes() at dst), and its tiles, threads and LDS.
+size_t many_pass_bytes();
+int many_pass(void* dst, const Plan& P, const Program& prog, const DevProgram& d, int p, int dtype, void* psi, void* lam,
+              double* gpartial, int pstride, int* ntiles, int* threads, size_t* lds);
+int many_obs(ManyObs& o, int* reg_bits, int* blocks, const void* psi, void* lam, double* psi64, int dtype, int n,
+             const yao_pauli_sum* h, double* partial);
+int launch_many_passes(bool bwd, int dtype, const ManyStep& s);
+int launch_many_obs(int dtype, int reg_bits, const ManyStep& s);
+int launch_many_rows(const ManyStep& s);
+int launch_many_resets(int dtype, void* const* states, const int* n, int count);
+
 // Drivers.
 int forward_fused(void* data, int dtype, int n, int B, const yao_circuit* c, const double* params);
 // Forward sweep at fusion width `width` (0: none) over tiles of tq qubits (<= 0: default);

@@ -78,19 +78,19 @@ struct PassArgs {
 };
 
 // The per-circuit pointers of a launch (the circuit's own, or its z slot's).
-__device__ __forceinline__ void* z_psi(const PassArgs& a)
+template <typename A> __device__ __forceinline__ void* z_psi(const A& a)
 {
     return a.zs ? a.zs[blockIdx.z].psi : a.psi;
 }
-__device__ __forceinline__ void* z_lam(const PassArgs& a)
+template <typename A> __device__ __forceinline__ void* z_lam(const A& a)
 {
     return a.zs ? a.zs[blockIdx.z].lam : a.lam;
 }
-__device__ __forceinline__ const POp* z_ops(const PassArgs& a)
+template <typename A> __device__ __forceinline__ const POp* z_ops(const A& a)
 {
     return a.zs ? a.zs[blockIdx.z].ops + a.op_first : a.ops;
 }
-__device__ __forceinline__ double* z_partial(const PassArgs& a, double* p)
+template <typename A> __device__ __forceinline__ double* z_partial(const A& a, double* p)
 {
     return a.zs ? a.zs[blockIdx.z].partial : p;
 }
@@ -501,11 +501,11 @@ struct TileCtx {
 
 // Load/store mapping: element e = th + r * nthr; the low c bits of th are the batch slot, the
 // next t - RB - c bits of th and then the RB bits of r are the tile qubits in ascending order.
-template <int RB> __device__ __forceinline__ TileCtx tile_ctx(const PassArgs& a, int th)
+// tid: the tile (of a launch over one state: blockIdx.x).
+template <int RB, typename A> __device__ __forceinline__ TileCtx tile_ctx(const A& a, int th, uint64_t tid)
 {
     TileCtx tc;
     uint64_t base = 0;
-    const uint64_t tid = blockIdx.x;
 #pragma unroll
     for (int j = 0; j < 40; ++j)
         if (j < a.nnt) base |= ((tid >> j) & uint64_t(1)) << a.nontile_qubits[j];
@@ -526,7 +526,7 @@ template <int RB> __device__ __forceinline__ TileCtx tile_ctx(const PassArgs& a,
 }
 
 // LDS tile bits of the thread part (the low nb bits of th) of a stored element.
-__device__ __forceinline__ uint32_t store_thread_bits(const PassArgs& a, int th, int nb)
+template <typename A> __device__ __forceinline__ uint32_t store_thread_bits(const A& a, int th, int nb)
 {
     uint32_t v = 0;
 #pragma unroll
@@ -537,7 +537,7 @@ __device__ __forceinline__ uint32_t store_thread_bits(const PassArgs& a, int th,
 
 // The register bits of the load mapping are tile qubits whose offsets are the same for every
 // thread: the host passes them per register.
-template <int RB> __device__ __forceinline__ uint64_t tile_off(const PassArgs& a, const TileCtx& tc, int r)
+template <int RB, typename A> __device__ __forceinline__ uint64_t tile_off(const A& a, const TileCtx& tc, int r)
 {
     return tc.toff + a.rofs[r];
 }
@@ -575,14 +575,14 @@ static_assert(sizeof(POp) % 16 == 0 && sizeof(PGroupDesc) % 16 == 0, "16-byte re
 constexpr int kDmRegs = 4;
 // With no dense matrices the words are read from the first op record (every forward pass has
 // one) and dropped, so the registers are always defined.
-__device__ __forceinline__ void dm_load(const PassArgs& a, int th, int nthr, uint4 (&w)[kDmRegs])
+template <typename A> __device__ __forceinline__ void dm_load(const A& a, int th, int nthr, uint4 (&w)[kDmRegs])
 {
     const uint4* src = a.ndm > 0 ? a.dmats : (const uint4*)a.ops;
     const int last = a.ndm > 0 ? a.ndm - 1 : 0;
 #pragma unroll
     for (int k = 0; k < kDmRegs; ++k) w[k] = src[min(th + k * nthr, last)];
 }
-__device__ __forceinline__ void dm_store(const PassArgs& a, uint4* ldm, int th, int nthr, const uint4 (&w)[kDmRegs])
+template <typename A> __device__ __forceinline__ void dm_store(const A& a, uint4* ldm, int th, int nthr, const uint4 (&w)[kDmRegs])
 {
     // Unconditional: a clamped index writes the word it loaded, so duplicates are identical.
 #pragma unroll
@@ -873,21 +873,21 @@ __device__ __forceinline__ void dense16_mfma(float2* lp, const float2* M, const 
 }
 
 // ------------------------------------------------------------------------------ forward kernel
-template <typename RP>
-__global__ __launch_bounds__(512, sizeof(RP) == 4 ? 3 : 1) void k_pass_fwd(PassArgs a)
+template <typename RP, typename Args>
+__device__ __forceinline__ void pass_fwd(const Args& a, uint64_t tile, unsigned char* smem)
 {
     constexpr int RB = kRegBitsFwd, N = 1 << RB;
     using VP = vec2_t<RP>;
-    extern __shared__ __align__(16) unsigned char smem[];
     const int t = a.t;
     const int nthr = 1 << (t - RB);
     const int th = threadIdx.x;
+    if (th >= nthr) return;  // a launch over tiles of several sizes
     // LDS: tile | dense block matrices (2 * 256 RP each), sized for this pass.
     VP* lp = (VP*)smem;
     uint4* ldm = (uint4*)(smem + (sizeof(VP) << t));
     const YAO_CONST POp* gops = cptr(z_ops(a));
     const YAO_CONST PGroupDesc* ggrp = cptr(a.groups);
-    const TileCtx tc = tile_ctx<RB>(a, th);
+    const TileCtx tc = tile_ctx<RB>(a, th, tile);
     VP* gp = (VP*)z_psi(a);
     // Every load is in bounds (slots past B read the last slot and are never stored), so all
     // of them are issued before the first wait.
@@ -998,6 +998,22 @@ __global__ __launch_bounds__(512, sizeof(RP) == 4 ? 3 : 1) void k_pass_fwd(PassA
 #pragma unroll
         for (int r = 0; r < N; ++r) gp[tile_off<RB>(a, tc, r)] = lp[swz(sth | a.sreg[r])];
     }
+}
+
+template <typename RP>
+__global__ __launch_bounds__(512, sizeof(RP) == 4 ? 3 : 1) void k_pass_fwd(PassArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    pass_fwd<RP>(a, blockIdx.x, smem);
+}
+
+// One pass of each of several circuits at once: block b works on tile blocks[b].y of items[blocks[b].x].
+template <typename RP>
+__global__ __launch_bounds__(512, sizeof(RP) == 4 ? 3 : 1) void k_pass_fwd_many(const PassArgs* items, const uint2* blocks)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint2 b = {(uint32_t)sc((int)blocks[blockIdx.x].x), (uint32_t)sc((int)blocks[blockIdx.x].y)};
+    pass_fwd<RP>(cptr(items)[b.x], b.y, smem);
 }
 
 // ------------------------------------------------------------------------------ backward kernel
@@ -1143,21 +1159,21 @@ __device__ __forceinline__ double2 reverse_groups(double2* lp, vec2_t<RL>* ll, d
 
 // C0: tiles of one batch slot (c = 0), where every row-sum step applies. At most 168 VGPRs, so
 // that three 256-thread tiles of 2^11 elements (48 KiB of LDS each) fit on one CU.
-template <typename RL, bool C0>
-__global__ __launch_bounds__(512, 3) void k_pass_bwd(PassArgs a)
+template <typename RL, bool C0, typename Args>
+__device__ __forceinline__ void pass_bwd(const Args& a, uint64_t tile, unsigned char* smem)
 {
     constexpr int RB = kRegBitsBwd, N = 1 << RB;
     using VL = vec2_t<RL>;
-    extern __shared__ __align__(16) unsigned char smem[];
     const int t = a.t;
     const int nthr = 1 << (t - RB);
     const int th = threadIdx.x;
+    if (th >= nthr) return;  // a launch over tiles of several sizes
     const int c = C0 ? 0 : a.c;
     // LDS: psi | lambda | gradient partials.
     double2* lp = (double2*)smem;
     VL* ll = (VL*)(smem + ((size_t)16 << t));
     double* red0 = (double*)(smem + ((size_t)(16 + sizeof(VL)) << t));
-    const TileCtx tc = tile_ctx<RB>(a, th);
+    const TileCtx tc = tile_ctx<RB>(a, th, tile);
     double2* gp = (double2*)z_psi(a);
     VL* gl = (VL*)z_lam(a);
     // Straight from global memory to LDS: a staging array here stayed in scratch memory
@@ -1171,7 +1187,7 @@ __global__ __launch_bounds__(512, 3) void k_pass_bwd(PassArgs a)
     }
     __syncthreads();
 
-    const GradOut go{z_partial(a, a.gpartial), a.B, a.pstride, (int)blockIdx.x, (int)blockIdx.y << c};
+    const GradOut go{z_partial(a, a.gpartial), a.B, a.pstride, (int)tile, (int)blockIdx.y << c};
     const double2 ph = reverse_groups<RL, C0>(lp, ll, red0, cptr(z_ops(a)), cptr(a.groups), a.groups, a.ngroups,
                                               a.mats, tc.base, t, c, nthr, th, a.mslots, go);
 
@@ -1188,6 +1204,22 @@ __global__ __launch_bounds__(512, 3) void k_pass_bwd(PassArgs a)
             gl[off] = mkv<VL, RL>((RL)(ph.x * wx - ph.y * wy), (RL)(ph.x * wy + ph.y * wx));
         }
     }
+}
+
+template <typename RL, bool C0>
+__global__ __launch_bounds__(512, 3) void k_pass_bwd(PassArgs a)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    pass_bwd<RL, C0>(a, blockIdx.x, smem);
+}
+
+// As k_pass_fwd_many, for reverse passes of single-slot states.
+template <typename RL>
+__global__ __launch_bounds__(512, 3) void k_pass_bwd_many(const PassArgs* items, const uint2* blocks)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const uint2 b = {(uint32_t)sc((int)blocks[blockIdx.x].x), (uint32_t)sc((int)blocks[blockIdx.x].y)};
+    pass_bwd<RL, true>(cptr(items)[b.x], b.y, smem);
 }
 
 // ------------------------------------------------------------------------------ small circuits
@@ -1449,7 +1481,7 @@ __global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsRec* __re
     const int th = threadIdx.x;
     VP* lp = (VP*)smem;
     double* red = (double*)(smem + (sizeof(VP) << t));
-    const TileCtx tc = tile_ctx<RB>(a, th);
+    const TileCtx tc = tile_ctx<RB>(a, th, blockIdx.x);
     const VP* gp = (const VP*)z_psi(a);
     // Straight from global memory to LDS (a staging array stayed in scratch memory).
 #pragma unroll
@@ -1511,20 +1543,16 @@ __global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsRec* __re
 // is bound by the latency of a handful of dependent steps.
 constexpr int kObsGatherThreads = 256;
 template <typename RP, typename RO, bool OUT, int RB>
-__global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather(PassArgs a, const ObsRec* __restrict__ recs, int nrec,
-                                                                  double* __restrict__ partial,
-                                                                  double2* __restrict__ psi64)
+__device__ __forceinline__ void obs_gather(const vec2_t<RP>* __restrict__ gp, vec2_t<RO>* __restrict__ go, int n,
+                                           uint32_t block, const ObsRec* recs, int nrec, double* __restrict__ partial,
+                                           double2* __restrict__ psi64, double* red)
 {
     constexpr int N = 1 << RB;
     using VP = vec2_t<RP>;
     using VO = vec2_t<RO>;
-    __shared__ double red[kObsGatherThreads];
     const int th = threadIdx.x;
-    const uint32_t gid = blockIdx.x * blockDim.x + (uint32_t)th;
-    const int top = a.n - RB;
-    const VP* gp = (const VP*)z_psi(a);
-    VO* go = (VO*)z_lam(a);
-    partial = z_partial(a, partial);
+    const uint32_t gid = block * blockDim.x + (uint32_t)th;
+    const int top = n - RB;
     VP own[N];
 #pragma unroll
     for (int r = 0; r < N; ++r) own[r] = gp[gid | ((uint32_t)r << top)];
@@ -1552,8 +1580,50 @@ __global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather(PassArgs a, co
         double v = 0;
         for (int i = th; i < (int)blockDim.x; i += 64) v += red[i];
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (th == 0) partial[blockIdx.x] = v;
+        if (th == 0) partial[block] = v;
     }
+}
+
+template <typename RP, typename RO, bool OUT, int RB>
+__global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather(PassArgs a, const ObsRec* __restrict__ recs, int nrec,
+                                                                  double* __restrict__ partial,
+                                                                  double2* __restrict__ psi64)
+{
+    __shared__ double red[kObsGatherThreads];
+    obs_gather<RP, RO, OUT, RB>((const vec2_t<RP>*)z_psi(a), (vec2_t<RO>*)z_lam(a), a.n, blockIdx.x, recs, nrec,
+                                z_partial(a, partial), psi64, red);
+}
+
+// H psi of several states at once: block b is block blocks[b].y of items[blocks[b].x].
+template <typename R, int RB>
+__global__ __launch_bounds__(kObsGatherThreads) void k_obs_gather_many(const ManyObs* items, const uint2* blocks)
+{
+    __shared__ double red[kObsGatherThreads];
+    const uint32_t x = (uint32_t)sc((int)blocks[blockIdx.x].x), y = (uint32_t)sc((int)blocks[blockIdx.x].y);
+    const YAO_CONST ManyObs* it = cptr(items) + x;
+    obs_gather<R, R, true, RB>((const vec2_t<R>*)it->psi, (vec2_t<R>*)it->lam, it->n, y, (const ObsRec*)it->recs, it->nrec,
+                               it->partial, (double2*)it->psi64, red);
+}
+
+// Row sums of several blocks of partials at once (a wave a row), and |0...0> into several states.
+__global__ __launch_bounds__(256) void k_rows_many(const ManyRows* items, const uint2* blocks)
+{
+    const uint32_t x = (uint32_t)sc((int)blocks[blockIdx.x].x), y = (uint32_t)sc((int)blocks[blockIdx.x].y);
+    const YAO_CONST ManyRows* it = cptr(items) + x;
+    const int lane = threadIdx.x & 63, r = (int)y * 4 + (int)(threadIdx.x >> 6);
+    if (r >= it->rows) return;
+    const double* row = it->partial + (uint64_t)r * it->W;
+    double v = 0;
+    for (int j = lane; j < it->W; j += 64) v += row[j];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) it->out[r] = v;
+}
+template <typename R> __global__ __launch_bounds__(256) void k_reset_many(void* const* states, const int* n)
+{
+    vec2_t<R>* s = (vec2_t<R>*)states[blockIdx.y];
+    const uint64_t elems = uint64_t(1) << n[blockIdx.y];
+    for (uint64_t e = (uint64_t)blockIdx.x * 256 + threadIdx.x; e < elems; e += (uint64_t)gridDim.x * 256)
+        s[e] = mkv<vec2_t<R>, R>(e == 0 ? R(1) : R(0), R(0));
 }
 
 // A step of the Lanczos recurrence as one launch: v = src / |src|, out = H v and the partials of
@@ -1786,6 +1856,10 @@ int prepare_pass_kernels()
     YAO_TRY(set_lds_limit(k_pass_bwd<double, true>));
     YAO_TRY(set_lds_limit(k_pass_bwd<double, false>));
     YAO_TRY(set_lds_limit(k_small_circuit));
+    YAO_TRY(set_lds_limit(k_pass_fwd_many<float>));
+    YAO_TRY(set_lds_limit(k_pass_fwd_many<double>));
+    YAO_TRY(set_lds_limit(k_pass_bwd_many<float>));
+    YAO_TRY(set_lds_limit(k_pass_bwd_many<double>));
     return 0;
 }
 
@@ -1835,10 +1909,12 @@ static void tile_args(PassArgs& a, int n, int B, int c, int t, const std::vector
     a.ntiles = 1 << a.nnt;
 }
 
-int launch_pass(bool bwd, int psi_dtype, int lam_dtype, void* psi, void* lam, const POp* ops, const PGroupDesc* groups,
-                const double* mats, double* gpartial, int pstride, int mslots, int n, int B, int c, int t, int group0,
-                int ngroups, const std::vector<int>& tile_qubits, const std::vector<int>& store_src, double flops,
-                int op_first, int nops, const double* dmats, int dm_words)
+// The arguments of one pass and the threads and LDS its tiles take.
+static int pass_setup(PassArgs& a, bool bwd, int psi_dtype, int lam_dtype, void* psi, void* lam, const POp* ops,
+                      const PGroupDesc* groups, const double* mats, double* gpartial, int pstride, int mslots, int n, int B,
+                      int c, int t, int group0, int ngroups, const std::vector<int>& tile_qubits,
+                      const std::vector<int>& store_src, int op_first, int nops, const double* dmats, int dm_words,
+                      int* threads, size_t* lds_bytes)
 {
     if (bwd && (mslots < 1 || mslots > kMaxGroupSlots))
         return set_error(YAO_EINVAL, "%d gradient slots per register group (1 .. %d)", mslots, kMaxGroupSlots);
@@ -1858,7 +1934,6 @@ int launch_pass(bool bwd, int psi_dtype, int lam_dtype, void* psi, void* lam, co
     const int dm_max = bwd ? 0 : kMaxPassDense * 256;  // 4 KiB per block in every layout
     if (dm_words < 0 || dm_words > dm_max)
         return set_error(YAO_EINVAL, "pass carries %d words of dense matrices (at most %d)", dm_words, dm_max);
-    PassArgs a;
     memset(&a, 0, sizeof(a));
     a.psi = psi;
     a.lam = lam;
@@ -1875,17 +1950,32 @@ int launch_pass(bool bwd, int psi_dtype, int lam_dtype, void* psi, void* lam, co
     a.op_first = op_first;
     tile_args(a, n, B, c, t, tile_qubits, bwd ? kRegBitsBwd : kRegBitsFwd, store_src);
     a.pstride = pstride > a.ntiles ? pstride : a.ntiles;
-    const int Bc = 1 << c;
     const int RBk = bwd ? kRegBitsBwd : kRegBitsFwd;
     // The kernels are compiled for at most 512 threads per block (one tile, 2^(t - RB) threads).
     if (t - RBk < 0 || t - RBk > 9) return set_error(YAO_EINVAL, "tile of 2^%d does not fit 1 .. 512 threads", t);
-    const int nz = g_zbatch.zs ? g_zbatch.nz : 1;
-    dim3 grid(a.ntiles, (B + Bc - 1) / Bc, nz);
-    dim3 block(1 << (t - RBk));
+    *threads = 1 << (t - RBk);
     const int pb = bwd ? 16 : (psi_dtype == YAO_C64 ? 8 : 16);
     const int lb = bwd ? (lam_dtype == YAO_C64 ? 8 : 16) : 0;
-    const size_t lds = pass_lds_bytes(bwd, t, c, pb, lb, bwd ? 0 : dm_words, mslots);
-    if (lds > 160 * 1024) return set_error(YAO_EINVAL, "tile of 2^%d needs %zu bytes of LDS", t, lds);
+    *lds_bytes = pass_lds_bytes(bwd, t, c, pb, lb, bwd ? 0 : dm_words, mslots);
+    if (*lds_bytes > 160 * 1024) return set_error(YAO_EINVAL, "tile of 2^%d needs %zu bytes of LDS", t, *lds_bytes);
+    return 0;
+}
+
+int launch_pass(bool bwd, int psi_dtype, int lam_dtype, void* psi, void* lam, const POp* ops, const PGroupDesc* groups,
+                const double* mats, double* gpartial, int pstride, int mslots, int n, int B, int c, int t, int group0,
+                int ngroups, const std::vector<int>& tile_qubits, const std::vector<int>& store_src, double flops,
+                int op_first, int nops, const double* dmats, int dm_words)
+{
+    PassArgs a;
+    int threads = 0;
+    size_t lds = 0;
+    YAO_TRY(pass_setup(a, bwd, psi_dtype, lam_dtype, psi, lam, ops, groups, mats, gpartial, pstride, mslots, n, B, c, t,
+                       group0, ngroups, tile_qubits, store_src, op_first, nops, dmats, dm_words, &threads, &lds));
+    const int Bc = 1 << c, nz = g_zbatch.zs ? g_zbatch.nz : 1;
+    const int pb = bwd ? 16 : (psi_dtype == YAO_C64 ? 8 : 16);
+    const int lb = bwd ? (lam_dtype == YAO_C64 ? 8 : 16) : 0;
+    dim3 grid(a.ntiles, (B + Bc - 1) / Bc, nz);
+    dim3 block(threads);
     hipStream_t st = stream();
     const int pi = prof_begin(bwd ? YAO_KF_PASS_BWD : YAO_KF_PASS_FWD);
     if (!bwd) {
@@ -1916,6 +2006,77 @@ int launch_pass(bool bwd, int psi_dtype, int lam_dtype, void* psi, void* lam, co
         }
     }
     prof_end(pi, 2.0 * (double)(uint64_t(1) << n) * B * (pb + lb) * nz, flops * nz);
+    YAO_HIP(hipGetLastError());
+    return 0;
+}
+
+// ---------------------------------------------------------------------- several circuits at once
+size_t many_pass_bytes()
+{
+    return sizeof(PassArgs);
+}
+
+int many_pass(void* dst, const Plan& P, const Program& prog, const DevProgram& d, int p, int dtype, void* psi, void* lam,
+              double* gpartial, int pstride, int* ntiles, int* threads, size_t* lds)
+{
+    const HostPass& pass = P.passes[p];
+    const bool bwd = P.reverse;
+    PassArgs a;
+    YAO_TRY(pass_setup(a, bwd, bwd ? YAO_C128 : dtype, dtype, psi, lam, d.ops, d.groups, d.mats, gpartial, pstride,
+                       bwd ? P.max_slots : 0, P.n, 1, P.c, P.t, prog.pass_group0[p], (int)pass.groups.size(),
+                       pass.tile_qubits, pass.store_src, prog.pass_op0[p], prog.pass_nops[p],
+                       bwd ? nullptr : d.mats + prog.pass_dmat0[p], bwd ? 0 : prog.pass_dmat_words[p], threads, lds));
+    a.zs = nullptr;
+    *ntiles = a.ntiles;
+    memcpy(dst, &a, sizeof(a));
+    return 0;
+}
+
+int launch_many_passes(bool bwd, int dtype, const ManyStep& s)
+{
+    if (s.nblocks <= 0) return 0;
+    const PassArgs* items = (const PassArgs*)s.items;
+    hipStream_t st = stream();
+    if (!bwd) {
+        if (dtype == YAO_C64) k_pass_fwd_many<float><<<s.nblocks, s.threads, s.lds, st>>>(items, s.blocks);
+        else k_pass_fwd_many<double><<<s.nblocks, s.threads, s.lds, st>>>(items, s.blocks);
+    } else {
+        if (dtype == YAO_C64) k_pass_bwd_many<float><<<s.nblocks, s.threads, s.lds, st>>>(items, s.blocks);
+        else k_pass_bwd_many<double><<<s.nblocks, s.threads, s.lds, st>>>(items, s.blocks);
+    }
+    YAO_HIP(hipGetLastError());
+    return 0;
+}
+
+int launch_many_obs(int dtype, int reg_bits, const ManyStep& s)
+{
+    if (s.nblocks <= 0) return 0;
+    const ManyObs* items = (const ManyObs*)s.items;
+    hipStream_t st = stream();
+    if (dtype == YAO_C64) {
+        if (reg_bits == 1) k_obs_gather_many<float, 1><<<s.nblocks, kObsGatherThreads, 0, st>>>(items, s.blocks);
+        else k_obs_gather_many<float, 2><<<s.nblocks, kObsGatherThreads, 0, st>>>(items, s.blocks);
+    } else {
+        if (reg_bits == 1) k_obs_gather_many<double, 1><<<s.nblocks, kObsGatherThreads, 0, st>>>(items, s.blocks);
+        else k_obs_gather_many<double, 2><<<s.nblocks, kObsGatherThreads, 0, st>>>(items, s.blocks);
+    }
+    YAO_HIP(hipGetLastError());
+    return 0;
+}
+
+int launch_many_rows(const ManyStep& s)
+{
+    if (s.nblocks <= 0) return 0;
+    k_rows_many<<<s.nblocks, 256, 0, stream()>>>((const ManyRows*)s.items, s.blocks);
+    YAO_HIP(hipGetLastError());
+    return 0;
+}
+
+int launch_many_resets(int dtype, void* const* states, const int* n, int count)
+{
+    if (count <= 0) return 0;
+    if (dtype == YAO_C64) k_reset_many<float><<<dim3(32, count), 256, 0, stream()>>>(states, n);
+    else k_reset_many<double><<<dim3(32, count), 256, 0, stream()>>>(states, n);
     YAO_HIP(hipGetLastError());
     return 0;
 }
@@ -2127,6 +2288,20 @@ bool obs_one_launch(const yao_pauli_sum* h, int n, int B, int dtype)
     if (n < kObsRegBits + 1) return false;
     const ObsPlan* P = obs_plan(h, n, B, dtype, OBS_VECTOR);
     return P && P->ok && P->gather;
+}
+
+// One item of launch_many_obs: its columns are obs_partial_doubles, its blocks *blocks of 256 threads.
+int many_obs(ManyObs& o, int* reg_bits, int* blocks, const void* psi, void* lam, double* psi64, int dtype, int n,
+             const yao_pauli_sum* h, double* partial)
+{
+    const ObsPlan* P = obs_plan(h, n, 1, dtype, OBS_VECTOR);
+    if (!P) return YAO_ENOMEM;
+    if (!P->ok || !P->gather || obs_gather_threads(n) != kObsGatherThreads)
+        return set_error(YAO_EINVAL, "observable takes more than one launch");
+    o = ManyObs{psi, lam, psi64, partial, P->drecs, P->passes[0].r1, n};
+    *reg_bits = obs_gather_reg_bits(n);
+    *blocks = obs_columns(P, n);
+    return 0;
 }
 
 int launch_lanczos_hv(const void* src, void* v, void* out, int dtype, int n, const yao_pauli_sum* h, const double* npart,

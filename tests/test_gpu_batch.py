@@ -231,6 +231,37 @@ def test_same_structure_circuits_share_launches(dtype):
             assert np.abs(states[i].download() - ref).max() <= (1e-5 if dtype == 0 else 1e-11), i
 
 
+@pytest.mark.parametrize("dtype,large", [(0, True), (1, True), (0, False), (1, False)])
+def test_unlike_circuits_share_launches(dtype, large):
+    """Passes of unlike circuits of 9 to 20 qubits in one launch: one tile and less than one, sizes on both
+    sides of the H psi split (17 and 18 qubits), enough tiles in all for the smaller reverse tile and
+    (without the 18 qubits) too few, circuits of unlike depth that leave after different passes,
+    a circuit listed three times (its later programs are built on the host), a wide random observable,
+    and a circuit of 8 qubits outside."""
+    sizes = [(9, 3), (10, 2), (11, 1), (12, 1), (13, 6), (13, 6), (13, 6), (14, 2), (17, 1), (8, 2)]
+    if large:
+        sizes += [(18, 1), (18, 1)]
+    states, circs, hams, params, refs, made = [], [], [], [], [], {}
+    for i, (n, d) in enumerate(sizes):
+        c = w.hea_circuit(n, d)
+        H = random_pauli_sum(n, 9, 8100 + n) if i % 3 == 1 else w.heisenberg(n)
+        if (n, d) not in made:
+            made[(n, d)] = yb.Circuit.from_workload(c)
+        states.append(yb.State(n, 1, dtype))
+        circs.append(made[(n, d)])
+        hams.append(yb.PauliSum.from_workload(H))
+        params.append(w.angles(8200 + i, c.nparams))
+        refs.append((c, H))
+    for rep in range(2):
+        if rep:
+            params = [w.angles(8300 + i, len(p)) for i, p in enumerate(params)]
+        e, g = yb.batch_run(states, circs, params, hams)
+        check(e, g, params, refs, dtype)
+        for i, (c, _) in enumerate(refs):
+            ref = oracle.forward(c, params[i], w.zero_state(c.n))
+            assert np.abs(states[i].download() - ref).max() <= (1e-5 if dtype == 0 else 1e-11), i
+
+
 def test_circuit_without_parameters_and_observable_only():
     c = w.ghz_circuit(7)
     H = w.heisenberg(7)
