@@ -64,6 +64,7 @@ struct Item {
     int bank = 0;
     int phase = 0;  // recording phase by state size (see record)
     bool small = false;  // run start to end by one workgroup (k_small_circuit)
+    bool lone = false;   // kept out of level units
     int nslots = 0;
     int W = 0;                    // partial-sum row stride of the reverse passes
     size_t out_e = 0, out_g = 0;  // positions in the output block
@@ -105,6 +106,7 @@ using Key = std::vector<std::tuple<const yao_circuit*, uint64_t, const yao_state
 struct Cache {
     Key key;
     yao_options opt{};
+    bool share = true;  // use level units
     std::vector<Item> items;  // recording order
     char* d_prog = nullptr;
     char* h_prog = nullptr;
@@ -431,7 +433,7 @@ bool z_capable(const Item& it)
 bool level_candidate(const Item& it)
 {
     const int n = it.s->n;
-    if (it.small || n < 9 || n > 20 || it.nslots == 0) return false;
+    if (it.small || it.lone || n < 9 || n > 20 || it.nslots == 0) return false;
     for (const GateRec& g : it.c->gates)
         if (g.k > kMaxFusedK) return false;
     return obs_one_launch(it.h, n, 1, it.s->dtype);
@@ -454,6 +456,7 @@ bool level_capable(const Item& it)
 // 16.1; 40 of 9 to 18, complex128: 2.28 against 1.95; 10 qubits 16.1 and 2.05).
 constexpr int kLevelTile = 11;
 constexpr uint64_t kLevelTiles = 256;
+constexpr size_t kLevelMax = 16384;  // circuits of one level unit at most (a grid dimension of its resets)
 
 // Scratch of one circuit of a z unit: psi in FP64, lambda, reverse and H psi partial sums.
 size_t z_item_bytes(const Item& it)
@@ -578,6 +581,7 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         it.nslots = count_param_slots(it.c);
         it.cost = (double)(it.c->gates.size() + 1) * (double)(uint64_t(1) << n);
         it.phase = batch_phase(n);
+        it.lone = !C.share;
     }
     // Circuits whose whole state fits one tile run start to end in one workgroup, from
     // programs of one pass each (3 register bits, FP64 matrices) bound on the device; a
@@ -661,7 +665,7 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
             if (level_capable(it)) {
                 const size_t bytes = z_item_bytes(it);
                 auto& u = levels[std::make_tuple(it.s->dtype, it.fwd->t, it.bwd->t)];
-                if (u.second == 0 || u.second + bytes > kZUnitBytes) {
+                if (u.second == 0 || u.second + bytes > kZUnitBytes || members[u.first].size() >= kLevelMax) {
                     u = {(int)members.size(), 0};
                     members.emplace_back();
                     zunit.push_back(false);
@@ -1110,6 +1114,16 @@ int batch_run(int ncirc, yao_state* const* states, const yao_circuit* const* cir
         Cache* c = new Cache;
         c->key = key;
         int rc = build_cache(*c, ncirc, states, circs, params, h);
+        if (rc == YAO_ENOMEM) {
+            // Level units hold the scratch of all their circuits at once; without them a stream's circuits
+            // take turns.
+            (void)hipGetLastError();
+            free_cache(c);
+            c = new Cache;
+            c->key = key;
+            c->share = false;
+            rc = build_cache(*c, ncirc, states, circs, params, h);
+        }
         if (!rc) rc = record(*c);
         set_stream(origin);
         if (rc) {

@@ -11,8 +11,8 @@
 // then applies U^dagger to both (eq. apply-back). Per-thread gradient partials go to LDS and
 // are reduced once per register group, in a fixed order.
 //
-// The pass's op records are copied to LDS together with the tile; LDS reads complete in
-// order, so the record of the next op is fetched while the current op computes.
+// The op records are read where they lie, through the scalar cache; the record of the next op is
+// fetched while the current op computes.
 #include <algorithm>
 #include <map>
 #include <tuple>
@@ -1812,9 +1812,10 @@ __global__ void k_bind_jobs(const BindJob* __restrict__ jobs)
 int launch_bind_jobs(const BindJob* jobs, int njobs, int max_nb)
 {
     if (njobs <= 0 || max_nb <= 0) return 0;
-    if (njobs > 65535) return set_error(YAO_EINVAL, "%d bind jobs in one launch", njobs);
-    k_bind_jobs<<<dim3((max_nb + 255) / 256, njobs), 256, 0, stream()>>>(jobs);
-    YAO_HIP(hipGetLastError());
+    for (int j = 0; j < njobs; j += 65535) {
+        k_bind_jobs<<<dim3((max_nb + 255) / 256, std::min(njobs - j, 65535)), 256, 0, stream()>>>(jobs + j);
+        YAO_HIP(hipGetLastError());
+    }
     return 0;
 }
 
