@@ -580,27 +580,38 @@ const BoundProgram* bound_program(const Plan& P, const yao_circuit* c, bool bwd,
     return b;
 }
 
-// Copy the parameters to the device (queued; the pinned buffer is reused only after the copy
-// is done). Returns the device array, or nullptr on failure.
-const double* upload_params(const double* params, int nparams)
+// The pinned parameter buffer is reused only after this event: the last copy from it, or the last launch
+// that reads it, is done.
+static hipEvent_t g_params_done = nullptr;
+
+const double* pinned_params(const double* params, int nparams)
 {
-    static hipEvent_t done = nullptr;
-    if (!done) {
-        if (hipEventCreateWithFlags(&done, hipEventDisableTiming) != hipSuccess) return nullptr;
-    } else if (hipEventSynchronize(done) != hipSuccess) {
+    if (!g_params_done) {
+        if (hipEventCreateWithFlags(&g_params_done, hipEventDisableTiming) != hipSuccess) return nullptr;
+    } else if (hipEventSynchronize(g_params_done) != hipSuccess) {
         return nullptr;
     }
-    const size_t bytes = sizeof(double) * (size_t)std::max(1, nparams);
-    double* dev = (double*)workspace(WS_PARAMS, bytes);
-    double* host = (double*)pinned(WS_PARAMS, bytes);
+    double* host = (double*)pinned(WS_PARAMS, sizeof(double) * (size_t)std::max(1, nparams));
+    if (host && nparams > 0) memcpy(host, params, sizeof(double) * (size_t)nparams);
+    return host;
+}
+
+int params_queued()
+{
+    YAO_HIP(hipEventRecord(g_params_done, stream()));
+    return 0;
+}
+
+// Copy the parameters to the device (queued). Returns the device array, or nullptr on failure.
+const double* upload_params(const double* params, int nparams)
+{
+    const double* host = pinned_params(params, nparams);
+    double* dev = (double*)workspace(WS_PARAMS, sizeof(double) * (size_t)std::max(1, nparams));
     if (!dev || !host) return nullptr;
-    if (nparams > 0) {
-        memcpy(host, params, sizeof(double) * (size_t)nparams);
-        if (hipMemcpyAsync(dev, host, sizeof(double) * (size_t)nparams, hipMemcpyHostToDevice, stream()) != hipSuccess)
-            return nullptr;
-    }
-    if (hipEventRecord(done, stream()) != hipSuccess) return nullptr;
-    return dev;
+    if (nparams > 0 &&
+        hipMemcpyAsync(dev, host, sizeof(double) * (size_t)nparams, hipMemcpyHostToDevice, stream()) != hipSuccess)
+        return nullptr;
+    return params_queued() == 0 ? dev : nullptr;
 }
 
 int bind_program(const BoundProgram* b, const double* dparams)
@@ -683,10 +694,25 @@ int forward_fused(void* data, int dtype, int n, int B, const yao_circuit* c, con
     return forward_sweep(data, dtype, n, B, c, params, 0, options().tile_qubits, nullptr);
 }
 
+// States that a step's binding launch copies along, in doubles (8 MB), and the parameters that it reads
+// from pinned memory. A 10-qubit step is a chain of launches of 2 to 30 us; the copies of its input and of
+// its angles took 2 us each and 10 us with the gaps around them (10 qubits, depth 5, complex128: 105 ->
+// 89 us; 15 qubits 221 -> 214). At the limits it makes no difference (20 qubits of complex64, 8 MB and 1200
+// angles: 858 and 857 us); beyond them the copy engines' rate counts.
+constexpr uint64_t kBindCopyMax = uint64_t(1) << 20;
+constexpr int kPinnedParams = 4096;
+
 int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, const double* params, int width, int tq,
-                  const double* dparams, const BoundProgram* also, bool* also_bound)
+                  const double* dparams, const BoundProgram* also, bool* also_bound, const CopyJob* copy)
 {
     if (also_bound) *also_bound = false;
+    auto copy_now = [&]() -> int {
+        if (copy) YAO_HIP(hipMemcpyAsync(copy->dst, copy->src, sizeof(double) * copy->count, hipMemcpyDeviceToDevice, stream()));
+        copy = nullptr;
+        return 0;
+    };
+    // A few MB go with the binding launch; beyond that the copy engine's full width counts.
+    if (c->gates.empty() || !also || (copy && copy->count > kBindCopyMax)) YAO_TRY(copy_now());
     if (c->gates.empty()) return 0;
     int t, cb, L;
     tile_geometry_tq(n, B, dtype, false, tq, &t, &cb, &L);
@@ -706,7 +732,8 @@ int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, con
                 auto job = [&](const BoundProgram* b) {
                     return BindJob{b->d.ops, b->dbinds, b->dfacs, dparams, (int)b->prog.binds.size(), 0};
                 };
-                YAO_TRY(launch_bind_pair(job(bp), job(also)));
+                YAO_TRY(launch_bind_pair(job(bp), job(also), copy ? *copy : CopyJob()));
+                copy = nullptr;
                 *also_bound = true;
             } else {
                 YAO_TRY(bind_program(bp, dparams));
@@ -714,6 +741,7 @@ int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, con
             return launch_forward_passes(*P, bp->prog, bp->d, data, dtype, n, B, sc, nullptr, bp);
         }
     }
+    YAO_TRY(copy_now());
     // Host-built program for these parameters (dense fused blocks, or gates the device cannot bind).
     const yao_circuit* hc = width > 0 && !c->transient ? fused_circuit(c, params, width) : c;
     const double* hp = hc == c ? params : nullptr;
@@ -744,7 +772,7 @@ static void gather_gradients(const yao_circuit* c, const std::vector<int>& slot_
 // it may fold gates into dense blocks; the reverse program is built on the host while the
 // device runs the forward sweep, and nothing waits for the device until the results are read.
 static int backward_reversible(yao_state* s, const yao_circuit* c, const double* params, yao_pauli_sum* h,
-                               bool reduce_batch, double* energy, double* grad, double* drift, const void* psi0,
+                               bool reduce_batch, double* energy, double* grad, double* drift, void* psi0,
                                bool check_drift)
 {
     const int n = s->n, B = s->batch;
@@ -772,12 +800,15 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     int width = 0;
     YAO_TRY(pick_forward_width(c, params, s->data, s->dtype, n, B, &width));
     const double* dp = nullptr;
+    const bool direct = bp && c->nparams <= kPinnedParams;
     if (c->nparams > 0) {
-        dp = upload_params(params, c->nparams);
+        dp = direct ? pinned_params(params, c->nparams) : upload_params(params, c->nparams);
         if (!dp) return YAO_ENOMEM;
     }
     bool bound = false;
-    YAO_TRY(forward_sweep(s->data, s->dtype, n, B, c, params, width, options().tile_qubits, dp, bp, &bound));
+    const CopyJob input{(double*)psi0, (const double*)s->data, s->bytes() / sizeof(double)};
+    YAO_TRY(forward_sweep(s->data, s->dtype, n, B, c, params, width, options().tile_qubits, dp, bp, &bound,
+                          &input));
 
     Program hprog;
     if (!bp) YAO_TRY(build_program(*P, c, params, true, s->dtype, hprog));
@@ -787,6 +818,7 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     DevProgram hd;
     if (!bp) YAO_TRY(upload_program(hprog, hd, WS_MAT2));
     else if (!bound) YAO_TRY(bind_program(bp, dp));
+    if (direct && dp) YAO_TRY(params_queued());
     const Program& prog = bp ? bp->prog : hprog;
     YAO_TRY(launch_backward_passes(*P, prog, bp ? bp->d : hd, c, params, psi, lam, s->dtype, n, B, gpartial, W, bp));
     const double *eh = nullptr, *sums = nullptr;
@@ -819,7 +851,6 @@ int backward_fused(yao_state* s, const yao_circuit* c, const double* params, yao
 
     void* psi0 = workspace(WS_PSI0, s->bytes());
     if (!psi0) return YAO_ENOMEM;
-    YAO_HIP(hipMemcpyAsync(psi0, s->data, s->bytes(), hipMemcpyDeviceToDevice, st));
     if (mode != YAO_GRAD_CHECKPOINT) {
         // Reversible sweep in constant memory. AUTO checks how far the uncomputed input strayed
         // from the kept input and, past the tolerance, restores the input and runs the

@@ -292,10 +292,17 @@ int forward_fused(void* data, int dtype, int n, int B, const yao_circuit* c, con
 // Forward sweep at fusion width `width` (0: none) over tiles of tq qubits (<= 0: default);
 // dparams: c's parameters already on the device, or null.
 // also: another program of c to bind in the same launch; *also_bound tells whether that happened (a
-// sweep from a host-built program binds nothing).
+// sweep from a host-built program binds nothing). copy: done before the sweep, in the same launch where
+// two programs are bound.
 struct BoundProgram;
+struct CopyJob {
+    double* dst = nullptr;
+    const double* src = nullptr;
+    uint64_t count = 0;  // doubles
+};
 int forward_sweep(void* data, int dtype, int n, int B, const yao_circuit* c, const double* params, int width, int tq,
-                  const double* dparams, const BoundProgram* also = nullptr, bool* also_bound = nullptr);
+                  const double* dparams, const BoundProgram* also = nullptr, bool* also_bound = nullptr,
+                  const CopyJob* copy = nullptr);
 // Device-bound programs (built once per plan; see BindRec).
 // One circuit of a batch whose whole state fits one tile, run start to end by one workgroup
 // (k_small_circuit): forward program, then H psi and the energy, then the reverse program
@@ -326,7 +333,7 @@ struct BindJob {
     int nb, pad;
 };
 int launch_bind_jobs(const BindJob* jobs, int njobs, int max_nb);
-int launch_bind_pair(const BindJob& a, const BindJob& b);
+int launch_bind_pair(const BindJob& a, const BindJob& b, const CopyJob& copy);
 // count circuits of n qubits each, one workgroup apiece.
 int launch_small_circuits(const SmallCircuit* items, int count, int n);
 constexpr int kSmallMaxQubits = 12;  // psi and lambda in FP64: 32 B x 2^12 = 128 KiB of LDS
@@ -384,6 +391,9 @@ void jit_suspend(bool on);
 const BoundProgram* bound_program(const Plan& P, const yao_circuit* c, bool bwd, int dtype,
                                   const std::vector<FusedPart>* parts, const yao_circuit* orig);
 const double* upload_params(const double* params, int nparams);
+// The same without a copy: the pinned array itself, for bind launches that params_queued() follows.
+const double* pinned_params(const double* params, int nparams);
+int params_queued();
 int bind_program(const BoundProgram* b, const double* dparams);
 void drop_bound(const yao_circuit* c);
 // Gates [g0, g1) only.

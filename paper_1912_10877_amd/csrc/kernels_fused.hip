@@ -1789,9 +1789,14 @@ __global__ void k_bind(POp* __restrict__ ops, const BindRec* __restrict__ binds,
     bind_one(ops, binds[b], facs, params);
 }
 
-// Two programs for one set of parameters (a step's forward and reverse sweep).
-__global__ void k_bind_pair(BindJob a, BindJob b)
+// Two programs for one set of parameters (a step's forward and reverse sweep), and a copy (its input).
+__global__ void k_bind_pair(BindJob a, BindJob b, CopyJob copy)
 {
+    if (blockIdx.y == 2) {
+        for (uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; e < copy.count; e += (uint64_t)gridDim.x * blockDim.x)
+            copy.dst[e] = copy.src[e];
+        return;
+    }
     const BindJob& j = blockIdx.y ? b : a;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= j.nb) return;
@@ -1838,11 +1843,12 @@ int launch_bind(POp* ops, const BindRec* binds, int nbinds, const BindFac* facs,
     return 0;
 }
 
-int launch_bind_pair(const BindJob& a, const BindJob& b)
+int launch_bind_pair(const BindJob& a, const BindJob& b, const CopyJob& copy)
 {
     const int nb = std::max(a.nb, b.nb);
-    if (nb <= 0) return 0;
-    k_bind_pair<<<dim3((nb + 255) / 256, 2), 256, 0, stream()>>>(a, b);
+    if (nb <= 0 && copy.count == 0) return 0;
+    const int gx = std::max((nb + 255) / 256, (int)std::min<uint64_t>((copy.count + 255) / 256, 1024));
+    k_bind_pair<<<dim3(gx, copy.count ? 3 : 2), 256, 0, stream()>>>(a, b, copy);
     YAO_HIP(hipGetLastError());
     return 0;
 }

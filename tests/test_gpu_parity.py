@@ -376,3 +376,29 @@ def test_permuted_layouts_between_passes(dtype, n, B, tq):
         assert np.abs(s.download() - want).max() <= amp_tol(dtype, len(circ.gates))
     finally:
         yb.set_options(tile_qubits=0)
+
+
+@pytest.mark.parametrize("n,depth,dtype,offset", [(10, 2, 0, 2), (10, 2, 1, 1), (5, 280, 1, 0), (20, 1, 0, 0), (21, 1, 0, 0)])
+def test_input_kept_and_angles_read_by_the_binding_launch(n, depth, dtype, offset):
+    """The launch that binds a step's programs also keeps its input (up to 8 MB, 20 qubits of complex64) and
+    reads up to 4096 angles where the host wrote them: a wrapped tensor that starts 16 bytes into its
+    storage, more angles than that, states on both sides of the limit, and three calls in turn with new
+    angles on the state that the call before left."""
+    import torch
+
+    c = w.hea_circuit(n, depth)
+    assert (c.nparams > 4096) == (n == 5)
+    H = w.heisenberg(n)
+    buf = torch.zeros((1 << n) + offset, dtype=torch.complex64 if dtype == 0 else torch.complex128, device="cuda")
+    s = yb.State(n, 1, dtype, tensor=buf[offset:])
+    s.upload(w.random_state(n, 1, 9))
+    circ, h = yb.Circuit.from_workload(c), yb.PauliSum.from_workload(H)
+    for rep in range(3 if n < 20 else 1):
+        psi0 = s.download().astype(np.complex128)
+        params = w.angles(600 + rep, c.nparams)
+        e, g, drift = yb.backward(s, circ, params, h)
+        e_ref, g_ref, _ = oracle.adjoint(H, c, params, psi0)
+        np.testing.assert_allclose(e, e_ref, atol=1e-10 if dtype == 1 else 1e-5)
+        assert np.abs(g - g_ref).max() <= grad_tol(dtype, g_ref)
+        assert drift <= (1e-11 if dtype == 1 else 1e-5)
+        assert np.abs(s.download() - oracle.forward(c, params, psi0)).max() <= amp_tol(dtype, len(c.gates))
