@@ -363,9 +363,27 @@ int build_programs(Cache& C, const double* const* params, bool first)
     return 0;
 }
 
-bool same_geometry(const Plan* a, const Plan* b)
+// Whether the records of two circuits of the same gates lie alike under these plans, so that one plan's
+// launches can read the other's: the same passes over the same tiles and register groups, in the same
+// form (compiled forward plans of complex64 states keep some matrices as float[16], see
+// use_real_forms; above 20 qubits they have the generic kernels' tiles).
+bool same_records(const Plan* a, const Plan* b)
 {
-    return a == b || (a->t == b->t && a->reg_bits == b->reg_bits);
+    if (a == b) return true;
+    if (a->compiled != b->compiled || a->c != b->c || a->t != b->t || a->reg_bits != b->reg_bits ||
+        a->max_slots != b->max_slots || a->passes.size() != b->passes.size())
+        return false;
+    for (size_t p = 0; p < a->passes.size(); ++p) {
+        const HostPass &x = a->passes[p], &y = b->passes[p];
+        if (x.tile_qubits != y.tile_qubits || x.store_src != y.store_src || x.phys != y.phys ||
+            x.standalone != y.standalone || x.groups.size() != y.groups.size())
+            return false;
+        for (size_t g = 0; g < x.groups.size(); ++g)
+            if (x.groups[g].ops != y.groups[g].ops || x.groups[g].rbits != y.groups[g].rbits ||
+                x.groups[g].lds != y.groups[g].lds || x.groups[g].dense != y.groups[g].dense)
+                return false;
+    }
+    return true;
 }
 
 const Program& fwd_prog(const Item& it)
@@ -686,7 +704,7 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
                 const Item& lead = C.items[members[v][0]];
                 if ((int)members[v].size() < kZUnitMax &&
                     z_item_bytes(lead) * (members[v].size() + 1) <= kZUnitBytes && lead.W == it.W &&
-                    lead.nslots == it.nslots && same_geometry(lead.fwd, it.fwd) && same_geometry(lead.bwd, it.bwd) &&
+                    lead.nslots == it.nslots && same_records(lead.fwd, it.fwd) && same_records(lead.bwd, it.bwd) &&
                     same_gates(lead.c, it.c) && same_observable(lead.h, it.h)) {
                     u = v;
                     break;

@@ -307,3 +307,56 @@ def test_full_1024_circuit_workload():
         assert len(g[i]) == len(g_ref)
         err = float(np.abs(g[i] - g_ref).max())
         assert err <= tg * max(1.0, float(np.abs(g_ref).max())), (i, spec[i], err)
+
+
+def against_oracle(states, circs, hams, params, refs, dtype):
+    e, g = yb.batch_run(states, circs, params, hams)
+    check(e, g, params, refs, dtype)
+    for i, (c, _) in enumerate(refs):
+        ref = oracle.forward(c, params[i], w.zero_state(c.n))
+        assert np.abs(states[i].download() - ref).max() <= (1e-5 if dtype == 0 else 1e-11), i
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_compiled_and_uncompiled_circuits_of_one_structure(first):
+    """Two equal circuits above 20 qubits, of which one has run alone before and is compiled: the compiled
+    forward passes of complex64 states keep their merged gates in a form of their own, over the same tiles
+    as the generic kernels, so the two must not share launches. In both orders."""
+    yb.set_options(jit=1, autotune=0, fuse_width=1)
+    try:
+        c, H = w.hea_circuit(21, 1), w.heisenberg(21)
+        states = [yb.State(21, 1, 0) for _ in range(2)]
+        circs = [yb.Circuit.from_workload(c) for _ in range(2)]
+        hams = [yb.PauliSum.from_workload(H) for _ in range(2)]
+        params = [w.angles(9100 + i, c.nparams) for i in range(2)]
+        l0 = yb.jit_stats()["fwd_launches"]
+        yb.backward(states[first], circs[first], params[first], hams[first])
+        assert yb.jit_stats()["fwd_launches"] > l0, "not compiled"
+        against_oracle(states, circs, hams, params, [(c, H)] * 2, 0)
+    finally:
+        yb.set_options(jit=3, autotune=1, fuse_width=0)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("what", ["large", "observable"])
+def test_units_of_the_generic_kernels(what, dtype):
+    """Circuits of one structure that share every launch through a slot table: above 20 qubits, and without
+    gradients (13 qubits, no parameters, from fixed gates alone)."""
+    yb.set_options(autotune=0, fuse_width=1)
+    try:
+        n = 21 if what == "large" else 13
+        if what == "large":
+            c = w.hea_circuit(n, 1)
+        else:
+            rng = np.random.default_rng(5)
+            c = w.Circuit(n, [w.Gate("dense", (q,), G=w.haar_su2(rng)) for q in range(n)] +
+                          [w.Gate("X", ((q + 1) % n,), (q,)) for q in range(n)], 0)
+        H = w.heisenberg(n)
+        states = [yb.State(n, 1, dtype) for _ in range(3)]
+        circs = [yb.Circuit.from_workload(c) for _ in range(3)]
+        hams = [yb.PauliSum.from_workload(H) for _ in range(3)]
+        for rep in range(2):
+            params = [w.angles(9200 + 10 * rep + i, c.nparams) for i in range(3)]
+            against_oracle(states, circs, hams, params, [(c, H)] * 3, dtype)
+    finally:
+        yb.set_options(autotune=1, fuse_width=0)
