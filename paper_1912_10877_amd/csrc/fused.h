@@ -88,7 +88,8 @@ __host__ __device__ inline void split_diag_phase(double* u)
 // The unit form of a rotation: [[c, i s], [i s, c]] = f [[1, i k], [i k, 1]] and diag(c + i s, c - i s) =
 // f diag(1 + i k, 1 - i k) with f = c and k = s / c, as u[1] = k, u[2] = f. A rotation by pi has
 // c = 6e-17 in FP64 and keeps its precision: each entry of the product is one rounding of a + k b,
-// whatever k is. c = 0 takes 2^-60, below the rounding of s.
+// whatever k is. c = 0 (no finite angle has it: the smallest cosine of a double is 2^-61) takes 2^-60, below
+// the rounding of s.
 __host__ __device__ inline void split_rotation(double* u, double s)
 {
     const double c = u[0] == 0.0 ? 0x1p-60 : u[0];

@@ -442,11 +442,12 @@ __device__ __forceinline__ void rz_unit(double2& a, double2& b, double k)
     a = make_double2(fma(-k, p.y, p.x), fma(k, p.x, p.y));
     b = make_double2(fma(k, q.y, q.x), fma(-k, q.x, q.y));
 }
-// |F| < 2^-40, wave-uniform.
-__device__ __forceinline__ bool scale_low(double F)
+// |F| < 2^-40 (the high word of F below lim), wave-uniform.
+constexpr unsigned kScaleLow = (1023u - 40u) << 20;
+__device__ __forceinline__ bool scale_low(double F, unsigned lim)
 {
     const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(__builtin_bit_cast(u64, F) >> 32));
-    return (hi & 0x7fffffffu) < ((1023u - 40u) << 20);
+    return (hi & 0x7fffffffu) < lim;
 }
 // Exchanges two double2 registers in place (v_swap_b32 on each 32-bit half), so that a swap
 // under a lane mask needs neither selects nor copies where the lanes rejoin.
@@ -532,15 +533,34 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     std::vector<uint64_t> rofs;
     o << tile_code(P, pass, n, rofs);
     o << "  {\n";
+    // Lambda of complex64 states as 64-bit words (as two floats, which the maximum below reads, its writes to LDS
+    // come out as pairs of 32 bits).
+    const std::string WL = c64 ? "u64" : VL;
     for (int r = 0; r < N; ++r)
-        o << "    const double2 v" << r << " = gp[toff + " << U(rofs[r]) << "]; const " << VL << " w" << r << " = gl[toff + "
-          << U(rofs[r]) << "];\n";
+        o << "    const double2 v" << r << " = gp[toff + " << U(rofs[r]) << "]; const " << WL << " w" << r << " = ((GLB " << WL
+          << "*)gl)[toff + " << U(rofs[r]) << "];\n";
     o << "    " << positions("lpos", thread_bits);
     for (int r = 0; r < N; ++r)
-        o << "    " << at_psi("lpos", (uint32_t)r * nthr) << " = v" << r << "; " << at_lam("lpos", (uint32_t)r * nthr) << " = w"
-          << r << ";\n";
+        o << "    " << at_psi("lpos", (uint32_t)r * nthr) << " = v" << r << "; *(LDS " << WL << "*)&"
+          << at_lam("lpos", (uint32_t)r * nthr) << " = w" << r << ";\n";
+    // big: some lambda of the tile is at 2^80 or above (see the scale F below). A word a wave, in the second
+    // buffer of partials, which the second register group writes first.
+    const size_t big_at = ((size_t)(16 + lb) << t) + sizeof(double) * (size_t)std::max(1, maxslots) * E;
+    if (c64) {
+        o << "    unsigned wm = 0;\n";
+        for (int r = 0; r < N; ++r)
+            o << "    wm = max(wm, max((unsigned)w" << r << " & 0x7fffffffu, (unsigned)(w" << r << " >> 32) & 0x7fffffffu));\n";
+        o << "    const u64 wide = __builtin_amdgcn_ballot_w64(wm >= " << ((127 + 80) << 23) << "u);\n"
+          << "    ((LDS unsigned*)((LDS char*)smem + " << big_at << "))[th >> 6] = wide != 0;\n";  // every lane the same
+    }
     o << "  }\n  __syncthreads();\n";
     o << "  double F = 1.0;\n";
+    if (c64) {
+        o << "  unsigned big = 0;\n";
+        for (int i = 0; i < std::max(1, nthr / 64); ++i)
+            o << "  big |= ((LDS unsigned*)((LDS char*)smem + " << big_at << "))[" << i << "];\n";
+        o << "  const unsigned lim = __builtin_amdgcn_readfirstlane(big) ? 0xffffffffu : kScaleLow;\n";
+    }
     // LDS address of a lane pair's first partial, kept in a register: the partials' own offsets are immediates.
     if (red_lanes == 2)
         o << "  unsigned rad = (unsigned)(u64)(LDS double*)red0 + " << (P.c ? "((th >> 4) * 8u + (th & 7u))" : "(th >> 1)") << " * 8u;\n  asm volatile(\"\" : \"+v\"(rad));\n";
@@ -592,17 +612,22 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
     // the plain matrix takes a multiply and an FMA, and their factors f collect in F, common to psi,
     // lambda and every element (gradients take F^2). The values in registers are 1 / F of what they
     // stand for; where |F| has come below 2^-40 they are multiplied by it, looked at after every
-    // kScaledOps rotations (their f is 6e-17 at least, so F^2 stays in range) and before lambda is
-    // rounded to the state's precision at a group's end. FP64 issue is most of a reverse pass: with
+    // kScaledOps rotations and before lambda is rounded to the state's precision at a group's end. Range:
+    // the cosine of half of pi is 2^-54 in FP64 and no finite angle's is below 2^-61, so the F that a gradient
+    // takes has at most five such factors and stays above 2^-345, F^2 above 2^-690; the products of two
+    // values in registers stay finite for |psi| |lambda| up to 2^334 (looked at after eight rotations: 2^90).
+    // Lambda lies in LDS as float for complex64 states, up to 2^40 above its value: tiles with an entry over
+    // 2^80 (their norm, and so every later entry, is below 2^86 where there is none) multiply by F at
+    // every group's end. FP64 issue is most of a reverse pass: with
     // 16 + 16 + 32 instructions for an Rx on 8 amplitudes in place of 16 + 64, with no phase
     // entries left among the scalar loads (they had spilled into vector lanes behind a wait each) and
     // the group's sums through DPP adds instead of LDS permutes, the 20-qubit depth-20 sweep's twelve
     // passes went from 737 to 636 us.
-    constexpr int kScaledOps = 8;
+    constexpr int kScaledOps = 6;
     bool scaled = false;  // F may differ from 1
     int nscaled = 0;
-    auto emit_rescale = [&]() {
-        o << "    if (scale_low(F)) {\n";
+    auto emit_rescale = [&](bool rounds) {
+        o << "    if (scale_low(F, " << (rounds && c64 ? "lim" : "kScaleLow") << ")) {\n";
         for (int r = 0; r < N; ++r)
             o << "      x" << r << ".x *= F; x" << r << ".y *= F; y" << r << ".x *= F; y" << r << ".y *= F;\n";
         o << "      F = 1.0;\n    }\n";
@@ -721,7 +746,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             if (cls <= 1) {
                 o << "      F *= u[2];\n";
                 scaled = true;
-                if (++nscaled == kScaledOps) emit_rescale();
+                if (++nscaled == kScaledOps) emit_rescale(false);
             }
             o << "    }\n";
             // The op's u[k] are the prefetched U<cur>_k.
@@ -735,7 +760,7 @@ std::string gen_backward_pass(const Plan& P, const Program& prog, int p, int n, 
             o << body;
         }
         if (nslot != G.nslot) return "";  // the record's slots and the group's list disagree
-        if (scaled) emit_rescale();
+        if (scaled) emit_rescale(true);
         for (int r = 0; r < N; ++r)
             o << "    " << at_psi("sw", er[r]) << " = x" << perm[r] << "; " << at_lam("sw", er[r]) << " = make_"
               << VL << "((" << RL << ")y" << perm[r] << ".x, (" << RL << ")y" << perm[r] << ".y);\n";

@@ -325,3 +325,28 @@ def test_compiled_passes_of_a_batch(n, B, dtype):
     s.upload(psi0)
     _, total, _ = yb.backward(s, circ, params, h, reduce_batch=True)
     assert np.abs(total - g_ref.sum(0)).max() <= tg * scale * B
+
+
+@pytest.mark.parametrize("n,B", [(13, 1), (17, 1), (10, 5)])
+@pytest.mark.parametrize("dtype,scale,angles", [(0, 1e-25, "random"), (0, 1e28, "random"), (0, 1e28, "pi"),
+                                                (1, 1e28, "random"), (1, 1e90, "pi")])
+def test_compiled_reverse_of_large_and_small_observables(dtype, scale, angles, n, B):
+    """Observables of coefficients far from 1: lambda = H psi is kept in the state's precision between the
+    register groups of a compiled reverse pass (a float reaches 3.4e38), and rotations by pi in a row divide
+    every value by 6e-17 each before it is put right. Same bounds as above, in units of the coefficients."""
+    yb.set_options(jit=1, autotune=0, fuse_width=0)
+    c, H = w.hea_circuit(n, 2), w.heisenberg(n)
+    circ = yb.Circuit.from_workload(c)
+    h = yb.PauliSum(n, np.asarray(H.coef) * scale, H.xmask, H.zmask)
+    params = w.angles(1700 + n, c.nparams) if angles == "random" else np.full(c.nparams, np.pi)
+    psi0 = w.random_state(n, B, 78)
+    s = yb.State(n, B, dtype)
+    s.upload(psi0)
+    psi0 = s.download().astype(np.complex128)
+    l0 = yb.jit_stats()["bwd_launches"]
+    e, g, _ = yb.backward(s, circ, params, h)
+    assert yb.jit_stats()["bwd_launches"] > l0, "the reverse sweep did not use the compiled passes"
+    e_ref, g_ref, _ = oracle.adjoint(H, c, params, psi0)
+    te, tg = (1e-5, 1e-4) if dtype == 0 else (1e-10, 1e-9)
+    assert np.abs(e / scale - e_ref).max() <= te
+    assert np.abs(g / scale - g_ref).max() <= tg * max(1.0, float(np.abs(g_ref).max()))
