@@ -801,9 +801,19 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     YAO_TRY(pick_forward_width(c, params, s->data, s->dtype, n, B, &width));
     const double* dp = nullptr;
     const bool direct = bp && c->nparams <= kPinnedParams;
+    // Where launches read the pinned angles, the event that says they have is recorded on every way out of
+    // here, failures after such a launch included.
+    struct Queued {
+        bool due = false;
+        ~Queued()
+        {
+            if (due && params_queued() != 0) (void)hipStreamSynchronize(stream());
+        }
+    } queued;
     if (c->nparams > 0) {
         dp = direct ? pinned_params(params, c->nparams) : upload_params(params, c->nparams);
         if (!dp) return YAO_ENOMEM;
+        queued.due = direct;
     }
     bool bound = false;
     const CopyJob input{(double*)psi0, (const double*)s->data, s->bytes() / sizeof(double)};
@@ -818,7 +828,10 @@ static int backward_reversible(yao_state* s, const yao_circuit* c, const double*
     DevProgram hd;
     if (!bp) YAO_TRY(upload_program(hprog, hd, WS_MAT2));
     else if (!bound) YAO_TRY(bind_program(bp, dp));
-    if (direct && dp) YAO_TRY(params_queued());
+    if (queued.due) {
+        YAO_TRY(params_queued());
+        queued.due = false;
+    }
     const Program& prog = bp ? bp->prog : hprog;
     YAO_TRY(launch_backward_passes(*P, prog, bp ? bp->d : hd, c, params, psi, lam, s->dtype, n, B, gpartial, W, bp));
     const double *eh = nullptr, *sums = nullptr;
