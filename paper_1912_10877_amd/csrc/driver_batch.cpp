@@ -64,7 +64,7 @@ struct Item {
     int bank = 0;
     int phase = 0;  // recording phase by state size (see record)
     bool small = false;  // run start to end by one workgroup (k_small_circuit)
-    bool lone = false;   // kept out of level units
+    bool level = false;  // in a level unit
     int nslots = 0;
     int W = 0;                    // partial-sum row stride of the reverse passes
     size_t out_e = 0, out_g = 0;  // positions in the output block
@@ -218,7 +218,8 @@ int reverse_stride(const Plan& P)
     return std::max(1 << (P.n - (P.t - P.c)), adjoint_nblk(P.n, 1, 1));
 }
 
-// A circuit whose passes were compiled by earlier calls of its own keeps them in a batch.
+// A circuit whose passes were compiled by earlier calls of its own keeps them in a batch, outside the
+// level units.
 void use_compiled(const Plan*& P, const BoundProgram*& bp)
 {
     if (!bp->alt) return;
@@ -332,14 +333,14 @@ int build_programs(Cache& C, const double* const* params, bool first)
             if (it.bf && !used.insert(it.bf).second) it.bf = nullptr;
             if (it.bf) {
                 it.fwd = &pf;
-                use_compiled(it.fwd, it.bf);
+                if (!it.level) use_compiled(it.fwd, it.bf);
                 it.fc = sc;
                 it.fc_version = sc->version;
             }
             it.bwd = &plan_for(it.c, it.s->n, dt, true, it.tune.tq_b);
             if (it.nslots) it.bb = bound_program(*it.bwd, it.c, true, dt, nullptr, nullptr);
             if (it.bb && !used.insert(it.bb).second) it.bb = nullptr;
-            if (it.bb) use_compiled(it.bwd, it.bb);
+            if (it.bb && !it.level) use_compiled(it.bwd, it.bb);
         }
         if (!it.bf) {
             const double* fp = nullptr;
@@ -446,27 +447,59 @@ bool z_capable(const Item& it)
     return obs_passes_ok(it.h, it.s->n, 1, it.s->dtype, OBS_VECTOR);
 }
 
-// A circuit that a level unit takes: gradients, every gate a tile pass takes, H psi one launch of full
-// blocks (9 to 20 qubits). Its programs may be bound on the device or built on the host.
+// A circuit that a level unit takes: gradients, tile passes alone, H psi one launch of full blocks (9 to 20
+// qubits). Its programs may be bound on the device or built on the host.
+bool tile_passes_only(const Plan& P)
+{
+    bool ok = P.valid && P.c == 0;
+    for (const HostPass& p : P.passes) ok &= p.standalone < 0;
+    return ok;
+}
 bool level_candidate(const Item& it)
 {
     const int n = it.s->n;
-    if (it.small || it.lone || n < 9 || n > 20 || it.nslots == 0) return false;
+    if (it.small || n < 9 || n > 20 || it.nslots == 0) return false;
     for (const GateRec& g : it.c->gates)
         if (g.k > kMaxFusedK) return false;
-    return obs_one_launch(it.h, n, 1, it.s->dtype);
+    const yao_circuit* sc = it.tune.width > 0 ? fused_shape(it.c, it.tune.width, nullptr) : it.c;
+    return tile_passes_only(plan_for(sc, n, it.s->dtype, false, it.tune.tq_f)) && obs_one_launch(it.h, n, 1, it.s->dtype);
 }
-// With its plans: tile passes of the generic kernels.
-bool level_capable(const Item& it)
+// Whether the reverse passes of a circuit, most of its time, were compiled by earlier calls of its own (which go by
+// the option's tiles, not by those tuned for the generic kernels).
+bool reverse_compiled(const Item& it)
 {
-    if (!level_candidate(it) || it.fwd->c != 0 || it.bwd->c != 0) return false;
-    if ((it.bf && it.bf->jit) || (it.bb && it.bb->jit)) return false;
-    for (const Plan* P : {it.fwd, it.bwd}) {
-        if (!P->valid) return false;
-        for (const HostPass& p : P->passes)
-            if (p.standalone >= 0) return false;
+    if (!any_compiled(it.c)) return false;
+    const BoundProgram* b =
+        find_bound(plan_for(it.c, it.s->n, it.s->dtype, true, options().tile_qubits), true, it.s->dtype);
+    return b && (b->jit || b->alt);
+}
+// The circuits of level units. Candidates that are all compiled stay outside where they are of three kinds at
+// most (of other gates, sizes or observables): those run side by side in the first phase, on streams of their own
+// and each kind in shared launches, while a level unit runs the generic kernels. Compiled against level: one of 20
+// qubits, depth 8, complex64 441 and 736 us; one of 14 qubits, depth 5, complex128 198 and 263; 16 and 17
+// qubits 307 and 328; three of 17 and 18 493 and 571. With more kinds their passes of a few tiles run
+// one after the other: of twelve from 12 to 16 qubits 1076 and 594, of 24 from 8 to 19 1873 and 1486.
+constexpr size_t kCompiledKinds = 3;
+void pick_level(std::vector<Item>& items)
+{
+    std::vector<const Item*> kinds;
+    bool compiled = true;
+    for (Item& it : items) {
+        it.level = level_candidate(it);
+        compiled = compiled && (!it.level || reverse_compiled(it));
+        if (!it.level || kinds.size() > kCompiledKinds) continue;
+        bool seen = false;
+        for (const Item* k : kinds)
+            seen |= k->s->n == it.s->n && same_gates(k->c, it.c) && same_observable(k->h, it.h);
+        if (!seen) kinds.push_back(&it);
     }
-    return true;
+    if (!compiled || kinds.size() > kCompiledKinds) return;
+    for (Item& it : items)
+        if (it.level) {
+            it.level = false;
+            it.phase = 0;
+            it.tune.tq_b = options().tile_qubits;
+        }
 }
 // The reverse tiles of level units, where they make a block a CU at least: tuned alone a 20-qubit circuit
 // takes 12 qubits (a 512-thread block a CU), but with other circuits' tiles at hand three
@@ -599,7 +632,6 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         it.nslots = count_param_slots(it.c);
         it.cost = (double)(it.c->gates.size() + 1) * (double)(uint64_t(1) << n);
         it.phase = batch_phase(n);
-        it.lone = !C.share;
     }
     // Circuits whose whole state fits one tile run start to end in one workgroup, from
     // programs of one pass each (3 register bits, FP64 matrices) bound on the device; a
@@ -659,16 +691,18 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         for (Item& it : C.items)
             if (!it.small && it.s->n == kv.first.first && it.s->dtype == kv.first.second) it.tune = t;
     }
+    if (C.share) pick_level(C.items);
     if (C.opt.tile_qubits == 0) {
         uint64_t tiles = 0;
         for (const Item& it : C.items)
-            if (level_candidate(it)) tiles += (uint64_t(1) << it.s->n) >> std::min(it.s->n, kLevelTile);
+            if (it.level) tiles += (uint64_t(1) << it.s->n) >> std::min(it.s->n, kLevelTile);
         for (Item& it : C.items)
-            if (tiles >= kLevelTiles && level_candidate(it)) it.tune.tq_b = kLevelTile;
+            if (it.level && tiles >= kLevelTiles) it.tune.tq_b = kLevelTile;
     }
     YAO_TRY(build_programs(C, params, true));
+    for (Item& it : C.items) it.level &= tile_passes_only(*it.fwd) && tile_passes_only(*it.bwd);
     for (Item& it : C.items)
-        if (!it.small) it.W = level_capable(it) ? 1 << (it.bwd->n - (it.bwd->t - it.bwd->c)) : reverse_stride(*it.bwd);
+        if (!it.small) it.W = it.level ? 1 << (it.bwd->n - (it.bwd->t - it.bwd->c)) : reverse_stride(*it.bwd);
 
     // Units: circuits of one structure with bound programs together (z units), every other
     // circuit alone; the small circuits stay outside the units.
@@ -680,7 +714,7 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         for (int i = 0; i < (int)C.items.size(); ++i) {
             const Item& it = C.items[i];
             if (it.small) continue;
-            if (level_capable(it)) {
+            if (it.level) {
                 const size_t bytes = z_item_bytes(it);
                 auto& u = levels[std::make_tuple(it.s->dtype, it.fwd->t, it.bwd->t)];
                 if (u.second == 0 || u.second + bytes > kZUnitBytes || members[u.first].size() >= kLevelMax) {
@@ -720,7 +754,7 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
         }
     }
     levelunit.assign(members.size(), false);
-    for (size_t u = 0; u < members.size(); ++u) levelunit[u] = level_capable(C.items[members[u][0]]);
+    for (size_t u = 0; u < members.size(); ++u) levelunit[u] = C.items[members[u][0]].level;
     // By phase, then largest units first, each on the least loaded stream of its phase; the
     // items are reordered so that each unit's circuits follow each other (their energies and
     // gradient sums then sit in consecutive output entries).

@@ -545,6 +545,21 @@ void drop_bound(const yao_circuit* c)
     }
 }
 
+const BoundProgram* find_bound(const Plan& P, bool bwd, int dtype)
+{
+    std::lock_guard<std::mutex> lk(g_bound_mu);
+    auto it = g_bound.find(std::make_tuple(&P, bwd, dtype));
+    return it != g_bound.end() && it->second->ok ? it->second : nullptr;
+}
+
+bool any_compiled(const yao_circuit* c)
+{
+    std::lock_guard<std::mutex> lk(g_bound_mu);
+    for (const auto& kv : g_bound)
+        if (kv.second->circ == c && kv.second->jit) return true;
+    return false;
+}
+
 // The bound program of plan P over circuit c (with parts/orig for a fused structure), or
 // nullptr when it cannot be bound on the device. Built and copied on first use.
 const BoundProgram* bound_program(const Plan& P, const yao_circuit* c, bool bwd, int dtype,

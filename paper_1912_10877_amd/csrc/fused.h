@@ -391,6 +391,9 @@ int jit_launch_backward(const JitPasses* J, int p, double* psi, void* lam, const
 void jit_suspend(bool on);
 const BoundProgram* bound_program(const Plan& P, const yao_circuit* c, bool bwd, int dtype,
                                   const std::vector<FusedPart>* parts, const yao_circuit* orig);
+// The same where it was built before, or nullptr; and whether a circuit has a program with compiled passes.
+const BoundProgram* find_bound(const Plan& P, bool bwd, int dtype);
+bool any_compiled(const yao_circuit* c);
 const double* upload_params(const double* params, int nparams);
 // The same without a copy: the pinned array itself, for bind launches that params_queued() follows.
 const double* pinned_params(const double* params, int nparams);

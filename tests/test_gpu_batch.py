@@ -360,3 +360,26 @@ def test_units_of_the_generic_kernels(what, dtype):
             against_oracle(states, circs, hams, params, [(c, H)] * 3, dtype)
     finally:
         yb.set_options(autotune=1, fuse_width=0)
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("sizes,alone", [([(13, 1), (13, 2), (14, 1), (14, 2), (15, 1)], False),
+                                         ([(13, 1), (14, 2), (13, 1)], True), ([(20, 1)], True)])
+def test_lists_of_compiled_circuits(sizes, alone, dtype):
+    """Circuits that have run alone before and are compiled: of more than three kinds they share launches of
+    the generic kernels with each other (no compiled pass is recorded), of fewer they keep their compiled
+    passes. Then the list in which only every other circuit is compiled, which keeps none beside another."""
+    yb.set_options(jit=1, autotune=0, fuse_width=1)
+    try:
+        for compiled in (range(len(sizes)), range(0, len(sizes), 2)):
+            states, circs, hams, params, refs = make_batch([(n, d, 9300 + i) for i, (n, d) in enumerate(sizes)], dtype)
+            for i in compiled:
+                yb.backward(states[i], circs[i], params[i], hams[i])
+            l0 = yb.jit_stats()
+            against_oracle(states, circs, hams, params, refs, dtype)
+            l1 = yb.jit_stats()
+            kept = alone and len(compiled) == len(sizes)
+            assert (l1["bwd_launches"] > l0["bwd_launches"]) == kept
+            assert (l1["fwd_launches"] > l0["fwd_launches"]) == kept
+    finally:
+        yb.set_options(jit=3, autotune=1, fuse_width=0)
