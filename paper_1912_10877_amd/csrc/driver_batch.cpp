@@ -483,10 +483,12 @@ constexpr size_t kCompiledKinds = 3;
 void pick_level(std::vector<Item>& items)
 {
     std::vector<const Item*> kinds;
+    std::set<const yao_circuit*> listed;
     bool compiled = true;
     for (Item& it : items) {
         it.level = level_candidate(it);
-        compiled = compiled && (!it.level || reverse_compiled(it));
+        // (listed twice: only one entry can have the compiled programs)
+        compiled = compiled && (!it.level || (listed.insert(it.c).second && reverse_compiled(it)));
         if (!it.level || kinds.size() > kCompiledKinds) continue;
         bool seen = false;
         for (const Item* k : kinds)

@@ -383,3 +383,17 @@ def test_lists_of_compiled_circuits(sizes, alone, dtype):
             assert (l1["fwd_launches"] > l0["fwd_launches"]) == kept
     finally:
         yb.set_options(jit=3, autotune=1, fuse_width=0)
+
+
+def test_compiled_circuit_listed_again_and_again():
+    """One compiled circuit with several registers and sets of angles: only one entry could run its compiled
+    programs, so all of them share launches of the generic kernels."""
+    yb.set_options(jit=1, autotune=0, fuse_width=1)
+    try:
+        states, circs, hams, params, refs = make_batch([(13, 2, 9400 + i) for i in range(4)], 0)
+        yb.backward(states[0], circs[0], params[0], hams[0])
+        l0 = yb.jit_stats()
+        against_oracle(states, [circs[0]] * 4, hams, params, refs, 0)
+        assert yb.jit_stats() == l0
+    finally:
+        yb.set_options(jit=3, autotune=1, fuse_width=0)
