@@ -219,10 +219,14 @@ int reverse_stride(const Plan& P)
 }
 
 // A circuit whose passes were compiled by earlier calls of its own keeps them in a batch, outside the
-// level units.
+// level units; not where the options name the tiles and those passes have others.
+bool takes_compiled(const Plan& P, const BoundProgram* bp)
+{
+    return bp->alt && (options().tile_qubits == 0 || bp->alt_plan->t == P.t);
+}
 void use_compiled(const Plan*& P, const BoundProgram*& bp)
 {
-    if (!bp->alt) return;
+    if (!takes_compiled(*P, bp)) return;
     P = bp->alt_plan;
     bp = bp->alt;
 }
@@ -469,9 +473,9 @@ bool level_candidate(const Item& it)
 bool reverse_compiled(const Item& it)
 {
     if (!any_compiled(it.c)) return false;
-    const BoundProgram* b =
-        find_bound(plan_for(it.c, it.s->n, it.s->dtype, true, options().tile_qubits), true, it.s->dtype);
-    return b && (b->jit || b->alt);
+    const Plan& P = plan_for(it.c, it.s->n, it.s->dtype, true, options().tile_qubits);
+    const BoundProgram* b = find_bound(P, true, it.s->dtype);
+    return b && (b->jit || takes_compiled(P, b));
 }
 // The circuits of level units. Candidates that are all compiled stay outside where they are of three kinds at
 // most (of other gates, sizes or observables): those run side by side in the first phase, on streams of their own

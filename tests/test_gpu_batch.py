@@ -397,3 +397,20 @@ def test_compiled_circuit_listed_again_and_again():
         assert yb.jit_stats() == l0
     finally:
         yb.set_options(jit=3, autotune=1, fuse_width=0)
+
+
+def test_named_tiles_are_taken_as_given():
+    """Circuits compiled over tiles of the library's choice (10 qubits in the reverse sweep of 13), then listed with
+    tile_qubits set to what the generic kernels would take by themselves: no compiled reverse pass is
+    recorded."""
+    yb.set_options(jit=1, autotune=0, fuse_width=1)
+    try:
+        states, circs, hams, params, refs = make_batch([(13, 1, 9500 + i) for i in range(2)], 0)
+        for i in range(2):
+            yb.backward(states[i], circs[i], params[i], hams[i])
+        yb.set_options(tile_qubits=12)
+        l0 = yb.jit_stats()["bwd_launches"]
+        against_oracle(states, circs, hams, params, refs, 0)
+        assert yb.jit_stats()["bwd_launches"] == l0
+    finally:
+        yb.set_options(jit=3, autotune=1, fuse_width=0, tile_qubits=0)
