@@ -466,7 +466,7 @@ bool level_candidate(const Item& it)
     for (const GateRec& g : it.c->gates)
         if (g.k > kMaxFusedK) return false;
     const yao_circuit* sc = it.tune.width > 0 ? fused_shape(it.c, it.tune.width, nullptr) : it.c;
-    return tile_passes_only(plan_for(sc, n, it.s->dtype, false, it.tune.tq_f)) && obs_one_launch(it.h, n, 1, it.s->dtype);
+    return tile_passes_only(plan_for(sc, n, it.s->dtype, false, it.tune.tq_f)) && obs_one_launch(it.h, n, 1, it.s->dtype, OBS_ONE);
 }
 // Whether the reverse passes of a circuit, most of its time, were compiled by earlier calls of its own (which go by
 // the option's tiles, not by those tuned for the generic kernels).
@@ -515,12 +515,19 @@ constexpr int kLevelTile = 11;
 constexpr uint64_t kLevelTiles = 256;
 constexpr size_t kLevelMax = 16384;  // circuits of one level unit at most (a grid dimension of its resets)
 
+// Partial sums of an item's H psi.
+size_t item_hpart(const Item& it)
+{
+    const int n = it.s->n, dt = it.s->dtype;
+    return it.level ? obs_partial_doubles(it.h, n, 1, dt, OBS_ONE) : hpsi_partial_doubles(it.h, n, 1, dt);
+}
+
 // Scratch of one circuit of a z unit: psi in FP64, lambda, reverse and H psi partial sums.
 size_t z_item_bytes(const Item& it)
 {
     const size_t N = size_t(1) << it.s->n;
     return (16 + it.s->elem_bytes()) * N +
-           sizeof(double) * ((size_t)std::max(1, it.nslots) * it.W + hpsi_partial_doubles(it.h, it.s->n, 1, it.s->dtype));
+           sizeof(double) * ((size_t)std::max(1, it.nslots) * it.W + item_hpart(it));
 }
 constexpr size_t kZUnitBytes = size_t(2) << 30;  // scratch of one z unit at most
 constexpr int kZUnitMax = 1024;                   // circuits of one z unit at most
@@ -558,7 +565,7 @@ int build_level(Cache& C, const Unit& U)
         lam.push_back((char*)C.lam[U.bank] + it.s->elem_bytes() * amps);
         gp.push_back(C.gpart[U.bank] + g);
         double* hp = C.hpart[U.bank] + e;
-        const size_t cols = hpsi_partial_doubles(it.h, n, 1, L.dtype);
+        const size_t cols = item_hpart(it);
         amps += size_t(1) << n;
         g += (size_t)it.nslots * it.W;
         e += cols;
@@ -825,7 +832,7 @@ int build_cache(Cache& C, int ncirc, yao_state* const* states, const yao_circuit
                 const Item& it = C.items[U.first + j];
                 amps += size_t(1) << it.s->n;
                 g += (size_t)it.nslots * it.W;
-                e += hpsi_partial_doubles(it.h, it.s->n, 1, it.s->dtype);
+                e += item_hpart(it);
             }
             psi_b[best] = std::max(psi_b[best], 16 * amps);
             lam_b[best] = std::max(lam_b[best], lead.s->elem_bytes() * amps);

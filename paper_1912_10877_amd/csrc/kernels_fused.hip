@@ -14,6 +14,7 @@
 // The op records are read where they lie, through the scalar cache; the record of the next op is
 // fetched while the current op computes.
 #include <algorithm>
+#include <cmath>
 #include <map>
 #include <tuple>
 #include <mutex>
@@ -2114,21 +2115,41 @@ int obs_gather_reg_bits(int n)
     return n <= 17 ? 1 : 2;
 }
 
-// Whether a single-slot state takes k_obs_gather rather than npasses tile passes over nmasks X
-// masks. Up to 20 qubits it always does (20-qubit Heisenberg H psi 20 against 47 us at complex64, 31
-// against 41 us at complex128; with 30 masks in one pass both 20 and 25 us). Above, a mask costs a
-// read of the state from the caches, and a pass its own read, with an output a read and a write of
-// that too: the Heisenberg chain's H psi (9 to 11 masks a pass) takes 540 against 955 us at 25
-// qubits complex64 and 493 against 561 us at 24 qubits complex128 (22 qubits: 121 against 111 us),
-// its energy 513 against 463 us at 25 qubits complex64. States beyond the 256 MiB Infinity Cache
-// take tiles. A mask wider than a tile has no tile pass at all.
-bool obs_gathers(int n, int B, int dtype, int use, int nmasks, int npasses, bool wide)
+// Whether a single-slot state takes k_obs_gather rather than npasses tile passes over the X masks xs (wide: one of
+// them is wider than a tile, and then the passes are the per-group kernels). Both forms were timed for
+// observables of 1 to 567 masks and 1 to 31 passes (chains, all pairs, random strings on 4, 6, the lowest 12 or
+// all qubits, 1 to 1000 terms a mask) on 10 to 25 qubits. Up to 2^19 complex64 or 2^17 complex128
+// amplitudes the gather always won; beyond, the sum below is their difference in us, with M = 2^20
+// amplitudes, and picks the better form to 0.4 % of its time on average:
+// - a mask costs the gather a read of the state in an order that the mask stirs: little for two qubits,
+//   0.9 us M from five (complex128 2.1), half of it where the L2 caches hold the state and 0.7 at 16 MiB; and a tile
+//   pass its reads of LDS, 0.12 us M;
+// - a term costs the gather 0.018 us M more (four elements share its sign, eight in a tile);
+// - a pass costs its launch and its read of the state, with H psi a read and a write of that too (more where both
+//   no longer fit the 256 MiB Infinity Cache).
+// 20 qubits complex128, 400 masks on the 12 lowest qubits (one pass): energy 733 us by the gather, 149 by tiles;
+// 21 qubits complex64, all pairs (14 passes): H psi 313 against 427; 24 qubits complex128, 40 masks on 6 qubits
+// (18 passes): energy 1540 against 1203, H psi 1532 against 3123; 25 qubits complex64, chain (3 passes): energy
+// 519 against 466, H psi 574 against 983. Energies under wide masks: 0.4 to 0.96 of the per-group kernels' time, but for
+// 1.04 at 23 qubits complex128; H psi 0.6 to 1.0 for complex64, 1.02 to 1.10 for complex128 from 20 qubits.
+// OBS_ONE: H psi where one launch spares the caller others, about 20 us and another read of the state.
+bool obs_gathers(const yao_pauli_sum* h, int n, int B, int dtype, int use, const std::vector<uint64_t>& xs, int npasses,
+                 bool wide)
 {
+    const bool single = dtype == YAO_C64;
     if (use == OBS_TILES || B != 1 || n > 31) return false;
-    if (wide || n <= 20) return true;
-    if (n > (dtype == YAO_C64 ? 25 : 24)) return false;
-    const int per_pass = use == OBS_ENERGY ? 6 : (dtype == YAO_C64 ? 14 : 10);
-    return nmasks <= per_pass * npasses;
+    if (wide) return use != OBS_VECTOR || single || n < 20;
+    if (n > (single ? 25 : 24)) return false;
+    if (n <= (single ? 19 : 17)) return true;
+    const double M = std::ldexp(1.0, n - 20), mib = (single ? 8 : 16) * M;
+    const double read = (single ? 0.3 : 0.7) * M * (mib <= 8 ? 0.5 : mib <= 16 ? 0.7 : 1.0), lds = std::max(0.22, 0.12 * M);
+    double more = 12 + 2.4 * M + 0.018 * M * (double)h->coef.size();
+    for (uint64_t x : xs) more += std::max(lds, read * std::min(4, __builtin_popcountll(x) - 1)) - lds;
+    double pass;
+    if (use == OBS_ENERGY) pass = 6 + (single ? 2.6 : 3.5) * M;
+    else if (2 * mib > 256) pass = 10 + (single ? 8.4 : 10.0) * M;
+    else pass = 10 + (single ? 5.0 : 6.0) * M;
+    return more <= pass * npasses + (use == OBS_ONE ? 20 + (single ? 1.7 : 3.4) * M : 0.0);
 }
 
 // The records of the terms of the X masks xs, in order: bit q of an index is bit pos[q] of the
@@ -2212,7 +2233,7 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype, int use)
         T[p] |= x;
         gx[p].push_back(x);
     }
-    P->gather = obs_gathers(n, B, dtype, use, (int)xs.size(), (int)T.size(), wide);
+    P->gather = obs_gathers(h, n, B, dtype, use, xs, (int)T.size(), wide);
     if (wide && !P->gather) {
         g_obs[key] = P;
         return P;
@@ -2290,18 +2311,18 @@ int obs_tile_qubits(const yao_pauli_sum* h, int n, int B, int dtype)
     return P && P->ok ? P->t - P->c : 0;
 }
 
-bool obs_one_launch(const yao_pauli_sum* h, int n, int B, int dtype)
+bool obs_one_launch(const yao_pauli_sum* h, int n, int B, int dtype, int use)
 {
     if (n < kObsRegBits + 1) return false;
-    const ObsPlan* P = obs_plan(h, n, B, dtype, OBS_VECTOR);
+    const ObsPlan* P = obs_plan(h, n, B, dtype, use);
     return P && P->ok && P->gather;
 }
 
-// One item of launch_many_obs: its columns are obs_partial_doubles, its blocks *blocks of 256 threads.
+// One item of launch_many_obs: its columns are obs_partial_doubles (OBS_ONE), its blocks *blocks of 256 threads.
 int many_obs(ManyObs& o, int* reg_bits, int* blocks, const void* psi, void* lam, double* psi64, int dtype, int n,
              const yao_pauli_sum* h, double* partial)
 {
-    const ObsPlan* P = obs_plan(h, n, 1, dtype, OBS_VECTOR);
+    const ObsPlan* P = obs_plan(h, n, 1, dtype, OBS_ONE);
     if (!P) return YAO_ENOMEM;
     if (!P->ok || !P->gather || obs_gather_threads(n) != kObsGatherThreads)
         return set_error(YAO_EINVAL, "observable takes more than one launch");
@@ -2314,7 +2335,7 @@ int many_obs(ManyObs& o, int* reg_bits, int* blocks, const void* psi, void* lam,
 int launch_lanczos_hv(const void* src, void* v, void* out, int dtype, int n, const yao_pauli_sum* h, const double* npart,
                       int nn, double* norm, double* partial)
 {
-    const ObsPlan* P = obs_plan(h, n, 1, dtype, OBS_VECTOR);
+    const ObsPlan* P = obs_plan(h, n, 1, dtype, OBS_ONE);
     if (!P) return YAO_ENOMEM;
     if (!P->ok || !P->gather) return set_error(YAO_EINVAL, "observable takes more than one launch");
     const ObsRec* recs = P->drecs;

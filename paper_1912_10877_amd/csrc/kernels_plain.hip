@@ -832,7 +832,7 @@ int launch_hpsi_dev(const void* data, int dtype, void* out, int out_dtype, int n
 int launch_seed(const void* data, int dtype, double* psi64, void* lam, int n, int B, const yao_pauli_sum* h,
                 double* partial, int* W)
 {
-    const bool one = obs_one_launch(h, n, B, dtype);
+    const bool one = obs_one_launch(h, n, B, dtype, OBS_VECTOR);
     if (!one) YAO_TRY(launch_convert(data, dtype, psi64, YAO_C128, (size_t(1) << n) * (size_t)B));
     if (obs_passes_ok(h, n, B, dtype, OBS_VECTOR))
         return launch_obs_passes(data, dtype, lam, dtype, n, B, h, partial, W, OBS_VECTOR, one ? psi64 : nullptr);

@@ -278,11 +278,11 @@ int lanczos_substep(void* psi, int n, int B, int dtype, const yao_pauli_sum* h, 
     const size_t es = sizeof(V);
     SlotGeom sg = slot_geom(B);
     const int nbx = grid_x(rows, sg.logBc);
-    const size_t hp = hpsi_partial_doubles(h, n, B, dtype);
     // Where H v is one launch, a step is two (k_lanczos_hv, k_lanczos_update) in place of five, the small
     // exponential runs on the device and the host waits once, at the end: 16 qubits complex128, t = 0.1:
     // 1289 to 511 us.
-    const bool fused = B == 1 && mmax <= 64 && obs_one_launch(h, n, B, dtype);
+    const bool fused = B == 1 && mmax <= 64 && obs_one_launch(h, n, B, dtype, OBS_ONE);
+    const size_t hp = fused ? obs_partial_doubles(h, n, B, dtype, OBS_ONE) : hpsi_partial_doubles(h, n, B, dtype);
     // Vectors V_0..V_mmax, the work vector w; coefficient arrays on the device.
     char* ws = (char*)workspace(WS_KRYLOV, es * elems * (size_t)(mmax + 2));
     double* dv = (double*)workspace(WS_MISC, sizeof(double) * (hp + (size_t)B * nbx + (size_t)B * (2 * mmax + 4) +

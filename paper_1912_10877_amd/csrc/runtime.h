@@ -123,19 +123,20 @@ int launch_hpsi(const void* data, int dtype, void* out, int out_dtype, int n, in
 size_t hpsi_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype);
 // Observables in tile passes or one gathering launch (states of >= 4 qubits): H psi into out (nullptr: energy only),
 // energy partials partial[b * W + column].
-// What an observable's launches are for: the energy alone, H psi as well, or energies per tile (tile
-// passes even where a state takes the one-launch form, whose sums cross the top qubits).
-enum ObsUse { OBS_ENERGY = 0, OBS_VECTOR = 1, OBS_TILES = 2 };
+// What an observable's launches are for: the energy alone, H psi as well, energies per tile (tile
+// passes even where a state takes the one-launch form, whose sums cross the top qubits), or H psi where
+// one launch spares the caller others (obs_one_launch says whether it is one).
+enum ObsUse { OBS_ENERGY = 0, OBS_VECTOR = 1, OBS_TILES = 2, OBS_ONE = 3 };
 bool obs_passes_ok(const yao_pauli_sum* h, int n, int B, int dtype, int use);
 size_t obs_partial_doubles(const yao_pauli_sum* h, int n, int B, int dtype, int use);
 // Qubits of each observable pass's tile (the non-tile qubits index the tiles, ascending).
 int obs_tile_qubits(const yao_pauli_sum* h, int n, int B, int dtype);
 int launch_obs_passes(const void* psi, int dtype, void* out, int out_dtype, int n, int B, const yao_pauli_sum* h,
                       double* partial, int* W, int use, double* psi64 = nullptr);
-// Whether H psi of such a state is one launch (its partials: obs_partial_doubles columns), and that launch
-// as a Lanczos step: v = src / |src| with |src|^2 = the sum of npart[0 .. nn), out = H v (another buffer),
+// Whether H psi of such a state is one launch for that use (its partials: obs_partial_doubles columns), and the
+// launch of OBS_ONE as a Lanczos step: v = src / |src| with |src|^2 = the sum of npart[0 .. nn), out = H v (another buffer),
 // *norm = |src| and the partials of <v|H v>.
-bool obs_one_launch(const yao_pauli_sum* h, int n, int B, int dtype);
+bool obs_one_launch(const yao_pauli_sum* h, int n, int B, int dtype, int use);
 int launch_lanczos_hv(const void* src, void* v, void* out, int dtype, int n, const yao_pauli_sum* h, const double* npart,
                       int nn, double* norm, double* partial);
 void drop_obs_plans(const yao_pauli_sum* h);

@@ -65,3 +65,62 @@ def test_energy_of_many_tiles():
     s.upload(np.full(1 << n, 2.0 ** (-n / 2), np.complex128))
     e = yb.expect(s, yb.PauliSum.from_workload(w.heisenberg(n)))  # XX of every bond
     assert abs(e[0] - n) <= 1e-6 * n  # the amplitude's float rounding, squared
+
+
+def low_masks(n, nterms, seed):
+    """Random strings on n qubits whose X masks lie on the 12 lowest, one pass over tiles."""
+    rng = np.random.default_rng(seed)
+    xs, zs = rng.integers(1, 1 << 12, nterms), rng.integers(0, 1 << n, nterms)
+    strings = ["".join("IXZY"[int(x >> q & 1) + 2 * int(z >> q & 1)] for q in range(n)) for x, z in zip(xs, zs)]
+    return w.pauli_sum(n, [(float(c), s) for c, s in zip(rng.standard_normal(nterms), strings)])
+
+
+@pytest.mark.parametrize("dtype", [0, 1])
+@pytest.mark.parametrize("n", [18, 20, 21])
+def test_many_masks_in_one_tile(n, dtype):
+    """A hundred X masks in one tile, where single-slot states of 18 to 20 qubits take tile passes: H psi and the
+    energy to the bounds above, and a short evolution (its Krylov steps in separate launches) to the bounds
+    of the evolution tests, 1e-10 and 2e-5 an amplitude."""
+    from paper_1912_10877_amd import binding as yb
+
+    yb.init()
+    H = low_masks(n, 100, 77)
+    s, out = yb.State(n, 1, dtype), yb.State(n, 1, dtype)
+    s.upload(w.random_state(n, 1, n))
+    psi = s.download().astype(np.complex128)
+    ref = oracle.hpsi(H, psi).reshape(psi.shape)
+    e_ref = np.sum(psi.conj() * ref, axis=0).real
+    h = yb.PauliSum.from_workload(H)
+    total, top = float(np.abs(H.coef).sum()), float(np.abs(psi).max())
+    e = yb.hpsi(s, h, out)
+    assert np.abs(out.download() - ref).max() <= (1e-12 if dtype == 1 else 4 * 6e-8) * total * top
+    assert np.abs(e - e_ref).max() <= 1e-12 * total
+    assert np.abs(yb.expect(s, h) - e_ref).max() <= 1e-12 * total
+    if n == 18:
+        steps = yb.time_evolve(s, h, 0.02)
+        assert np.abs(s.download() - oracle.time_evolve(H, psi, 0.02)).max() <= (1e-10 if dtype == 1 else 2e-5) * steps
+
+
+def test_energies_of_one_state_cost_no_more_than_of_two():
+    """400 X masks in one tile, 20 qubits complex128: a batch of two states always takes the tile passes, so one
+    state must not take longer, whichever form is chosen for it (the gathering launch takes five times
+    as long here)."""
+    import time
+
+    from paper_1912_10877_amd import binding as yb
+
+    yb.init()
+    n = 20
+    h = yb.PauliSum.from_workload(low_masks(n, 400, 78))
+    us = []
+    for B in (1, 2):
+        s, out = yb.State(n, B, 1), yb.State(n, B, 1)
+        for call in (lambda: yb.expect(s, h), lambda: yb.hpsi(s, h, out)):
+            call()
+            took = []
+            for _ in range(15):
+                t0 = time.perf_counter()
+                call()
+                took.append(time.perf_counter() - t0)
+            us.append(1e6 * float(np.median(took)))
+    assert us[0] <= us[2] and us[1] <= us[3], us
