@@ -615,7 +615,9 @@ int build_level(Cache& C, const Unit& U)
                 YAO_TRY(many_pass(items.data() + many_pass_bytes() * k, dir ? *it.bwd : *it.fwd, dir ? bwd_prog(it) : fwd_prog(it),
                                   dir ? it.db : it.df, (int)p, L.dtype, dir ? (void*)psi[in[k]] : it.s->data,
                                   dir ? lam[in[k]] : nullptr, dir ? gp[in[k]] : nullptr, dir ? it.W : 0, &ntiles, &threads, &lds));
-                st.threads = std::max(st.threads, threads);
+                if (k > 0 && threads != st.threads)
+                    return set_error(YAO_EINVAL, "tiles of %d and %d threads in one launch", st.threads, threads);
+                st.threads = threads;
                 st.lds = std::max(st.lds, lds);
                 for (int b = 0; b < ntiles; ++b) blocks.push_back(make_uint2((unsigned)k, (unsigned)b));
             }

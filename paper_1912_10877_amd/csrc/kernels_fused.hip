@@ -882,7 +882,6 @@ __device__ __forceinline__ void pass_fwd(const Args& a, uint64_t tile, unsigned 
     const int t = a.t;
     const int nthr = 1 << (t - RB);
     const int th = threadIdx.x;
-    if (th >= nthr) return;  // a launch over tiles of several sizes
     // LDS: tile | dense block matrices (2 * 256 RP each), sized for this pass.
     VP* lp = (VP*)smem;
     uint4* ldm = (uint4*)(smem + (sizeof(VP) << t));
@@ -1168,7 +1167,6 @@ __device__ __forceinline__ void pass_bwd(const Args& a, uint64_t tile, unsigned 
     const int t = a.t;
     const int nthr = 1 << (t - RB);
     const int th = threadIdx.x;
-    if (th >= nthr) return;  // a launch over tiles of several sizes
     const int c = C0 ? 0 : a.c;
     // LDS: psi | lambda | gradient partials.
     double2* lp = (double2*)smem;
