@@ -44,8 +44,9 @@ std::string U(unsigned long long v)
 // 8-byte rows; the low 4 are those of 16-byte rows) XORed with a column per high bit. The columns were
 // searched so that the tile bits outside a register group, any 2 to 4 bits taken out of 12 (780 of
 // 781 choices), hold 5 whose images are independent: lane_order puts those on the lowest lanes, so
-// that a wave's accesses meet every bank once. With the generic kernels' swizzle and the tile bits in
-// order, 41 % of the LDS cycles of a 25-qubit forward pass were bank conflicts.
+// that a wave's accesses of the tile meet every bank once. 25 qubits, depth 20, complex64, SQ counters of 126
+// passes: 9.9e9 LDS cycles with the generic kernels' swizzle and the tile bits in order, 4.4e9 of them
+// conflicts; 6.9e9 and 2.8e9 now (with the matrices' reads and the loads' and stores' own order).
 uint32_t swz_host(uint32_t e)
 {
     static const uint32_t col[8] = {26, 7, 22, 21, 3, 28, 13, 19};
@@ -248,9 +249,9 @@ std::string tile_code(const Plan& P, const HostPass& pass, int n, std::vector<ui
 // compiled plan runs on the matrix cores instead, as the real 4 x 4 product of v_mfma_f32_4x4x1: a
 // lane's own pair (re p, im p, re q, im q) is its column of B and D, so no amplitude moves, and 4
 // instructions of 8 cycles replace 16 of 4. (Rx-like and diagonal gates cost both the same. Two gates
-// as one complex 4 x 4 product cost the same as two real ones, and counters show the matrix and
-// vector instructions of a SIMD's waves taking turns.) 25 qubits, depth 20: 4.52 to 4.30 ms, now bound
-// by the exchanges through LDS; the 20-qubit sweep 237 to 219 us.
+// as one complex 4 x 4 product cost the same as two real ones.) 25 qubits, depth 20: 4.52 to 4.30 ms, the
+// 20-qubit sweep 237 to 219 us: the passes issue a third of the vector instructions (5.1e9 for 15.2e9 over
+// 126 passes, beside 25e9 cycles of the matrix cores), so issue no longer bounds them.
 std::string gen_forward_pass(const Plan& P, const Program& prog, int p, int n, int dtype, const std::string& name,
                              int* nthr_out, size_t* lds_out)
 {

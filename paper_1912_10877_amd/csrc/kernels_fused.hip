@@ -1536,10 +1536,10 @@ __global__ __launch_bounds__(512) void k_obs_pass(PassArgs a, const ObsRec* __re
     }
 }
 
-// The whole observable in one launch for single-slot states that the L2 caches hold: a thread's
+// The whole observable in one launch for single-slot states (obs_gathers says which): a thread's
 // partners are read from global memory (a wave's partners are one or a few contiguous runs for
-// any mask). Tiles of 2^12 leave most CUs idle on such states (16 tiles at 16 qubits). The launch
-// is bound by the latency of a handful of dependent steps.
+// any mask). Tiles of 2^12 leave most CUs idle on small states (16 tiles at 16 qubits), where the launch
+// is bound by the latency of a handful of dependent steps; on large ones by the reads of the caches.
 constexpr int kObsGatherThreads = 256;
 template <typename RP, typename RO, bool OUT, int RB>
 __device__ __forceinline__ void obs_gather(const vec2_t<RP>* __restrict__ gp, vec2_t<RO>* __restrict__ go, int n,

@@ -1,8 +1,8 @@
 """Run-time compiled forward passes (yao_options.jit) against the oracle: the ansatz workload
 and random one-qubit gate lists with controls on register bits, other tile bits and qubits
 outside the tile, in both dtypes; the compiled kernels read the matrices from the bound
-records, so new angles after compiling must give new results; states of a batch and passes
-with LDS-applied gates keep the generic kernels in the same sweep."""
+records, so new angles after compiling must give new results; passes with LDS-applied gates keep
+the generic kernels in the same sweep (batches have compiled passes of their own)."""
 import numpy as np
 import pytest
 
