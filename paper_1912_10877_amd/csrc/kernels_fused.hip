@@ -18,6 +18,7 @@
 #include <map>
 #include <tuple>
 #include <mutex>
+#include <unordered_map>
 #include <vector>
 
 #include "fused.h"
@@ -2150,10 +2151,30 @@ bool obs_gathers(const yao_pauli_sum* h, int n, int B, int dtype, int use, const
     return more <= pass * npasses + (use == OBS_ONE ? 20 + (single ? 1.7 : 3.4) * M : 0.0);
 }
 
-// The records of the terms of the X masks xs, in order: bit q of an index is bit pos[q] of the
-// thread's coordinates (-1: outside the tile), of which the top rb of nb bits are register bits.
-void obs_records(const yao_pauli_sum* h, const std::vector<uint64_t>& xs, const std::vector<int>& pos, int nb, int rb,
-                 std::vector<ObsRec>& out)
+// The X masks of an observable in order of appearance, and the terms of each.
+struct ObsMasks {
+    std::vector<uint64_t> xs;
+    std::vector<std::vector<int>> terms;
+    explicit ObsMasks(const yao_pauli_sum* h)
+    {
+        std::unordered_map<uint64_t, int> at;
+        for (size_t k = 0; k < h->x.size(); ++k) {
+            const auto e = at.emplace(h->x[k], (int)xs.size());
+            if (e.second) {
+                xs.push_back(h->x[k]);
+                terms.emplace_back();
+            }
+            terms[e.first->second].push_back((int)k);
+        }
+    }
+};
+
+// The records of the terms of some X masks (which: indices into M), in order: bit q of an index is bit pos[q] of
+// the thread's coordinates (-1: outside the tile), of which the top rb of nb bits are register bits. One
+// step a term: a plan per use of an observable of 20000 terms takes a few ms, where a look over all
+// terms for every mask took 50.
+void obs_records(const yao_pauli_sum* h, const ObsMasks& M, const std::vector<int>& which, const std::vector<int>& pos,
+                 int nb, int rb, std::vector<ObsRec>& out)
 {
     auto inside = [&](uint64_t m) {
         uint32_t r = 0;
@@ -2165,12 +2186,12 @@ void obs_records(const yao_pauli_sum* h, const std::vector<uint64_t>& xs, const 
     for (size_t q = 0; q < pos.size(); ++q)
         if (pos[q] < 0) outer |= uint64_t(1) << q;
     const uint32_t own = (1u << (nb - rb)) - 1;
-    const size_t first = out.size();
-    for (uint64_t x : xs) {
+    size_t last = out.size();  // first record of the mask before
+    for (int m : which) {
         const size_t at = out.size();
-        for (size_t k = 0; k < h->coef.size(); ++k) {
-            if (h->x[k] != x) continue;
-            const uint32_t z = inside(h->z[k]), xi = inside(x);
+        const uint32_t xi = inside(M.xs[m]);
+        for (int k : M.terms[m]) {
+            const uint32_t z = inside(h->z[k]);
             const int ny = __builtin_popcountll(h->x[k] & h->z[k]);
             // Every element's source is its own index ^ x: the sign of |x & z| belongs to the term.
             const bool neg = (((ny >> 1) ^ __builtin_popcount(xi & z)) & 1) != 0;
@@ -2187,8 +2208,8 @@ void obs_records(const yao_pauli_sum* h, const std::vector<uint64_t>& xs, const 
         for (size_t k = at; k < out.size(); ++k)
             if (k + 1 == out.size() || (out[k + 1].flags & 15) != (out[k].flags & 15)) out[k].flags |= kObsLast;
         out[at].flags |= kObsFirst;
-        for (size_t k = first; k < at; ++k)
-            if (out[k].x == out[at - 1].x) out[k].xnext = out[at].x;
+        for (size_t k = last; k < at; ++k) out[k].xnext = out[at].x;
+        last = at;
     }
 }
 
@@ -2205,22 +2226,18 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype, int use)
     const int c = lb < 3 ? lb : 3;
     const int tq = std::min(n, kObsMaxTile - c);
     const int L = std::max(0, std::min((dtype == YAO_C64 ? 4 : 3) - c, tq));
-    std::vector<uint64_t> xs;
+    const ObsMasks M(h);
+    const std::vector<uint64_t>& xs = M.xs;
     bool wide = false;
-    for (size_t k = 0; k < h->coef.size(); ++k) {
-        bool seen = false;
-        for (uint64_t x : xs) seen |= x == h->x[k];
-        if (!seen) xs.push_back(h->x[k]);
-        wide |= __builtin_popcountll(h->x[k]) > tq;
-    }
+    for (uint64_t x : xs) wide |= __builtin_popcountll(x) > tq;
     const uint64_t low = L > 0 ? ((uint64_t(1) << L) - 1) : 0;
     ObsPlan* P = new ObsPlan;
     P->c = c;
     P->t = c + tq;
-    std::vector<uint64_t> T;                // qubits of each pass
-    std::vector<std::vector<uint64_t>> gx;  // X masks of each pass
-    for (uint64_t x : xs) {
-        if (wide) break;
+    std::vector<uint64_t> T;           // qubits of each pass
+    std::vector<std::vector<int>> gx;  // X masks of each pass
+    for (size_t m = 0; m < xs.size() && !wide; ++m) {
+        const uint64_t x = xs[m];
         size_t p = 0;
         while (p < T.size() && __builtin_popcountll(T[p] | x) > tq) ++p;
         if (p == T.size()) {
@@ -2229,7 +2246,7 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype, int use)
             gx.emplace_back();
         }
         T[p] |= x;
-        gx[p].push_back(x);
+        gx[p].push_back((int)m);
     }
     P->gather = obs_gathers(h, n, B, dtype, use, xs, (int)T.size(), wide);
     if (wide && !P->gather) {
@@ -2241,7 +2258,9 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype, int use)
         std::vector<int> pos(n);
         for (int q = 0; q < n; ++q) pos[q] = q;
         ObsPass ps;
-        obs_records(h, xs, pos, n, obs_gather_reg_bits(n), hr);
+        std::vector<int> all(xs.size());
+        for (size_t m = 0; m < all.size(); ++m) all[m] = (int)m;
+        obs_records(h, M, all, pos, n, obs_gather_reg_bits(n), hr);
         ps.r1 = (int)hr.size();
         P->passes.push_back(ps);
     }
@@ -2256,7 +2275,7 @@ ObsPlan* obs_plan(const yao_pauli_sum* h, int n, int B, int dtype, int use)
                 ps.tile_qubits.push_back(q);
             }
         ps.r0 = (int)hr.size();
-        obs_records(h, gx[p], pos, P->t, kObsRegBits, hr);
+        obs_records(h, M, gx[p], pos, P->t, kObsRegBits, hr);
         ps.r1 = (int)hr.size();
         P->passes.push_back(ps);
     }
